@@ -20,6 +20,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
+#include <deque>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -69,9 +70,10 @@ struct PendingTiming {
   hipEvent_t a, b;
   double flops;
 };
-constexpr int kNumTimed = 6;
+constexpr int kNumTimed = 8;
 const char *const kTimedKernels[kNumTimed] = {"pi_build_f64", "lu_bordered", "pi_build_mixed",
-                                              "jacobi_apply", "jacobi_pairs", "ldlt_bordered"};
+                                              "jacobi_apply", "jacobi_pairs", "ldlt_bordered",
+                                              "spectral_reduce", "spectral_w"};
 std::mutex g_timing_mutex;
 std::atomic<bool> g_timing{false};
 TimerStat g_stats[kNumTimed];
@@ -687,6 +689,154 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
   status_all.insert(status_all.end(), st.begin(), st.end());
 }
 
+// ---------------------------------------------------------------------------
+// Spectral screening (kernels_spectral.hip): the transition matrix of a system
+// reduced to a band, with the vectors u = V^T b_nm of the call's core states.
+struct Spectral {
+  int np = 0, nb = 0;
+  std::vector<int> column;  // by state: its first vector, or -1
+  DevBuf band, Ut, flag;
+  std::vector<PendingTiming> pending;
+  // host sources of the uploads, kept until the call has synchronised
+  std::vector<int> perm;
+  std::vector<double> diag2;
+  std::deque<std::vector<SpectralTask>> tasks;
+  explicit Spectral(hipStream_t s) : band(s), Ut(s), flag(s) {}
+};
+
+struct SpectralSizes {
+  int pad, np, R, Rp;
+  size_t bytes;  // the most the reduction holds at a time
+};
+
+SpectralSizes spectral_sizes(const ResidentSystem &rs, int n_core) {
+  SpectralSizes z;
+  z.np = (int)round_up(rs.n_ov, SPECTRAL_BAND);
+  z.pad = z.np - rs.n_ov;
+  z.R = n_core * rs.nb;
+  z.Rp = (int)round_up(z.R, SPECTRAL_BAND);
+  const size_t np = z.np, ext = (size_t)z.np + z.Rp;
+  z.bytes = sizeof(double) * (np * ext + (size_t)rs.N * ext + SPECTRAL_BAND * (4 * np + (3 + SPECTRAL_MAX_SPLITS) * ext) +
+                              (np / 16 + 2) * 768 + np * z.R + spectral_gram_parts(z.np) + spectral_xsum_parts(z.np)) +
+            np * (sizeof(int) + sizeof(double)) + spectral_small_bytes() + 8192;
+  return z;
+}
+
+// Whether the W of a call come from the reduced transition matrix.  FP64
+// contour deformation only: the mixed forms are defined by their Pi builds, and
+// a continued fraction magnifies any change of rounding in its nodes.
+bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t batch_bytes) {
+  if (args->precision != GWC_PREC_FP64 || args->wac || std::getenv("GWC_FACTORIZATION")) return false;
+  const SpectralSizes z = spectral_sizes(rs, args->n_core);
+  if (z.bytes > batch_bytes || (long long)z.np + z.Rp > (1 << 20)) return false;
+  // rounding of the reduction, eps max(Delta^2), against the distance of z^2
+  // from the poles, 2 x eta with x at least the smallest transition
+  double max_d = 0.0, min_d = std::numeric_limits<double>::infinity();
+  {
+    double lo = rs.eps[0], hi = rs.eps[0], vlo = rs.eps[rs.no], vhi = rs.eps[rs.no];
+    for (int m = 0; m < rs.no; ++m) lo = std::min(lo, rs.eps[m]), hi = std::max(hi, rs.eps[m]);
+    for (int m = rs.no; m < rs.nb; ++m) vlo = std::min(vlo, rs.eps[m]), vhi = std::max(vhi, rs.eps[m]);
+    max_d = vhi - lo;
+    min_d = vlo - hi;
+  }
+  if (std::numeric_limits<double>::epsilon() * max_d * max_d > 1e-10 * 2.0 * min_d * args->eta) return false;
+  // The times of the two routes for ONE core state, so that a call for several
+  // cores and one for each take the same route.  Reduction: 95 us of dependent
+  // steps a panel and n^3 at 0.044 ps (measured 26 ms at n_ov = 5859, 245 ms at
+  // 16524).  Pi builds: 58 TFLOP/s over 2 N^2 n + 4/3 N^3 a frequency and about
+  // 200 us of dependent factorisation steps per 64 rows of N (measured 0.28 ms
+  // a frequency at N = 1200, n_ov = 5859 and 2.4 ms at 2100, 16524).
+  const double n = rs.n_ov, N = rs.N;
+  const double tasks = args->n_imag + (double)args->n_real * (args->mode == GWC_MODE_FULL ? rs.no : 1) + rs.no;
+  const double t_reduce = 95e-6 * (n / SPECTRAL_BAND) + 4.4e-14 * n * n * n;
+  const double t_build = 200e-6 * std::ceil(N / 64) + tasks * (2.0 * N * N * n + 4.0 / 3.0 * N * N * N) / 58e12;
+  return t_reduce < t_build;
+}
+
+void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int *d_core, Spectral &sp, hipStream_t s) {
+  const int no = rs.no, nv = rs.nv, n = rs.n_ov, N = rs.N;
+  const SpectralSizes z = spectral_sizes(rs, (int)core.size());
+  const int np = z.np;
+  const long long lda = (long long)np + z.Rp;
+  sp.np = np;
+  sp.nb = rs.nb;
+  sp.column.assign(no, -1);
+  for (size_t c = core.size(); c-- > 0;) sp.column[core[c]] = (int)c * rs.nb;
+  // transitions by ascending Delta
+  std::vector<int> &perm = sp.perm;
+  std::vector<double> &diag2 = sp.diag2, delta(n);
+  perm.resize(n);
+  diag2.resize(n);
+  for (int i = 0; i < no; ++i)
+    for (int a = 0; a < nv; ++a) delta[(size_t)i * nv + a] = rs.eps[no + a] - rs.eps[i];
+  for (int k = 0; k < n; ++k) perm[k] = k;
+  std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) { return delta[x] < delta[y]; });
+  for (int k = 0; k < n; ++k) diag2[k] = delta[perm[k]] * delta[perm[k]];
+  DevBuf dperm(s), ddiag(s), dA(s), dV(s), dB(s), dQ(s), dY(s), dY2(s), dX(s), dW(s), dW2(s), dXp(s), dBk(s), dpart(s), dsm(s);
+  const int *d_perm = upload(dperm, perm, s);
+  const double *d_diag2 = upload(ddiag, diag2, s);
+  dA.alloc((size_t)np * lda * sizeof(double));
+  dV.alloc((size_t)N * np * sizeof(double));
+  dB.alloc((size_t)N * z.Rp * sizeof(double));
+  const size_t row = SPECTRAL_BAND * sizeof(double);
+  dQ.alloc(np * row);
+  dY.alloc(np * row);
+  dY2.alloc(np * row);
+  dX.alloc(lda * row);
+  dW.alloc(lda * row);
+  dW2.alloc(lda * row);
+  dXp.alloc(SPECTRAL_MAX_SPLITS * lda * row);
+  dBk.alloc(np * row);
+  dpart.alloc((size_t)std::max(spectral_gram_parts(np), spectral_xsum_parts(np)) * sizeof(double));
+  dsm.alloc(spectral_small_bytes());
+  sp.band.alloc((size_t)(np / 16 + 2) * 768 * sizeof(double));
+  sp.Ut.alloc((size_t)z.R * np * sizeof(double));
+  sp.flag.alloc(2 * sizeof(int));
+  launch_zero_counters(sp.flag.as<int>(), 2, s);
+  launch_spectral_operand(rs.d_Mov.as<double>(), rs.d_eps.as<double>(), d_perm, N, no, nv, z.pad, np, dV.as<double>(), s);
+  launch_spectral_pairs(rs.d_Moo.as<double>(), rs.d_Mov.as<double>(), N, no, nv, d_core, z.R, z.Rp, dB.as<double>(), s);
+  hipEvent_t ea = g_timing ? timing_mark(s) : nullptr;
+  launch_spectral_matrix(dV.as<double>(), np, dB.as<double>(), z.Rp, N, d_diag2, z.pad, dA.as<double>(), lda, s);
+  const SpectralWork w{dQ.as<double>(), {dY.as<double>(), dY2.as<double>()}, dX.as<double>(),
+                       {dW.as<double>(), dW2.as<double>()}, dXp.as<double>(),
+                       dBk.as<double>(), dpart.as<double>(), dsm.p, sp.flag.as<int>(), sp.flag.as<int>() + 1};
+  launch_spectral_reduce(dA.as<double>(), lda, np, z.pad, z.Rp, w, s);
+  launch_spectral_pack(dA.as<double>(), lda, np, z.R, dBk.as<double>(), sp.band.as<double>(), sp.Ut.as<double>(), s);
+  HIPCHECK(hipGetLastError());
+  if (ea) {
+    // V^T V (its half) and V^T b, the reduction of the matrix and of u
+    const double nn = (double)n * n;
+    sp.pending.push_back({6, ea, timing_mark(s), nn * N + 2.0 * N * n * z.R + 4.0 / 3.0 * nn * n + 2.0 * nn * z.R});
+  }
+}
+
+// W of every task from the band (the spectral counterpart of run_screening).
+void spectral_screen(Spectral &sp, const TaskList &tl, int R, double2 *W_out, hipStream_t s) {
+  const size_t T = tl.size();
+  if (T == 0) return;
+  sp.tasks.emplace_back();
+  std::vector<SpectralTask> &tasks = sp.tasks.back();
+  bool real = true;
+  for (size_t t = 0; t < T; ++t) {
+    const double x = tl.z[t].x, y = tl.z[t].y;
+    real = real && x == 0.0;
+    SpectralTask k{(x - y) * (x + y), 2.0 * x * y, tl.out_base[t], tl.out_stride[t], sp.column[tl.n[t]] + std::max(tl.m[t], 0), 1};
+    for (int r = 0; r < R; r += SPECTRAL_MAX_RHS) {
+      SpectralTask q = k;
+      q.out_base += (long long)r * k.out_stride;
+      q.col += r;
+      q.nrhs = std::min(SPECTRAL_MAX_RHS, R - r);
+      tasks.push_back(q);
+    }
+  }
+  DevBuf dt(s);
+  const SpectralTask *d_t = upload(dt, tasks, s);
+  hipEvent_t ea = g_timing ? timing_mark(s) : nullptr;
+  launch_spectral_w(sp.band.as<double>(), sp.Ut.as<double>(), sp.np, d_t, (int)tasks.size(), real, W_out, s);
+  HIPCHECK(hipGetLastError());
+  if (ea) sp.pending.push_back({7, ea, timing_mark(s), (real ? 1.0 : 4.0) * tasks.size() * SPECTRAL_BAND * SPECTRAL_BAND * sp.np});
+}
+
 struct SigmaInputs {
   std::vector<int> core;
   std::vector<double> wi, wwi, wr, vxc;
@@ -934,7 +1084,7 @@ void run_qp_newton(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_
                    const SigmaInputs &in, const double2 *d_Wimag, const double *d_wi,
                    const double *d_wwi, const std::vector<double> &sx, std::vector<double> &E,
                    std::vector<int> &iters, std::vector<int> &status, hipStream_t s,
-                   size_t batch_bytes) {
+                   size_t batch_bytes, Spectral *sp) {
   const gwc_qp_params &q = in.qpp;
   const int nc = args->n_core, ni = args->n_imag, nb = rs.nb;
   E.resize(nc);
@@ -976,7 +1126,8 @@ void run_qp_newton(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_
       HIPCHECK(hipMemcpyAsync(dW.as<double2>() + (size_t)k * nb * ni, d_Wimag + (size_t)idx[k] * nb * ni,
                               (size_t)nb * ni * sizeof(double2), hipMemcpyDeviceToDevice, s));
     dWr.alloc(std::max<size_t>(tr.size(), 1) * sizeof(double2));
-    run_screening(rs, mx, args->precision, tr, 1, dWr.as<double2>(), status, s, batch_bytes);
+    if (sp) spectral_screen(*sp, tr, 1, dWr.as<double2>(), s);
+    else run_screening(rs, mx, args->precision, tr, 1, dWr.as<double2>(), status, s, batch_bytes);
     for (int v : status)
       if (v) fail(GWC_ERR_FACTORIZATION, "exactly singular pivot in the LU of 1 - Pi(z)");
     const int *d_core = upload(dcore, sub.core, s);
@@ -1043,14 +1194,16 @@ size_t predict_sigma_bytes(const ResidentSystem &rs, const gwc_sigma_args *args,
   }
   const size_t fixed = (size_t)nc * rs.nb * ni * sizeof(double2) + t_real * (sizeof(double2) + sizeof(double)) +
                        (size_t)nc * (nr + 1) * 8 * sizeof(double) + (1 << 20);
-  return std::max(pi.bytes, pr.bytes) + fixed;
+  size_t most = std::max(pi.bytes, pr.bytes);
+  if (spectral_route(rs, args, batch_bytes)) most = std::max(most, spectral_sizes(rs, nc).bytes);
+  return most + fixed;
 }
 
-void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *out, hipStream_t s,
-               size_t batch_bytes) {
-  if (!out) fail(GWC_ERR_INVALID_ARG, "NULL out");
-  const SigmaInputs in = check_sigma_args(rs.no, rs.nb, args, out, s);
-  if (batch_bytes == 0) batch_bytes = default_batch_bytes();
+// One evaluation by one of the two routes to W; false when the reduced
+// transition matrix turned out unusable (a panel of dependent columns, a
+// value that is not finite), and the outputs are then to be computed by Pi builds.
+static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const SigmaInputs &in, gwc_sigma_out *out,
+                         hipStream_t s, size_t batch_bytes, bool spectral) {
   const int N = rs.N, nb = rs.nb;
   const int nc = args->n_core, ni = args->n_imag, nr = args->n_real;
   const bool full = args->mode == GWC_MODE_FULL;
@@ -1064,6 +1217,8 @@ void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *ou
   const double *d_wr = upload(dwr, in.wr, s);
   const double *d_vxc = upload(dvxc, in.vxc, s);
   std::vector<int> status;
+  Spectral spec(s), *sp = spectral ? &spec : nullptr;
+  if (sp) spectral_build(rs, in.core, d_core, *sp, s);
 
   // ---- imaginary axis: W_imag[c][m][k]
   DevBuf dWi(s);
@@ -1078,7 +1233,8 @@ void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *ou
         tl.out_base.push_back((long long)c * nb * ni + k);
         tl.out_stride.push_back(ni);
       }
-    run_screening(rs, mx, args->precision, tl, nb, dWi.as<double2>(), status, s, batch_bytes);
+    if (sp) spectral_screen(*sp, tl, nb, dWi.as<double2>(), s);
+    else run_screening(rs, mx, args->precision, tl, nb, dWi.as<double2>(), status, s, batch_bytes);
   }
 
   // ---- residues
@@ -1090,6 +1246,8 @@ void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *ou
   dWr.alloc(std::max<size_t>(tr.size(), 1) * sizeof(double2));
   if (in.wac)
     run_wac(rs, mx, args, in, tr, cj_off, dWi.as<double2>(), dWr.as<double2>(), status, s, batch_bytes);
+  else if (sp)
+    spectral_screen(*sp, tr, 1, dWr.as<double2>(), s);
   else
     run_screening(rs, mx, args->precision, tr, 1, dWr.as<double2>(), status, s, batch_bytes);
   for (int v : status)
@@ -1119,6 +1277,15 @@ void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *ou
   copy_out(out->sigma_c_eps, dse.p, (size_t)nc * 2 * sizeof(double), s);
   copy_out(out->sigma_x, dsx.p, (size_t)nc * sizeof(double), s);
   copy_out(out->e_qp, deq.p, (size_t)nc * sizeof(double), s);
+  int unusable = 0;
+  if (sp) {
+    launch_nonfinite(dWi.as<double>(), (long long)nc * nb * ni * 2, sp->flag.as<int>() + 1, s);
+    launch_nonfinite(dWr.as<double>(), (long long)tr.size() * 2, sp->flag.as<int>() + 1, s);
+    HIPCHECK(hipMemcpyAsync(&unusable, sp->flag.as<int>() + 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipStreamSynchronize(s));
+    timing_resolve(sp->pending);
+    if (unusable) return false;
+  }
   std::vector<double> e_newton;
   std::vector<int> qp_it;
   if (in.qp) {
@@ -1126,11 +1293,22 @@ void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *ou
     HIPCHECK(hipMemcpyAsync(sx.data(), dsx.p, nc * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
     run_qp_newton(rs, mx, args, in, dWi.as<double2>(), d_wi, d_wwi, sx, e_newton, qp_it, status, s,
-                  batch_bytes);
+                  batch_bytes, sp);
+    if (sp) timing_resolve(sp->pending);
     copy_out(out->e_qp_newton, e_newton.data(), (size_t)nc * sizeof(double), s);
     copy_out(out->qp_iterations, qp_it.data(), (size_t)nc * sizeof(int), s);
   }
   HIPCHECK(hipStreamSynchronize(s));
+  return true;
+}
+
+void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *out, hipStream_t s,
+               size_t batch_bytes) {
+  if (!out) fail(GWC_ERR_INVALID_ARG, "NULL out");
+  const SigmaInputs in = check_sigma_args(rs.no, rs.nb, args, out, s);
+  if (batch_bytes == 0) batch_bytes = default_batch_bytes();
+  if (spectral_route(rs, args, batch_bytes) && run_sigma_by(rs, args, in, out, s, batch_bytes, true)) return;
+  (void)run_sigma_by(rs, args, in, out, s, batch_bytes, false);
 }
 
 size_t predict_cumulant_bytes(int n_real, int n_t, int n_out) {

@@ -104,6 +104,45 @@ void launch_assemble(const double2 *W_real, const double *f_task, const int *tas
 
 void launch_nonfinite(const double *x, long long n, int *flag, hipStream_t stream);
 
+// Spectral screening (kernels_spectral.hip): C = diag(Delta^2) + V^T V over the
+// n_ov transitions, reduced once to half-bandwidth SPECTRAL_BAND; each W is a
+// banded elimination.  np = n_ov rounded up to the band (pad = np - n_ov zero
+// rows in front); A is np x lda with the vectors u in the columns from np on,
+// Rp of them (a multiple of 32, the unused ones zero).
+constexpr int SPECTRAL_BAND = 32;
+constexpr int SPECTRAL_MAX_SPLITS = 8;
+constexpr int SPECTRAL_MAX_RHS = 16;
+struct SpectralTask {
+  double z2_re, z2_im;  // z^2
+  long long out_base;
+  int out_stride, col, nrhs;  // vectors col .. col + nrhs - 1, nrhs <= SPECTRAL_MAX_RHS
+};
+struct SpectralWork {  // doubles unless stated
+  double *Q, *Y[2];    // np x SPECTRAL_BAND
+  double *X, *W[2];    // (np + Rp) x SPECTRAL_BAND
+  double *Xpart;       // SPECTRAL_MAX_SPLITS times that
+  double *Bk;          // np x SPECTRAL_BAND: the couplings of the blocks
+  double *part;        // max(spectral_gram_parts, spectral_xsum_parts)
+  void *small;         // spectral_small_bytes
+  int *ticket, *flag;  // one int each, 0 at the start; flag = 1: a dependent panel
+};
+size_t spectral_small_bytes();
+int spectral_gram_parts(int np);
+int spectral_xsum_parts(int np);
+void launch_spectral_operand(const double *M_ov, const double *eps, const int *perm, int n_aux, int n_occ,
+                             int n_virt, int pad, int np, double *V, hipStream_t s);
+void launch_spectral_pairs(const double *M_oo, const double *M_ov, int n_aux, int n_occ, int n_virt,
+                           const int *core, int R, int Rp, double *B, hipStream_t s);
+void launch_spectral_matrix(const double *V, int np, const double *Bp, int Rp, int n_aux, const double *diag2,
+                            int pad, double *A, long long lda, hipStream_t s);
+void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, const SpectralWork &w,
+                            hipStream_t s);
+// band: (np / 16 + 2) x 768; Ut: R x np.
+void launch_spectral_pack(const double *A, long long lda, int np, int R, const double *Bk, double *band,
+                          double *Ut, hipStream_t s);
+void launch_spectral_w(const double *band, const double *Ut, int np, const SpectralTask *tasks, int n_tasks,
+                       bool real, double2 *W_out, hipStream_t s);
+
 // Cumulant tail.
 void launch_cumulant_weights(const double *omega_real, const double *im_sigma, int n_real,
                              double eps_n, double *nu, double *c, double *z_out,

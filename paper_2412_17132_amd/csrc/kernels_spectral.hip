@@ -1,0 +1,1408 @@
+// Screened-interaction elements from one reduction of the transition matrix
+// (FP64).
+//
+// With V[P][ia] = 2 Delta_ia^1/2 M^P_ia and C = diag(Delta^2) + V^T V (the RPA
+// matrix in its symmetric form, frequency independent), the Woodbury identity
+// turns W^c_nm(z) = b^T [(1 - Pi(z))^-1 - 1] b into
+//
+//        W^c_nm(z) = u^T (z^2 - C)^-1 u,      u = V^T b_nm,
+//
+// so every frequency of a call is a shift of the same real symmetric matrix.
+// C is brought once to block-tridiagonal form by orthogonal transformations
+// that are applied to the vectors u as well; each W is then a banded complex
+// symmetric elimination of order n_ov and half-bandwidth SB = 32 instead of an
+// N_aux x N_aux Pi build (2 N^2 n_ov flops) and a factorisation (4/3 N^3):
+// about 8 32^2 n_ov flops.  The reduction costs 4/3 n_ov^3 flops, once a call.
+//
+// Reduction (indices ordered by Delta, so that the large Delta^2 of the core
+// transitions come last and do not spread their rounding over the small ones;
+// SB - n_ov % SB decoupled zero rows in front make the order a multiple of
+// SB).  Per panel P of SB columns with the m rows below its diagonal block, five
+// dependent launches:
+//   panel_q        Q = P L1^-T by rows, with G = P^T P = L1 L1^T from the launch
+//                  before, and partial sums of G2 = Q^T Q = 1 + E;
+//   panel_x        Xq = A22 Q (and u^T Q), the product that reads the matrix; one
+//                  more workgroup meanwhile sums G2, orthonormalises Q1 =
+//                  Q (1 - Phi) and reconstructs the Householder form of Q1:
+//                  Phi = the upper triangle of E, its diagonal halved (1 - Phi
+//                  inverts the Cholesky factor R2 = 1 + Phi of 1 + E to O(E^2);
+//                  where |E| > 1e-8, as in a last square panel, it is factored);
+//                  Q1_top - S = Y1 U without pivoting, S_jj = -sign, T = -U S
+//                  Y1^-T, so that H = 1 - Y T Y^T with Y = (Q1 - [S; 0]) U^-1
+//                  has H^T P = [S R2 L1^T; 0];
+//   panel_xsum     Y = Q M2 - [SU; 0] and X = A22 Y = Xq M2 - A22[:, :SB] SU with
+//                  M2 = (1 - Phi) U^-1, SU = S U^-1, Xq summed over its splits;
+//                  Y^T X, and in the last workgroup E2 = T^T (Y^T X) T / 2;
+//   panel_w        W = X T - Y E2;
+//   panel_update   A22 -= Y W^T + W Y^T (tiles on or above the diagonal, each
+//                  written with its mirror), u -= Y (u^T Y T)^T; the tiles that
+//                  hold the next panel also form its G, and the last of them
+//                  the Cholesky factor, while the others go on.
+// Panels go in pairs: after the first of a pair only the columns of the second
+// (and u's rows beside them) are updated, the second takes what is missing of
+// A22 in its products (A22 Y = A Y - Ya (Wa^T Y) - Wa (Ya^T Y)), and one update
+// with both halves its passes over the matrix.
+// Two Cholesky passes orthogonalise a panel of condition up to 3e6; beyond that
+// (dependent columns) a flag is raised and the caller screens by Pi builds.
+#include <algorithm>
+
+#include "gwc_internal.h"
+
+namespace gwc {
+
+namespace {
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+constexpr int SB = SPECTRAL_BAND;
+constexpr int SLD = SB + 1;   // LDS row stride of 32-wide rows
+constexpr int PROWS = 256;    // panel rows per workgroup of panel_gram
+constexpr int XROWS = 128;    // rows per workgroup of panel_xsum
+constexpr int UT = 64;        // tile of the rank update and the transition matrix
+constexpr int ULD = SB + 2;   // LDS row stride of its operands (no bank conflicts)
+// Rows from which panels go in pairs: the second panel's own products cost about
+// 60 us, half a pass over the matrix more than that from here on (whole reduction
+// at order 16524 in pairs down to 7168 rows: 295 -> 258 ms; at 5859 in pairs
+// throughout: 36 -> 38 ms).
+constexpr int PAIR_ROWS = 7168;
+constexpr int Q_PART = 768, Q_PART2 = 768 + 2 * SB * SB;  // partial sums of panel_q
+
+// 32 x 32 matrices and 32-vectors one panel step hands to the next.
+struct PanelSmall {
+  double R1[SB * SB], rd1[SB];    // L1^T, reciprocal diagonal
+  double M2[SB * SB], SU[SB * SB];
+  double T[SB * SB], E2[SB * SB];
+  double V1[SB * SB], V2[SB * SB];  // Wa^T Y, Ya^T Y of a pair's second panel
+};
+
+__device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ double bcast(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+// Orders a wave's LDS accesses across its lanes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Values that the workgroups of one launch hand to the last of them: written
+// through to memory and read past the caches of the reader's XCD, so that no
+// cache has to be flushed or invalidated around them.
+__device__ __forceinline__ void put_through(double *p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get_through(const double *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// True in exactly one workgroup of `count`, the one that arrives last: what the
+// others wrote through is then in memory (every wave has waited for its stores
+// before the workgroup's arrival).  The ticket is left at 0.
+__device__ __forceinline__ bool last_arrival(int *ticket, int count, int *shared_flag) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int old = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *shared_flag = old == count - 1;
+    if (old == count - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  return *shared_flag != 0;
+}
+
+// 1 / x and 1 / sqrt(x) by Newton steps from the hardware's estimates (2^-14
+// and better): two steps reach rounding, and their chain is short.
+__device__ __forceinline__ double fast_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ double fast_rsqrt(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
+}
+
+// Tile (wave / 2, wave % 2) of the 32 x 32 product op(A) op(B) of matrices in
+// LDS; element r of the result is [4 r + lk][li] of the tile.
+template <bool TA, bool TB>
+__device__ __forceinline__ d4 prod32(const double (*A)[SLD], const double (*B)[SLD], int wave, int li, int lk) {
+  const int i = 16 * (wave >> 1) + li, j = 16 * (wave & 1) + li;
+  d4 x{0.0, 0.0, 0.0, 0.0}, y = x;
+#pragma unroll
+  for (int s = 0; s < 8; s += 2) {
+    const int k = 4 * s + lk;
+    x = mfma(TA ? A[k][i] : A[i][k], TB ? B[j][k] : B[k][j], x);
+    y = mfma(TA ? A[k + 4][i] : A[i][k + 4], TB ? B[j][k + 4] : B[k + 4][j], y);
+  }
+  return x + y;
+}
+
+// sum_w p[w stride], in order, with up to 16 loads in flight.
+__device__ __forceinline__ double ordered_sum(const double *p, long long stride, int count) {
+  double x = 0.0;
+  for (int w0 = 0; w0 < count; w0 += 16) {
+    double v[16];
+#pragma unroll
+    for (int w = 0; w < 16; ++w) v[w] = get_through(p + (long long)min(w0 + w, count - 1) * stride);
+#pragma unroll
+    for (int w = 0; w < 16; ++w) x += w0 + w < count ? v[w] : 0.0;
+  }
+  return x;
+}
+
+// Cholesky factor of the symmetric 32 x 32 G in place (lower triangle), by one
+// wave: lane i holds row i, eight columns at a time in registers; a step's
+// column is broadcast lane by lane.  True when a pivot is not above 1e-13 of
+// its diagonal element.
+__device__ bool chol32(double (*G)[SLD], double *rd, int lane) {
+  const int i = lane & (SB - 1);
+  const double gd = G[i][i];
+  bool bad = false;
+#pragma unroll 1
+  for (int kb = 0; kb < SB; kb += 8) {
+    double p[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) p[c] = G[i][kb + c];
+#pragma unroll 4
+    for (int t = 0; t < kb; ++t) {
+      const double l = G[i][t];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) p[c] = fma(-l, bcast(l, kb + c), p[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      double d = bcast(p[c], kb + c);
+      if (!(d > 1e-13 * bcast(gd, kb + c))) {
+        bad = true;
+        d = 1.0;
+      }
+      const double r = fast_rsqrt(d);
+      const double l = p[c] * r;
+      p[c] = l;
+      if (i == kb + c) rd[kb + c] = r;
+#pragma unroll
+      for (int e = c + 1; e < 8; ++e) p[e] = fma(-l, bcast(l, kb + e), p[e]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (lane < SB) G[i][kb + c] = i >= kb + c ? p[c] : 0.0;
+  }
+  return bad;
+}
+
+// X = L^-1 (lower triangular) of a Cholesky factor, by one wave: lane i holds
+// row i of X^T, i.e. column i of X, and takes L's rows by broadcast.
+__device__ void invert_lower32(const double (*L)[SLD], const double *rd, double (*XT)[SLD], int lane) {
+  const int i = lane & (SB - 1);
+#pragma unroll 1
+  for (int j = 0; j < SB; ++j) {
+    double x = i == j ? 1.0 : 0.0;
+    for (int k = 0; k < j; ++k) x = fma(-L[j][k], XT[i][k], x);
+    if (lane < SB) XT[i][j] = j >= i ? x * rd[j] : 0.0;
+    wave_sync();
+  }
+}
+
+// H - S = Y1 U without pivoting, S_jj = -sign of the pivot (so |U_jj| >= 1 for
+// orthonormal columns), in place; returns lane j's S_jj.
+__device__ double lu32(double (*H)[SLD], double *rdu, int lane) {
+  const int i = lane & (SB - 1);
+  double mysign = 1.0;
+#pragma unroll 1
+  for (int kb = 0; kb < SB; kb += 8) {
+    double p[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) p[c] = H[i][kb + c];
+#pragma unroll 4
+    for (int t = 0; t < kb; ++t) {
+      const double l = i > t ? H[i][t] : 0.0;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) p[c] = fma(-l, bcast(p[c], t), p[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int t = kb + c;
+      const double x = bcast(p[c], t);
+      const double s = x >= 0.0 ? -1.0 : 1.0;
+      const double inv = fast_rcp(x - s);
+      const double l = i > t ? p[c] * inv : 0.0;
+      if (i == t) {
+        mysign = s;
+        rdu[t] = inv;
+        p[c] = x - s;
+      } else if (i > t) {
+        p[c] = l;
+      }
+#pragma unroll
+      for (int e = c + 1; e < 8; ++e) p[e] = fma(-l, bcast(p[e], t), p[e]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (lane < SB) H[i][kb + c] = p[c];
+  }
+  return mysign;
+}
+
+// X = U^-1 (upper triangular, U in H on and above the diagonal), by one wave:
+// lane i holds row i of X, eight columns at a time, U's rows by broadcast.
+__device__ void invert_upper32(const double (*H)[SLD], const double *rdu, double (*X)[SLD], int lane) {
+  const int i = lane & (SB - 1);
+#pragma unroll 1
+  for (int jb = 0; jb < SB; jb += 8) {
+    double p[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) p[c] = i == jb + c ? 1.0 : 0.0;
+#pragma unroll 4
+    for (int t = 0; t < jb; ++t) {
+      const double x = X[i][t];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) p[c] = fma(-x, H[t][jb + c], p[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      p[c] = jb + c >= i ? p[c] * rdu[jb + c] : 0.0;
+#pragma unroll
+      for (int e = c + 1; e < 8; ++e) p[e] = fma(-p[c], H[jb + c][jb + e], p[e]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (lane < SB) X[i][jb + c] = p[c];
+  }
+}
+
+// T = -U S Y1^-T (upper triangular) from lu32's factors in H.
+__device__ void tfactor32(const double (*H)[SLD], double (*T)[SLD], double mysign, int lane) {
+  const int i = lane & (SB - 1);
+#pragma unroll 1
+  for (int jb = 0; jb < SB; jb += 8) {
+    double p[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) p[c] = jb + c >= i ? -H[i][jb + c] * bcast(mysign, jb + c) : 0.0;
+#pragma unroll 4
+    for (int t = 0; t < jb; ++t) {
+      const double x = T[i][t], y = H[i][t];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) p[c] = fma(-x, bcast(y, jb + c), p[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const double y = H[i][jb + c];
+#pragma unroll
+      for (int e = c + 1; e < 8; ++e) p[e] = fma(-p[c], bcast(y, jb + e), p[e]);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (lane < SB) T[i][jb + c] = p[c];
+  }
+}
+
+}  // namespace
+
+// V[P][pad + k] = 2 sqrt(Delta_ia) M^P_ia, ia = perm[k]; zero for the `pad`
+// columns in front.
+__global__ void __launch_bounds__(256)
+spectral_operand_kernel(const double *__restrict__ M_ov, const double *__restrict__ eps,
+                        const int *__restrict__ perm, int n_aux, int n_occ, int n_virt, int pad,
+                        int np, double *__restrict__ V) {
+  const int n_ov = n_occ * n_virt;
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= np) return;
+  int ia = 0;
+  double sd = 0.0;
+  if (k >= pad) {
+    ia = perm[k - pad];
+    const int i = ia / n_virt, a = ia - i * n_virt;
+    sd = 2.0 * sqrt(eps[n_occ + a] - eps[i]);
+  }
+  for (int P = blockIdx.y; P < n_aux; P += gridDim.y)
+    V[(long long)P * np + k] = k >= pad ? sd * M_ov[(long long)P * n_ov + ia] : 0.0;
+}
+
+// B[P][c n_basis + m] = M^P_nm for the c-th core state n, zero-padded to Rp columns.
+__global__ void __launch_bounds__(256)
+spectral_pairs_kernel(const double *__restrict__ M_oo, const double *__restrict__ M_ov, int n_aux, int n_occ,
+                      int n_virt, const int *__restrict__ core, int R, int Rp, double *__restrict__ B) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= Rp) return;
+  const int nb = n_occ + n_virt, c = r / nb, m = r - c * nb, n = r < R ? core[c] : 0;
+  for (int P = blockIdx.y; P < n_aux; P += gridDim.y) {
+    const long long row = (long long)P * n_occ + n;
+    B[(long long)P * Rp + r] = r >= R ? 0.0 : (m < n_occ ? M_oo[row * n_occ + m] : M_ov[row * n_virt + m - n_occ]);
+  }
+}
+
+// Workgroup -> tile (i, j), i <= j < nt, of a triangle of tiles: row a and row
+// nt - 1 - a share nt + 1 consecutive workgroups.
+__device__ __forceinline__ bool triangle_tile(int wg, int nt, int &i, int &j) {
+  const int a = wg / (nt + 1), b = wg - a * (nt + 1);
+  if (b < nt - a) {
+    i = a;
+    j = a + b;
+  } else {
+    i = nt - 1 - a;
+    j = i + (b - (nt - a));
+    if (i == a) return false;
+  }
+  return true;
+}
+static unsigned triangle_tiles(int nt) { return (unsigned)((nt + 1) / 2) * (unsigned)(nt + 1); }
+
+// out[i][j] = sum_P A[P][i] B[P][j], 64 x 64 tiles, one 32 x 32 quadrant per
+// wave on MFMA; the operands are rows of A and B (16 consecutive doubles a
+// quarter wave), read through the L1.  SYM: A = B, tiles i <= j with their
+// mirror, and diag2[i - pad] is added on the diagonal.  Sizes are multiples of 32.
+template <bool SYM>
+__global__ void __launch_bounds__(256)
+spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__restrict__ B, int ldb,
+                     int M, int N, int K, const double *__restrict__ diag2, int pad,
+                     double *__restrict__ out, long long ldo) {
+  int ti, tj;
+  if (SYM) {
+    if (!triangle_tile(blockIdx.x, (M + UT - 1) / UT, ti, tj)) return;
+  } else {
+    const int nj = (N + UT - 1) / UT;
+    ti = blockIdx.x / nj;
+    tj = blockIdx.x - ti * nj;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int i0 = ti * UT + (wave >> 1) * 32, j0 = tj * UT + (wave & 1) * 32;
+  if (i0 >= M || j0 >= N) return;  // the whole wave
+  d4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  const double *pa = A + i0 + li, *pb = B + j0 + li;
+  int k = 0;
+#pragma unroll 4
+  for (; k + 4 <= K; k += 4) {
+    const double *ra = pa + (long long)(k + lk) * lda, *rb = pb + (long long)(k + lk) * ldb;
+    const double a0 = ra[0], a1 = ra[16], b0 = rb[0], b1 = rb[16];
+    acc[0][0] = mfma(a0, b0, acc[0][0]);
+    acc[0][1] = mfma(a0, b1, acc[0][1]);
+    acc[1][0] = mfma(a1, b0, acc[1][0]);
+    acc[1][1] = mfma(a1, b1, acc[1][1]);
+  }
+  if (k < K) {
+    const bool in = k + lk < K;
+    const double *ra = pa + (long long)(in ? k + lk : k) * lda, *rb = pb + (long long)(in ? k + lk : k) * ldb;
+    const double a0 = in ? ra[0] : 0.0, a1 = in ? ra[16] : 0.0, b0 = in ? rb[0] : 0.0, b1 = in ? rb[16] : 0.0;
+    acc[0][0] = mfma(a0, b0, acc[0][0]);
+    acc[0][1] = mfma(a0, b1, acc[0][1]);
+    acc[1][0] = mfma(a1, b0, acc[1][0]);
+    acc[1][1] = mfma(a1, b1, acc[1][1]);
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = i0 + 16 * a + 4 * r + lk, j = j0 + 16 * b + li;
+        double x = acc[a][b][r];
+        if (SYM && i == j && i >= pad) x += diag2[i - pad];
+        out[(long long)i * ldo + j] = x;
+        if (SYM && ti != tj) out[(long long)j * ldo + i] = x;
+      }
+}
+
+// Sum of the per-wave Gram tiles (0,0), (0,1), (1,1) through LDS: element
+// q 256 + tid of the three tiles goes to out(q, value).
+template <class F>
+__device__ __forceinline__ void gram_combine(double *buf, const d4 &g00, const d4 &g01, const d4 &g11, F &&out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int o = wave * 768 + (4 * r + lk) * 16 + li;
+    buf[o] = g00[r];
+    buf[o + 256] = g01[r];
+    buf[o + 512] = g11[r];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int e = q * 256 + tid;
+    out(e, ((buf[e] + buf[768 + e]) + buf[1536 + e]) + buf[2304 + e]);
+  }
+}
+
+// The symmetric 32 x 32 matrix of `count` partial sums; a unit diagonal for
+// the inactive columns bw ..
+__device__ __forceinline__ void gram_collect(const double *part, int stride, int count, int bw, double (*G)[SLD]) {
+  const int tid = threadIdx.x, i = tid >> 4, j = tid & 15;
+  const double s0 = ordered_sum(part + tid, stride, count), s1 = ordered_sum(part + 256 + tid, stride, count),
+               s2 = ordered_sum(part + 512 + tid, stride, count);
+  G[i][j] = (i == j && i >= bw) ? 1.0 : s0;
+  G[i][16 + j] = s1;
+  G[16 + j][i] = s1;
+  G[16 + i][16 + j] = (i == j && 16 + i >= bw) ? 1.0 : s2;
+}
+
+// G = L1 L1^T by one workgroup; buf holds SB SLD doubles.
+__device__ void panel_factor(const double *part, int count, int bw, double *buf, PanelSmall *sm, int *flag) {
+  __shared__ double rdsh[SB];
+  double(*G)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
+  const int tid = threadIdx.x;
+  gram_collect(part, 768, count, bw, G);
+  __syncthreads();
+  if (tid < 64) {
+    const bool bad = chol32(G, rdsh, tid);
+    if (bad && tid == 0) *flag = 1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid;
+    sm->R1[e] = G[e % SB][e / SB];
+  }
+  if (tid < SB) sm->rd1[tid] = rdsh[tid];
+}
+
+// G of the first panel (m rows from P, `bw` active columns; the others count as
+// zero) and its factor: 256 rows per workgroup.
+__global__ void __launch_bounds__(PROWS)
+panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, int bw, PanelSmall *__restrict__ sm,
+                  double *part, int *__restrict__ ticket, int *__restrict__ flag) {
+  __shared__ double buf[PROWS * SLD];
+  __shared__ int last;
+  double(*S)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const int row0 = blockIdx.x * PROWS;
+#pragma unroll 8
+  for (int it = 0; it < SB; ++it) {
+    const int e = it * PROWS + tid, r = e / SB, c = e % SB;
+    S[r][c] = (row0 + r < m && c < bw) ? P[(long long)(row0 + r) * ldp + c] : 0.0;
+  }
+  __syncthreads();
+  d4 g00{0.0, 0.0, 0.0, 0.0}, g01 = g00, g11 = g00;
+#pragma unroll 4
+  for (int s = 0; s < 16; ++s) {
+    const int k = 64 * wave + 4 * s + lk;
+    const double a0 = S[k][li], a1 = S[k][16 + li];
+    g00 = mfma(a0, a0, g00);
+    g01 = mfma(a0, a1, g01);
+    g11 = mfma(a1, a1, g11);
+  }
+  __syncthreads();
+  gram_combine(buf, g00, g01, g11, [&](int e, double v) { put_through(part + (long long)blockIdx.x * 768 + e, v); });
+  if (last_arrival(ticket, gridDim.x, &last)) panel_factor(part, gridDim.x, bw, buf, sm, flag);
+}
+
+// Q = P L1^-T, one row per thread, and the partial sums of Q^T Q; for a pair's
+// second panel also of Wa^T Q and Ya^T Q.
+template <bool SECOND>
+__global__ void __launch_bounds__(PROWS)
+panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const PanelSmall *__restrict__ sm,
+               const double *__restrict__ Ya, const double *__restrict__ Wa, double *__restrict__ Q,
+               double *__restrict__ part) {
+  __shared__ double buf[PROWS * SLD];
+  double(*S)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const int row0 = blockIdx.x * PROWS;
+#pragma unroll 8
+  for (int it = 0; it < SB; ++it) {
+    const int e = it * PROWS + tid, r = e / SB, c = e % SB;
+    S[r][c] = (row0 + r < m && c < bw) ? P[(long long)(row0 + r) * ldp + c] : 0.0;
+  }
+  __syncthreads();
+  double q[SB];
+#pragma unroll
+  for (int j = 0; j < SB; ++j) q[j] = S[tid][j];
+#pragma unroll
+  for (int j = 0; j < SB; ++j) {
+    q[j] *= sm->rd1[j];
+#pragma unroll
+    for (int k = j + 1; k < SB; ++k) q[k] = fma(-q[j], sm->R1[j * SB + k], q[k]);
+  }
+#pragma unroll
+  for (int j = 0; j < SB; ++j) S[tid][j] = q[j];
+  __syncthreads();
+#pragma unroll 8
+  for (int it = 0; it < SB; ++it) {
+    const int e = it * PROWS + tid, r = e / SB, c = e % SB;
+    if (row0 + r < m) Q[(long long)row0 * SB + e] = S[r][c];
+  }
+  d4 g00{0.0, 0.0, 0.0, 0.0}, g01 = g00, g11 = g00;
+#pragma unroll 4
+  for (int s = 0; s < 16; ++s) {
+    const int k = 64 * wave + 4 * s + lk;
+    const double a0 = S[k][li], a1 = S[k][16 + li];
+    g00 = mfma(a0, a0, g00);
+    g01 = mfma(a0, a1, g01);
+    g11 = mfma(a1, a1, g11);
+  }
+  constexpr int PART = SECOND ? Q_PART2 : Q_PART;
+  double *o = part + (long long)blockIdx.x * PART;
+  d4 c[2][2][2];
+  if (SECOND) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const double *Z = (p ? Ya : Wa) + (long long)row0 * SB;
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) c[p][a][b] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+      for (int s = 0; s < 16; ++s) {
+        const int k = 64 * wave + 4 * s + lk;
+        const bool in = row0 + k < m;
+        const double *z = Z + (long long)(in ? k : 0) * SB + li;
+        const double z0 = in ? z[0] : 0.0, z1 = in ? z[16] : 0.0, q0 = S[k][li], q1 = S[k][16 + li];
+        c[p][0][0] = mfma(z0, q0, c[p][0][0]);
+        c[p][0][1] = mfma(z0, q1, c[p][0][1]);
+        c[p][1][0] = mfma(z1, q0, c[p][1][0]);
+        c[p][1][1] = mfma(z1, q1, c[p][1][1]);
+      }
+    }
+  }
+  __syncthreads();
+  gram_combine(buf, g00, g01, g11, [&](int e, double v) { o[e] = v; });
+  if (SECOND) {
+    double *red = buf + 4 * 768;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            red[wave * SB * SB + (16 * a + 4 * r + lk) * SB + 16 * b + li] = c[p][a][b][r];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int e = q * 256 + tid;
+        o[768 + p * SB * SB + e] = ((red[e] + red[SB * SB + e]) + red[2 * SB * SB + e]) + red[3 * SB * SB + e];
+      }
+      __syncthreads();
+    }
+  }
+}
+
+
+// From G2's partial sums to M2, SU, T and the block's coupling Bk = S R2 L1^T
+// (see the head of this file), by one workgroup, and V1, V2 of a pair's second
+// panel; buf holds 4 SB SLD + SB doubles.
+template <bool SECOND>
+__device__ void panel_reconstruct(const double *__restrict__ Q, const double *part, int count, int bw,
+                                  const double *__restrict__ Ya, const double *__restrict__ Wa, double *buf,
+                                  PanelSmall *__restrict__ sm, int *flag, double *__restrict__ Bk) {
+  constexpr int PART = SECOND ? Q_PART2 : Q_PART;
+  __shared__ double rdsh[SB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+  double(*G)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
+  double(*H)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + SB * SLD);
+  double(*T)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + 2 * SB * SLD);
+  double(*L)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + 3 * SB * SLD);
+  double *sg = buf + 4 * SB * SLD;
+  double q0[4], r1[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid;
+    q0[q] = Q[e];
+    r1[q] = sm->R1[e];
+  }
+  gram_collect(part, PART, count, bw, G);
+  __syncthreads();
+  int off = 0;
+  double phi[4], r2[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid, i = e / SB, j = e % SB;
+    const double x = G[i][j] - (i == j ? 1.0 : 0.0);
+    off |= !(fabs(x) <= 1e-8);
+    phi[q] = i < j ? x : (i == j ? 0.5 * x : 0.0);
+    r2[q] = phi[q] + (i == j ? 1.0 : 0.0);
+  }
+  if (__syncthreads_or(off)) {
+    if (wave == 0) {
+      const bool bad = chol32(G, rdsh, lane);
+      if (bad && lane == 0) *flag = 1;
+      wave_sync();
+      invert_lower32(G, rdsh, T, lane);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = q * 256 + tid, i = e / SB, j = e % SB;
+      phi[q] = (i == j ? 1.0 : 0.0) - T[i][j];  // T = L2^-T
+      r2[q] = i <= j ? G[j][i] : 0.0;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid, i = e / SB, j = e % SB;
+    T[i][j] = phi[q];
+    G[i][j] = r2[q];
+    H[i][j] = q0[q];
+    L[i][j] = r1[q];
+  }
+  __syncthreads();
+  const int i0 = 16 * (wave >> 1) + lk, j0 = 16 * (wave & 1) + li;  // of this lane's product elements
+  const d4 h = prod32<false, false>(H, T, wave, li, lk);
+  const d4 b = prod32<false, false>(G, L, wave, li, lk);  // S times the coupling, S not yet known
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) H[i0 + 4 * r][j0] -= h[r];
+  __syncthreads();
+  // wave 0: S, Y1 and U, then T; wave 1: U^-1
+  if (wave == 0) {
+    const double mysign = lu32(H, rdsh, lane);
+    if (lane < SB) sg[lane] = mysign;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid;
+    L[e / SB][e % SB] = phi[q];
+  }
+  __syncthreads();
+  if (wave == 0) tfactor32(H, T, sg[lane & (SB - 1)], lane);
+  if (wave == 1) invert_upper32(H, rdsh, G, lane);
+  __syncthreads();
+  const d4 pu = prod32<false, false>(L, G, wave, li, lk);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = i0 + 4 * r, j = j0, e = i * SB + j;
+    sm->M2[e] = j < bw ? G[i][j] - pu[r] : 0.0;
+    sm->SU[e] = j < bw ? sg[i] * G[i][j] : 0.0;
+    sm->T[e] = (i < bw && j < bw) ? T[i][j] : 0.0;
+    // column j of the panel is column SB - bw + j of its block
+    if (j < bw) Bk[i * SB + SB - bw + j] = i <= j ? sg[i] * b[r] : 0.0;
+    else Bk[i * SB + j - bw] = 0.0;
+  }
+  if (SECOND) {
+    // V = (Z^T Q) M2 - Z_top^T SU for Z = Wa, Ya: M2 in G, SU in H
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 4 * r;
+      H[i][j0] = sg[i] * G[i][j0];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) G[i0 + 4 * r][j0] -= pu[r];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const double *Z = p ? Ya : Wa;
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int e = q * 256 + tid;
+        T[e / SB][e % SB] = ordered_sum(part + 768 + p * SB * SB + e, PART, count);
+        L[e / SB][e % SB] = Z[e];
+      }
+      __syncthreads();
+      const d4 v = prod32<false, false>(T, G, wave, li, lk), w = prod32<true, false>(L, H, wave, li, lk);
+      double *V = p ? sm->V2 : sm->V1;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) V[(i0 + 4 * r) * SB + j0] = v[r] - w[r];
+    }
+  }
+}
+
+// Xq = A22^T Q over the columns from A (A22's own, then u's): workgroup
+// (32 columns, split s), its four waves on consecutive parts of the split's
+// rows, summed in order.  A's rows are read 16 doubles a quarter wave.
+// Workgroup 0 does the panel's small matrices instead: about 25 us of
+// dependent steps, hidden behind the product.
+template <bool SECOND>
+__global__ void __launch_bounds__(256)
+panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int bw, int splits,
+               const double *__restrict__ Q, double *__restrict__ Xpart, const double *__restrict__ part,
+               int parts2, const double *__restrict__ Ya, const double *__restrict__ Wa,
+               PanelSmall *__restrict__ sm, int *__restrict__ flag, double *__restrict__ Bk) {
+  __shared__ double buf[4 * SB * SLD + SB];
+  if (blockIdx.x == 0) {
+    panel_reconstruct<SECOND>(Q, part, parts2, bw, Ya, Wa, buf, sm, flag, Bk);
+    return;
+  }
+  double(*red)[SB * SB] = reinterpret_cast<double(*)[SB * SB]>(buf);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const int nx = mx / SB, split = (blockIdx.x - 1) / nx, c0 = (blockIdx.x - 1 - split * nx) * SB;
+  const int nkb = m / SB, parts = 4 * splits, w = 4 * split + wave;
+  const int k0 = (int)((long long)nkb * w / parts) * SB, k1 = (int)((long long)nkb * (w + 1) / parts) * SB;
+  d4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  const double *pa = A + (long long)(k0 + lk) * lda + c0 + li;
+  const double *py = Q + (long long)(k0 + lk) * SB + li;
+  for (int k = k0; k < k1; k += 32) {
+    double a0[8], a1[8], y0[8], y1[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      a0[s] = pa[(long long)(4 * s) * lda];
+      a1[s] = pa[(long long)(4 * s) * lda + 16];
+      y0[s] = py[4 * s * SB];
+      y1[s] = py[4 * s * SB + 16];
+    }
+    pa += 32 * lda;
+    py += 32 * SB;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      acc[0][0] = mfma(a0[s], y0[s], acc[0][0]);
+      acc[0][1] = mfma(a0[s], y1[s], acc[0][1]);
+      acc[1][0] = mfma(a1[s], y0[s], acc[1][0]);
+      acc[1][1] = mfma(a1[s], y1[s], acc[1][1]);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][(16 * a + 4 * r + lk) * SB + 16 * b + li] = acc[a][b][r];
+  __syncthreads();
+  double *o = Xpart + ((long long)split * mx + c0) * SB;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid;
+    o[e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+  }
+}
+
+// Y, X and E2 (see the head of this file), 128 rows per workgroup, 32 a wave.
+template <bool SECOND>
+__global__ void __launch_bounds__(256)
+panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__restrict__ A, long long lda, int m,
+                  int mx, const double *__restrict__ Q, const double *__restrict__ Ya,
+                  const double *__restrict__ Wa, const PanelSmall *__restrict__ sm_in, PanelSmall *__restrict__ sm,
+                  double *__restrict__ X, double *__restrict__ Y, double *part,
+                  int *__restrict__ ticket) {
+  __shared__ double buf[2 * XROWS * SLD];
+  __shared__ int last;
+  double(*Xs)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
+  double(*Ys)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + XROWS * SLD);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const int row0 = blockIdx.x * XROWS;
+#pragma unroll 4
+  for (int it = 0; it < XROWS * SB / 256; ++it) {
+    const int e = it * 256 + tid, r = e / SB, c = e % SB;
+    const long long o = row0 + r < mx ? (long long)row0 * SB + e : 0;
+    double v[SPECTRAL_MAX_SPLITS], x = 0.0;
+#pragma unroll
+    for (int s = 0; s < SPECTRAL_MAX_SPLITS; ++s) v[s] = Xpart[(long long)min(s, splits - 1) * mx * SB + o];
+    const double y = Q[row0 + r < m ? o : 0];
+#pragma unroll
+    for (int s = 0; s < SPECTRAL_MAX_SPLITS; ++s) x += s < splits ? v[s] : 0.0;
+    Xs[r][c] = x;
+    Ys[r][c] = row0 + r < m ? y : 0.0;
+  }
+  // this wave's 32 rows: m, mx are multiples of 32
+  const int wr = 32 * wave, row = row0 + wr;
+  const bool in = row < mx, mat = row < m;
+  double st[2][8];  // the first SB rows of A22 at this wave's columns
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) st[a][s] = in ? -A[(long long)(4 * s + lk) * lda + row + 16 * a + li] : 0.0;
+  double m2[2][8], su[2][8];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      m2[b][s] = sm_in->M2[(4 * s + lk) * SB + 16 * b + li];
+      su[b][s] = sm_in->SU[(4 * s + lk) * SB + 16 * b + li];
+    }
+  __syncthreads();
+  d4 x[2][2], y[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      x[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+      y[a][b] = x[a][b];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const int i = wr + 16 * a + li, k = 4 * s + lk;
+        x[a][b] = mfma(Xs[i][k], m2[b][s], x[a][b]);
+        x[a][b] = mfma(st[a][s], su[b][s], x[a][b]);
+        y[a][b] = mfma(Ys[i][k], m2[b][s], y[a][b]);
+      }
+    }
+  if (SECOND) {
+    // what the first panel's update would have taken from A22
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int k = 4 * s + lk;
+      double v1[2], v2[2];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        v1[b] = sm_in->V1[k * SB + 16 * b + li];
+        v2[b] = sm_in->V2[k * SB + 16 * b + li];
+      }
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const long long o = (long long)(row + 16 * a + li) * SB + k;
+        const double wa = in ? -Wa[o] : 0.0, ya = mat ? -Ya[o] : 0.0;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          x[a][b] = mfma(wa, v2[b], x[a][b]);
+          x[a][b] = mfma(ya, v1[b], x[a][b]);
+        }
+      }
+    }
+  }
+  if (row == 0) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[a][b][r] -= sm_in->SU[(16 * a + 4 * r + lk) * SB + 16 * b + li];
+  }
+  wave_sync();  // each wave reads and writes its own rows of Xs and Ys
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * a + 4 * r + lk, j = 16 * b + li;
+        if (in) X[(long long)(row + i) * SB + j] = x[a][b][r];
+        if (mat) Y[(long long)(row + i) * SB + j] = y[a][b][r];
+        Xs[wr + i][j] = x[a][b][r];
+        Ys[wr + i][j] = mat ? y[a][b][r] : 0.0;
+      }
+  if (row0 >= m) return;  // the whole workgroup: rows of u only
+  __syncthreads();
+  d4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < XROWS / 16; ++s) {
+    const int k = wr + 4 * s + lk;
+    const double y0 = Ys[k][li], y1 = Ys[k][16 + li], x0 = Xs[k][li], x1 = Xs[k][16 + li];
+    acc[0][0] = mfma(y0, x0, acc[0][0]);
+    acc[0][1] = mfma(y0, x1, acc[0][1]);
+    acc[1][0] = mfma(y1, x0, acc[1][0]);
+    acc[1][1] = mfma(y1, x1, acc[1][1]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) buf[wave * SB * SB + (16 * a + 4 * r + lk) * SB + 16 * b + li] = acc[a][b][r];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid;
+    put_through(part + (long long)blockIdx.x * SB * SB + e,
+                ((buf[e] + buf[SB * SB + e]) + buf[2 * SB * SB + e]) + buf[3 * SB * SB + e]);
+  }
+  const int count = (m + XROWS - 1) / XROWS;
+  if (!last_arrival(ticket, count, &last)) return;
+  double(*M)[SLD] = Xs;
+  double(*T)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + SB * SLD);
+  double(*MT)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + 2 * SB * SLD);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 256 + tid;
+    M[e / SB][e % SB] = ordered_sum(part + e, SB * SB, count);
+    T[e / SB][e % SB] = sm_in->T[e];
+  }
+  __syncthreads();
+  const int i0 = 16 * (wave >> 1) + lk, j0 = 16 * (wave & 1) + li;
+  const d4 mt = prod32<false, false>(M, T, wave, li, lk);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) MT[i0 + 4 * r][j0] = mt[r];
+  __syncthreads();
+  const d4 e2 = prod32<true, false>(T, MT, wave, li, lk);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) sm->E2[(i0 + 4 * r) * SB + j0] = 0.5 * e2[r];
+}
+
+// W = X T - Y E2 for the m matrix rows, W = X T for the rows of u; 16 rows a wave.
+__global__ void __launch_bounds__(256)
+panel_w_kernel(const double *__restrict__ X, const double *__restrict__ Y, int m, int mx,
+               const PanelSmall *__restrict__ sm, double *__restrict__ W) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int row = (blockIdx.x * 4 + wave) * 16;
+  if (row >= mx) return;
+  d4 acc[2];
+  acc[0] = d4{0.0, 0.0, 0.0, 0.0};
+  acc[1] = acc[0];
+  const bool mat = row < m;  // m is a multiple of 32
+  double x[8], y[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    x[s] = X[(long long)(row + li) * SB + 4 * s + lk];
+    y[s] = mat ? -Y[(long long)(row + li) * SB + 4 * s + lk] : 0.0;
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const int o = (4 * s + lk) * SB + li;
+    acc[0] = mfma(x[s], sm->T[o], acc[0]);
+    acc[1] = mfma(x[s], sm->T[o + 16], acc[1]);
+  }
+  if (mat) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int o = (4 * s + lk) * SB + li;
+      acc[0] = mfma(y[s], sm->E2[o], acc[0]);
+      acc[1] = mfma(y[s], sm->E2[o + 16], acc[1]);
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) W[(long long)(row + 4 * r + lk) * SB + 16 * b + li] = acc[b][r];
+}
+
+// A22 -= Y W^T + W Y^T for one panel or both of a pair, on 64 x 64 tiles on or
+// above the diagonal, the others from their mirror; and u -= Y Wu^T on the
+// columns behind the matrix (the workgroups from n_mat on).  m, mx multiples of
+// 32.  STRIP: only the first SB rows and their mirror (a pair's second panel).
+// The first row of tiles (the first workgroups) holds the next panel
+// transposed, A22[:SB, SB:], and forms its G.  A wave owns a quadrant of the
+// tile, loads its old values first, and writes the mirror through LDS so that
+// both copies go out in whole lines.
+template <bool STRIP>
+__global__ void __launch_bounds__(256)
+panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const double *__restrict__ Ya,
+                    const double *__restrict__ Wa, const double *__restrict__ Yb, const double *__restrict__ Wb,
+                    int n_mat, PanelSmall *__restrict__ sm, double *part, int *__restrict__ ticket,
+                    int *__restrict__ flag) {
+  constexpr int PER = UT * SB / 2 / 256;
+  __shared__ double Ls[UT * ULD], Rs[4 * 768 > UT * ULD ? 4 * 768 : UT * ULD];
+  __shared__ int last;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const int nt = (m + UT - 1) / UT, mrow = STRIP ? SB : m;
+  int i0, j0, jend;
+  bool mirror = false, next = false;
+  const bool mat = (int)blockIdx.x < n_mat;
+  if (mat) {
+    int ti = 0, tj = blockIdx.x;
+    if (!STRIP && !triangle_tile(blockIdx.x, nt, ti, tj)) return;
+    i0 = ti * UT;
+    j0 = tj * UT;
+    jend = m;
+    mirror = STRIP || ti != tj;
+    next = ti == 0 && m > SB;
+  } else {
+    const int q = blockIdx.x - n_mat, tj = STRIP ? q : q / nt;
+    i0 = STRIP ? 0 : (q - tj * nt) * UT;
+    j0 = m + tj * UT;
+    jend = mx;
+  }
+  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+  const bool in = i0 + wr < mrow && j0 + wc < jend;  // the whole quadrant
+  double *At = A + (long long)(i0 + wr) * lda + j0 + wc;
+  double old[2][2][4];
+  if (in) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) old[a][b][r] = At[(long long)(16 * a + 4 * r + lk) * lda + 16 * b + li];
+  }
+  d4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  // Y W^T and W Y^T of each panel; u's columns take Y W^T only
+  const int step = mat ? 1 : 2, parts = Yb ? 4 : 2;
+  d2 lv[PER], rv[PER];
+  auto fetch = [&](int h) {
+    const double *Y = h < 2 ? Ya : Yb, *W = h < 2 ? Wa : Wb;
+    const double *Lp = ((h & 1) ? W : Y) + (long long)i0 * SB, *Rp = ((h & 1) ? Y : W) + (long long)j0 * SB;
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int e = (it * 256 + tid) * 2, r = e / SB;
+      lv[it] = d2{0.0, 0.0};
+      rv[it] = d2{0.0, 0.0};
+      if (i0 + r < mrow) lv[it] = *reinterpret_cast<const d2 *>(Lp + e);
+      if (j0 + r < jend) rv[it] = *reinterpret_cast<const d2 *>(Rp + e);
+    }
+  };
+  fetch(0);
+  for (int h = 0; h < parts; h += step) {
+    if (h) __syncthreads();
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int e = (it * 256 + tid) * 2, r = e / SB, c = e % SB;
+      *reinterpret_cast<d2 *>(&Ls[r * ULD + c]) = lv[it];
+      *reinterpret_cast<d2 *>(&Rs[r * ULD + c]) = rv[it];
+    }
+    __syncthreads();
+    if (h + step < parts) fetch(h + step);
+    if (!in) continue;
+#pragma unroll
+    for (int s = 0; s < SB / 4; ++s) {
+      const int k = 4 * s + lk;
+      const double a0 = Ls[(wr + li) * ULD + k], a1 = Ls[(wr + 16 + li) * ULD + k];
+      const double b0 = Rs[(wc + li) * ULD + k], b1 = Rs[(wc + 16 + li) * ULD + k];
+      acc[0][0] = mfma(a0, b0, acc[0][0]);
+      acc[0][1] = mfma(a0, b1, acc[0][1]);
+      acc[1][0] = mfma(a1, b0, acc[1][0]);
+      acc[1][1] = mfma(a1, b1, acc[1][1]);
+    }
+  }
+  if (STRIP && j0 + wc == 0) mirror = false;  // the diagonal block
+  if (in) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double x = old[a][b][r] - acc[a][b][r];
+          At[(long long)(16 * a + 4 * r + lk) * lda + 16 * b + li] = x;
+          old[a][b][r] = x;
+        }
+  }
+  __syncthreads();  // the operands have been read
+  if (in && mirror) {
+    double *Tq = (wave & 1 ? Rs : Ls) + (wave >> 1) * SB * SLD;  // this quadrant, transposed
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Tq[(16 * b + li) * SLD + 16 * a + 4 * r + lk] = old[a][b][r];
+    wave_sync();
+    double *Am = A + (long long)(j0 + wc) * lda + i0 + wr;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int j = 2 * q + (lane >> 5), i = lane & 31;
+      Am[(long long)j * lda + i] = Tq[j * SLD + i];
+    }
+  }
+  if (!next) return;  // the whole workgroup
+  // Ls[c][j] = A22[c][j0 + j] for c < SB, zero outside the panel
+  constexpr int PLD = UT + 2;
+  static_assert(UT * ULD >= SB * PLD && UT * ULD >= 2 * SB * SLD, "the panel's tile fits");
+  __syncthreads();
+  if (wr == 0) {
+    const bool panel = in && j0 + wc >= SB;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          Ls[(16 * a + 4 * r + lk) * PLD + wc + 16 * b + li] = panel ? old[a][b][r] : 0.0;
+  }
+  __syncthreads();
+  d4 g00{0.0, 0.0, 0.0, 0.0}, g01 = g00, g11 = g00;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int k = 16 * wave + 4 * s + lk;
+    const double a0 = Ls[li * PLD + k], a1 = Ls[(16 + li) * PLD + k];
+    g00 = mfma(a0, a0, g00);
+    g01 = mfma(a0, a1, g01);
+    g11 = mfma(a1, a1, g11);
+  }
+  __syncthreads();
+  gram_combine(Rs, g00, g01, g11, [&](int e, double v) { put_through(part + (long long)(j0 / UT) * 768 + e, v); });
+  if (last_arrival(ticket, nt, &last)) panel_factor(part, nt, SB, Ls, sm, flag);
+}
+
+// The band in 16 x 16 tiles, per 16-row block p: (p, p), (p, p + 1), (p, p + 2);
+// two zero blocks behind the last.  Even p: diagonal block k = p / 2 holds the
+// first two, the transposed coupling B_k the third; odd p: B_k both.
+__global__ void __launch_bounds__(256)
+spectral_band_kernel(const double *__restrict__ A, long long lda, const double *__restrict__ Bk,
+                     int nblk, double *__restrict__ band) {
+  const int p = blockIdx.x, k = p >> 1, h = p & 1;
+  const int i = threadIdx.x >> 4, j = threadIdx.x & 15;
+  double d = 0.0, e = 0.0, f = 0.0;
+  if (k < nblk) {
+    const double *D = A + (long long)k * SB * lda + (long long)k * SB;
+    d = D[(long long)(16 * h + i) * lda + 16 * h + j];
+    if (h == 0) e = D[(long long)i * lda + 16 + j];
+    if (k + 1 < nblk) {
+      const double *B = Bk + (long long)k * SB * SB;  // rows of block k + 1, columns of block k
+      if (h == 0) {
+        f = B[j * SB + i];
+      } else {
+        e = B[j * SB + 16 + i];
+        f = B[(16 + j) * SB + 16 + i];
+      }
+    }
+  }
+  double *o = band + (long long)p * 768 + threadIdx.x;
+  o[0] = d;
+  o[256] = e;
+  o[512] = f;
+}
+
+// u's columns as rows: Ut[r][i] = A[i][c0 + r].  32 x 32 tiles through LDS.
+__global__ void __launch_bounds__(256)
+spectral_transpose_kernel(const double *__restrict__ A, long long lda, int np, int R, double *__restrict__ Ut) {
+  __shared__ double t[32][33];
+  const int i0 = blockIdx.x * 32, r0 = blockIdx.y * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
+#pragma unroll
+  for (int q = 0; q < 32; q += 8) t[q + y][x] = r0 + x < R ? A[(long long)(i0 + q + y) * lda + r0 + x] : 0.0;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 32; q += 8)
+    if (r0 + q + y < R) Ut[(long long)(r0 + q + y) * np + i0 + x] = t[x][q + y];
+}
+
+// W = u^T (z^2 - C)^-1 u of a task's one to 16 vectors u by elimination of the
+// band, one wave per task.
+//
+// Step p eliminates 16 rows.  Their 48 columns inside the band and 16 vectors
+// sit one column per lane (rows in registers); a pivot's multipliers are the
+// pivot row scaled by 1/d (the matrix is symmetric), broadcast from the lanes
+// that hold them.  z^2 - C has the imaginary part 2 x eta 1, or is definite on
+// the imaginary axis, so no pivot vanishes.  What the step leaves on the next
+// two blocks and their vectors is a product of the eliminated rows, on MFMA
+// (accumulators initialised with the band itself); the layouts change through
+// the wave's LDS.  COMPLEX = false is the imaginary axis (z^2 = -w^2, real).
+template <bool COMPLEX>
+__global__ void __launch_bounds__(64)
+spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut, int np, int nb16,
+                  const SpectralTask *__restrict__ tasks, double2 *__restrict__ W_out) {
+  constexpr int C2 = COMPLEX ? 2 : 1;
+  __shared__ double row[16 * 64 * C2];  // eliminated rows, [t][column]
+  __shared__ double mul[16 * 32 * C2];  // the same times 1/d_t, columns 16 .. 47
+  const SpectralTask task = tasks[blockIdx.x];
+  const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
+  const double zr = task.z2_re, zi = COMPLEX ? task.z2_im : 0.0;
+  const double *u = Ut + (long long)(task.col + min(li, task.nrhs - 1)) * np;
+  const bool urow = li < task.nrhs;
+
+  // tile `which` of block p in accumulator layout: element r is [4 r + lk][li]
+  auto tile = [&](int p, int which) {
+    const double *b = band + (long long)p * 768 + which * 256 + lane;
+    return d4{b[0], b[64], b[128], b[192]};
+  };
+  auto vec = [&](int p) {
+    d4 v{0.0, 0.0, 0.0, 0.0};
+    if (p < nb16) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double x = u[16 * p + 4 * r + lk];
+        v[r] = urow ? x : 0.0;
+      }
+    }
+    return v;
+  };
+  auto shifted_diag = [&](const d4 &d, d4 &re, d4 &im) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool on = 4 * r + lk == li;
+      re[r] = (on ? zr : 0.0) - d[r];
+      im[r] = on ? zi : 0.0;
+    }
+  };
+  auto put = [&](double *buf, int ld, int c, const d4 &re, const d4 &im) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double *q = buf + ((4 * r + lk) * ld + c + li) * C2;
+      if (COMPLEX) *reinterpret_cast<double2 *>(q) = make_double2(re[r], im[r]);
+      else *q = re[r];
+    }
+  };
+  const d4 zero{0.0, 0.0, 0.0, 0.0};
+  d4 s11r, s11i, s22r, s22i;
+  shifted_diag(tile(0, 0), s11r, s11i);
+  shifted_diag(tile(1, 0), s22r, s22i);
+  d4 s12r = -tile(0, 1), s12i = zero, f = -tile(0, 2);
+  d4 y1r = vec(0), y1i = zero, y2r = vec(1), y2i = zero;
+  double wr = 0.0, wi = 0.0;
+
+#pragma unroll 1
+  for (int p = 0; p < nb16; ++p) {
+    // the next step's fresh tiles
+    const d4 nd = tile(p + 2, 0), ne = tile(p + 1, 1), nf = tile(p + 1, 2), nu = vec(p + 2);
+    put(row, 64, 0, s11r, s11i);
+    put(row, 64, 16, s12r, s12i);
+    put(row, 64, 32, f, zero);
+    put(row, 64, 48, y1r, y1i);
+    wave_sync();
+    double mr[16], mi[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const double *q = row + (t * 64 + lane) * C2;
+      if (COMPLEX) {
+        const double2 v = *reinterpret_cast<const double2 *>(q);
+        mr[t] = v.x;
+        mi[t] = v.y;
+      } else {
+        mr[t] = *q;
+        mi[t] = 0.0;
+      }
+    }
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const double dr = bcast(mr[t], t);
+      double lr, lm;
+      if (COMPLEX) {
+        const double di = bcast(mi[t], t);
+        const double q = 1.0 / (dr * dr + di * di);
+        const double ir = dr * q, ii = -di * q;
+        lr = mr[t] * ir - mi[t] * ii;
+        lm = mr[t] * ii + mi[t] * ir;
+        wr += mr[t] * lr - mi[t] * lm;
+        wi += mr[t] * lm + mi[t] * lr;
+#pragma unroll
+        for (int i = t + 1; i < 16; ++i) {
+          const double a = bcast(lr, i), b = bcast(lm, i);
+          mr[i] = fma(b, mi[t], fma(-a, mr[t], mr[i]));
+          mi[i] = fma(-b, mr[t], fma(-a, mi[t], mi[i]));
+        }
+      } else {
+        lr = mr[t] * (1.0 / dr);
+        lm = 0.0;
+        wr += mr[t] * lr;
+#pragma unroll
+        for (int i = t + 1; i < 16; ++i) mr[i] = fma(-bcast(lr, i), mr[t], mr[i]);
+      }
+      double *q = row + (t * 64 + lane) * C2;
+      double *g = mul + (t * 32 + lane - 16) * C2;
+      if (COMPLEX) {
+        *reinterpret_cast<double2 *>(q) = make_double2(mr[t], mi[t]);
+        if (lane >= 16 && lane < 48) *reinterpret_cast<double2 *>(g) = make_double2(lr, lm);
+      } else {
+        *q = mr[t];
+        if (lane >= 16 && lane < 48) *g = lr;
+      }
+    }
+    wave_sync();
+    // what is left on blocks p + 1, p + 2
+    d4 n11r = s22r, n11i = s22i, n12r = -ne, n12i = zero, n22r, n22i, ny1r = y2r, ny1i = y2i, ny2r = nu, ny2i = zero;
+    shifted_diag(nd, n22r, n22i);
+    auto add = [&](d4 &re, d4 &im, double ar, double ai, double br, double bi) {
+      re = mfma(-ar, br, re);
+      if (COMPLEX) {
+        re = mfma(ai, bi, re);
+        im = mfma(-ar, bi, im);
+        im = mfma(-ai, br, im);
+      }
+    };
+    auto get = [&](const double *buf, int o, double &re, double &im) {
+      if (COMPLEX) {
+        const double2 v = *reinterpret_cast<const double2 *>(buf + o * C2);
+        re = v.x;
+        im = v.y;
+      } else {
+        re = buf[o];
+        im = 0.0;
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int t = 4 * s + lk;
+      double a1r, a1i, a2r, a2i, b1r, b1i, b2r, b2i, cr, ci;
+      get(mul, t * 32 + li, a1r, a1i);
+      get(mul, t * 32 + 16 + li, a2r, a2i);
+      get(row, t * 64 + 16 + li, b1r, b1i);
+      get(row, t * 64 + 32 + li, b2r, b2i);
+      get(row, t * 64 + 48 + li, cr, ci);
+      add(n11r, n11i, a1r, a1i, b1r, b1i);
+      add(n12r, n12i, a1r, a1i, b2r, b2i);
+      add(n22r, n22i, a2r, a2i, b2r, b2i);
+      add(ny1r, ny1i, a1r, a1i, cr, ci);
+      add(ny2r, ny2i, a2r, a2i, cr, ci);
+    }
+    wave_sync();
+    s11r = n11r; s11i = n11i; s12r = n12r; s12i = n12i; s22r = n22r; s22i = n22i;
+    y1r = ny1r; y1i = ny1i; y2r = ny2r; y2i = ny2i;
+    f = -nf;
+  }
+  if (lane >= 48 && lane - 48 < task.nrhs)
+    W_out[task.out_base + (long long)(lane - 48) * task.out_stride] = make_double2(wr, wi);
+}
+
+size_t spectral_small_bytes() { return sizeof(PanelSmall); }
+int spectral_gram_parts(int np) { return (np + UT - 1) / UT * 768; }
+int spectral_xsum_parts(int np) {
+  return std::max((np + XROWS - 1) / XROWS * SB * SB, (np + PROWS - 1) / PROWS * Q_PART2);
+}
+
+void launch_spectral_operand(const double *M_ov, const double *eps, const int *perm, int n_aux, int n_occ,
+                             int n_virt, int pad, int np, double *V, hipStream_t s) {
+  dim3 grid((np + 255) / 256, std::min(n_aux, 256));
+  spectral_operand_kernel<<<grid, 256, 0, s>>>(M_ov, eps, perm, n_aux, n_occ, n_virt, pad, np, V);
+}
+
+void launch_spectral_pairs(const double *M_oo, const double *M_ov, int n_aux, int n_occ, int n_virt,
+                           const int *core, int R, int Rp, double *B, hipStream_t s) {
+  dim3 grid((Rp + 255) / 256, std::min(n_aux, 256));
+  spectral_pairs_kernel<<<grid, 256, 0, s>>>(M_oo, M_ov, n_aux, n_occ, n_virt, core, R, Rp, B);
+}
+
+void launch_spectral_matrix(const double *V, int np, const double *Bp, int Rp, int n_aux, const double *diag2,
+                            int pad, double *A, long long lda, hipStream_t s) {
+  const int nt = (np + UT - 1) / UT;
+  spectral_gemm_kernel<true><<<triangle_tiles(nt), 256, 0, s>>>(V, np, V, np, np, np, n_aux, diag2, pad, A, lda);
+  spectral_gemm_kernel<false><<<nt * ((Rp + UT - 1) / UT), 256, 0, s>>>(V, np, Bp, Rp, np, Rp, n_aux, nullptr, 0,
+                                                                      A + np, lda);
+}
+
+void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, const SpectralWork &w, hipStream_t s) {
+  PanelSmall *sm = static_cast<PanelSmall *>(w.small);
+  const int panels = np / SB - 1;
+  bool pair = false, second = false;
+  for (int k = 0; k < panels; ++k) {
+    const int c0 = k * SB, r0 = c0 + SB, m = np - r0, mx = m + Rp;
+    const int off = k == 0 ? pad : 0, bw = SB - off;  // the first block's zero columns are no panel
+    if (k & 1) second = pair;
+    else second = false;
+    // a pair saves a pass over A22 and costs about 60 us of products of its own
+    pair = !(k & 1) && k + 1 < panels && m >= PAIR_ROWS;
+    const double *P = A + (long long)r0 * lda + c0 + off;
+    double *A22 = A + (long long)r0 * lda + r0;
+    // rows of the first panel's Y and W from this panel's first row on
+    const double *Ya = w.Y[0] + SB * SB, *Wa = w.W[0] + SB * SB;
+    double *Y = w.Y[second], *W = w.W[second], *Bk = w.Bk + (long long)k * SB * SB;
+    const int ng = (m + PROWS - 1) / PROWS, nx = mx / SB;
+    // splits of the rows: about eight workgroups a CU, a wave's part at least 32 rows
+    const int splits = std::max(1, std::min({SPECTRAL_MAX_SPLITS, 2048 / nx, m / 128}));
+    const unsigned gx = 1 + nx * splits, gs = (mx + XROWS - 1) / XROWS;
+    if (k == 0) panel_gram_kernel<<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, w.part, w.ticket, w.flag);
+    if (second) {
+      panel_q_kernel<true><<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, Ya, Wa, w.Q, w.part);
+      panel_x_kernel<true><<<gx, 256, 0, s>>>(A22, lda, m, mx, bw, splits, w.Q, w.Xpart, w.part, ng, Ya, Wa, sm, w.flag, Bk);
+      panel_xsum_kernel<true><<<gs, 256, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, Ya, Wa, sm, sm, w.X, Y, w.part, w.ticket);
+    } else {
+      panel_q_kernel<false><<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, nullptr, nullptr, w.Q, w.part);
+      panel_x_kernel<false><<<gx, 256, 0, s>>>(A22, lda, m, mx, bw, splits, w.Q, w.Xpart, w.part, ng, nullptr, nullptr, sm, w.flag, Bk);
+      panel_xsum_kernel<false><<<gs, 256, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, nullptr, nullptr, sm, sm, w.X, Y, w.part, w.ticket);
+    }
+    panel_w_kernel<<<(mx + 63) / 64, 256, 0, s>>>(w.X, Y, m, mx, sm, W);
+    const double *y0 = second ? Ya : Y, *w0 = second ? Wa : W, *y1 = second ? Y : nullptr, *w1 = second ? W : nullptr;
+    const int nt = (m + UT - 1) / UT, nu = (Rp + UT - 1) / UT;
+    const unsigned tri = triangle_tiles(nt);
+    if (pair) panel_update_kernel<true><<<nt + nu, 256, 0, s>>>(A22, lda, m, mx, y0, w0, y1, w1, nt, sm, w.part, w.ticket, w.flag);
+    else panel_update_kernel<false><<<tri + nt * nu, 256, 0, s>>>(A22, lda, m, mx, y0, w0, y1, w1, (int)tri, sm, w.part, w.ticket, w.flag);
+  }
+}
+
+void launch_spectral_pack(const double *A, long long lda, int np, int R, const double *Bk, double *band, double *Ut,
+                          hipStream_t s) {
+  spectral_band_kernel<<<np / 16 + 2, 256, 0, s>>>(A, lda, Bk, np / SB, band);
+  spectral_transpose_kernel<<<dim3(np / 32, (R + 31) / 32), 256, 0, s>>>(A + np, lda, np, R, Ut);
+}
+
+void launch_spectral_w(const double *band, const double *Ut, int np, const SpectralTask *tasks, int n_tasks,
+                       bool real, double2 *W_out, hipStream_t s) {
+  if (real) spectral_w_kernel<false><<<n_tasks, 64, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
+  else spectral_w_kernel<true><<<n_tasks, 64, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
+}
+
+}  // namespace gwc
