@@ -351,8 +351,10 @@ bool all_finite(const std::vector<double> &v) {
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-size_t default_batch_bytes() {
-  size_t budget = size_t(48) << 30;
+// The workspace of one call: the environment's, else `most` (for a batch of
+// matrices, whose size gains nothing beyond that), and at most half of what is free.
+size_t default_batch_bytes(size_t most = size_t(48) << 30) {
+  size_t budget = most;
   if (const char *e = std::getenv("GWC_BATCH_BYTES")) {
     const long long v = std::atoll(e);
     if (v > 0) budget = (size_t)v;
@@ -1306,8 +1308,9 @@ void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *ou
                size_t batch_bytes) {
   if (!out) fail(GWC_ERR_INVALID_ARG, "NULL out");
   const SigmaInputs in = check_sigma_args(rs.no, rs.nb, args, out, s);
+  const size_t reduction = batch_bytes ? batch_bytes : default_batch_bytes(~size_t(0));
   if (batch_bytes == 0) batch_bytes = default_batch_bytes();
-  if (spectral_route(rs, args, batch_bytes) && run_sigma_by(rs, args, in, out, s, batch_bytes, true)) return;
+  if (spectral_route(rs, args, reduction) && run_sigma_by(rs, args, in, out, s, batch_bytes, true)) return;
   (void)run_sigma_by(rs, args, in, out, s, batch_bytes, false);
 }
 
