@@ -164,6 +164,99 @@ gemm_tn_kernel(const double *__restrict__ A, long long lda, const double *__rest
   }
 }
 
+namespace {
+
+// Slot k's index pair of the circle ordering of the JP items, from round to round.
+struct CirclePair {
+  int k, x, y;
+  __device__ explicit CirclePair(int slot) : k(slot), x(slot), y(slot == 0 ? JP - 1 : JP - 1 - slot) {}
+  __device__ void next() {
+    x = x == JP - 2 ? 0 : x + 1;
+    if (k != 0) y = y == JP - 2 ? 0 : y + 1;
+  }
+};
+
+struct Rotation {
+  double c, s, cm1;
+  bool on;
+};
+
+// a / b and sqrt(x), correctly rounded, for operands and results far from the
+// ends of the exponent range: the compiler's sequences (Newton steps from the
+// hardware's estimate, then one on the residual) without the scaling around them.
+__device__ __forceinline__ double div_mid(double a, double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = fma(r, fma(-b, r, 1.0), r);
+  r = fma(r, fma(-b, r, 1.0), r);
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ double sqrt_mid(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double s = x * y, h = 0.5 * y;
+  const double r = fma(-h, s, 0.5);
+  h = fma(h, r, h);
+  s = fma(s, r, s);
+  s = fma(fma(-s, s, x), h, s);
+  return fma(fma(-s, s, x), h, s);
+}
+
+// The plane rotation that annihilates apq (the identity below the threshold).
+// The threshold is worked out beside the rotation, not before it.
+__device__ __forceinline__ Rotation rotation_of(double app, double aqq, double apq, double tol) {
+  Rotation o;
+  const double d = aqq - app, b = 2.0 * apq;
+  o.on = apq != 0.0 && fabs(apq) > tol * sqrt(fabs(app * aqq));
+  const double th = div_mid(d, b);
+  const double t = div_mid(th >= 0.0 ? 1.0 : -1.0, fabs(th) + sqrt_mid(1.0 + th * th));
+  o.c = div_mid(1.0, sqrt_mid(1.0 + t * t));
+  o.s = t * o.c;
+  o.cm1 = div_mid(-o.s * o.s, 1.0 + o.c);
+  const bool mid = fabs(b) > 0x1p-400 && fabs(b) < 0x1p400 && (d == 0.0 || (fabs(d) > 0x1p-400 && fabs(d) < 0x1p400)) &&
+                   fabs(th) < 1e100 && fabs(th) > 1e-100;
+  if (__any(o.on && !mid)) {
+    if (o.on) {
+      const double th = d / b;
+      const double t = fabs(th) > 1e100 ? 0.5 / th
+                                        : (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(1.0 + th * th));
+      o.c = 1.0 / sqrt(1.0 + t * t);
+      o.s = t * o.c;
+      o.cm1 = -o.s * o.s / (1.0 + o.c);
+    }
+  }
+  if (!o.on) {
+    o.c = 1.0;
+    o.s = 0.0;
+    o.cm1 = 0.0;
+  }
+  return o;
+}
+
+// The value of the next (previous) lane; lane 63 (0) keeps its own.
+__device__ __forceinline__ double from_next(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double from_previous(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xf, 0xf, false));
+}
+
+// J_a^T B J_b of a 2 x 2 block, rows first.
+__device__ __forceinline__ void rotate_block(double &b00, double &b01, double &b10, double &b11, double ca, double sa,
+                                             double cb, double sb) {
+  const double r00 = ca * b00 - sa * b10, r01 = ca * b01 - sa * b11;
+  const double r10 = sa * b00 + ca * b10, r11 = sa * b01 + ca * b11;
+  b00 = cb * r00 - sb * r01;
+  b01 = sb * r00 + cb * r01;
+  b10 = cb * r10 - sb * r11;
+  b11 = sb * r10 + cb * r11;
+}
+
+}  // namespace
+
 // One cyclic Jacobi sweep on the 64 x 64 submatrix of each block pair of round
 // r; E_out[pair] receives V - I for the accumulated rotation V (columns = new
 // basis) and active[pair] whether any rotation was applied.  Each inner round
@@ -171,26 +264,34 @@ gemm_tn_kernel(const double *__restrict__ A, long long lda, const double *__rest
 // J_alpha^T S_ab J_beta with J = [[c, s], [-s, c]], and E's columns p, q follow
 // V's (d = the identity's columns):
 //   E_p <- c E_p - s E_q + (c - 1) d_p - s d_q,  E_q <- s E_p + c E_q + s d_p + (c - 1) d_q.
+//
+// The 63 rounds are one dependent chain: a round's rotations (three divisions
+// and two square roots in a row) need the elements the round before leaves.
+// Wave 0 does nothing but rotations, one round ahead: it forms the three
+// elements of each of its 32 pairs from the blocks as they were, by the same
+// arithmetic as the waves that update them, while those waves write the round's
+// S into the other of two buffers and update E.  One barrier a round.  E stays in
+// registers, a lane holding a slot's two columns of a row; between rounds the
+// columns move to the neighbouring slots, so that LDS carries S alone.  Bound by
+// that chain (about 0.75 us a round); 82 -> 56 us a launch with 22 pairs, the
+// results unchanged to the last bit.
 __global__ void __launch_bounds__(JPT)
 jacobi_pair_kernel(const double *__restrict__ C, long long ldc, int nb, int r, double tol,
                    double *__restrict__ E_out, int *__restrict__ active, int *__restrict__ rotations) {
-  __shared__ double S[JP][JLD];
-  __shared__ double V[JP][JLD];  // E = V - I
-  __shared__ double rc[JB], rs[JB], rcm1[JB];
-  __shared__ int2 rpq[JB];
+  __shared__ double S[2][JP][JLD];
+  __shared__ double rc[2][JB][3];  // a round's c, s, c - 1
   __shared__ int nrot_block;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int2 IJ = circle_pair(nb, r, blockIdx.x);
-  load_pair_tile(C, ldc, IJ, IJ, S);
-  for (int e = tid; e < JP * JP; e += JPT) V[e / JP][e % JP] = 0.0;
+  load_pair_tile(C, ldc, IJ, IJ, S[0]);
   if (tid == 0) nrot_block = 0;
   __syncthreads();
   // a submatrix already diagonal to the threshold needs no sweep: E = 0
   int big = 0;
   for (int e = tid; e < JP * JP; e += JPT) {
     const int a = e / JP, b = e % JP;
-    const double x = S[a][b];
-    big |= a < b && x != 0.0 && fabs(x) > tol * sqrt(fabs(S[a][a] * S[b][b]));
+    const double x = S[0][a][b];
+    big |= a < b && x != 0.0 && fabs(x) > tol * sqrt(fabs(S[0][a][a] * S[0][b][b]));
   }
   if (!__syncthreads_or(big)) {
     double *Eo = E_out + (long long)blockIdx.x * JP * JP;
@@ -198,57 +299,96 @@ jacobi_pair_kernel(const double *__restrict__ C, long long ldc, int nb, int r, d
     if (tid == 0) active[blockIdx.x] = 0;
     return;
   }
+  auto publish = [&](int buf, const Rotation &o) {
+    rc[buf][lane][0] = o.c;
+    rc[buf][lane][1] = o.s;
+    rc[buf][lane][2] = o.cm1;
+  };
   int nrot = 0;
-  for (int rr = 0; rr < JP - 1; ++rr) {
-    if (tid < JB) {
-      const int2 pq = circle_pair(JP, rr, tid);
-      const double app = S[pq.x][pq.x], aqq = S[pq.y][pq.y], apq = S[pq.x][pq.y];
-      double c = 1.0, s = 0.0, cm1 = 0.0;
-      if (apq != 0.0 && fabs(apq) > tol * sqrt(fabs(app * aqq))) {
-        const double th = (aqq - app) / (2.0 * apq);
-        const double t = fabs(th) > 1e100 ? 0.5 / th
-                                          : (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(1.0 + th * th));
-        c = 1.0 / sqrt(1.0 + t * t);
-        s = t * c;
-        cm1 = -s * s / (1.0 + c);
-        ++nrot;
+  if (wave == 0) {
+    // slot k of the next round takes p from slot k + 1 (its x; the last slot: its
+    // own y) and q from slot k - 1 (its y; slot 1: slot 0's x, slot 0: its own y)
+    const int k = lane & 31, sa = min(k + 1, JB - 1), sb = max(k - 1, 0);
+    const bool ya = k == JB - 1, yb = k != 1;
+    CirclePair pa(sa), pb(sb);
+    if (lane < JB) {
+      const CirclePair p0(lane);
+      const Rotation o = rotation_of(S[0][p0.x][p0.x], S[0][p0.y][p0.y], S[0][p0.x][p0.y], tol);
+      nrot += o.on;
+      publish(0, o);
+    }
+    __syncthreads();
+    for (int rr = 0; rr < JP - 1; ++rr) {
+      if (lane < JB && rr < JP - 2) {
+        const double (*A)[JLD] = S[rr & 1];
+        const double (*R)[3] = rc[rr & 1];
+        const double ca = R[sa][0], s_a = R[sa][1], cb = R[sb][0], s_b = R[sb][1];
+        double a00 = A[pa.x][pa.x], a01 = A[pa.x][pa.y], a10 = A[pa.y][pa.x], a11 = A[pa.y][pa.y];
+        double b00 = A[pb.x][pb.x], b01 = A[pb.x][pb.y], b10 = A[pb.y][pb.x], b11 = A[pb.y][pb.y];
+        double m00 = A[pa.x][pb.x], m01 = A[pa.x][pb.y], m10 = A[pa.y][pb.x], m11 = A[pa.y][pb.y];
+        rotate_block(a00, a01, a10, a11, ca, s_a, ca, s_a);
+        rotate_block(b00, b01, b10, b11, cb, s_b, cb, s_b);
+        rotate_block(m00, m01, m10, m11, ca, s_a, cb, s_b);
+        const double app = ya ? a11 : a00, aqq = yb ? b11 : b00;
+        const double apq = ya ? (yb ? m11 : m10) : (yb ? m01 : m00);
+        const Rotation o = rotation_of(app, aqq, apq, tol);
+        nrot += o.on;
+        publish((rr + 1) & 1, o);
+        pa.next();
+        pb.next();
       }
-      rc[tid] = c;
-      rs[tid] = s;
-      rcm1[tid] = cm1;
-      rpq[tid] = pq;
+      __syncthreads();
     }
+  } else {
+    // blocks of S: 64 a wave and the last 64 in wave 15 too; rows of E: three
+    // pairs in waves 1 .. 4, two in 5 .. 14, a pair's second row in the upper half wave
+    const int e0 = (wave - 1) * 64 + lane, nblk = wave == 15 ? 2 : 1;
+    const int vn = wave < 5 ? 3 : (wave < 15 ? 2 : 0), v0 = wave < 5 ? 3 * (wave - 1) : 12 + 2 * (wave - 5);
+    const int be = e0 % JB, row0 = 2 * v0 + (lane >> 5);
+    CirclePair pa(e0 / JB), pc((e0 / JB + 2) % JB), pb(be);
+    double vx[3] = {0.0, 0.0, 0.0}, vy[3] = {0.0, 0.0, 0.0};
     __syncthreads();
-    // S: 2 x 2 blocks (alpha, beta), four per thread
-    for (int e = tid; e < JB * JB; e += JPT) {
-      const int al = e / JB, be = e % JB;
-      const int2 pa = rpq[al], pb = rpq[be];
-      const double ca = rc[al], sa = rs[al], cb = rc[be], sb = rs[be];
-      const double b00 = S[pa.x][pb.x], b01 = S[pa.x][pb.y], b10 = S[pa.y][pb.x], b11 = S[pa.y][pb.y];
-      // rows: J_a^T B
-      const double r00 = ca * b00 - sa * b10, r01 = ca * b01 - sa * b11;
-      const double r10 = sa * b00 + ca * b10, r11 = sa * b01 + ca * b11;
-      // columns: (J_a^T B) J_b
-      S[pa.x][pb.x] = cb * r00 - sb * r01;
-      S[pa.x][pb.y] = sb * r00 + cb * r01;
-      S[pa.y][pb.x] = cb * r10 - sb * r11;
-      S[pa.y][pb.y] = sb * r10 + cb * r11;
+    for (int rr = 0; rr < JP - 1; ++rr) {
+      const double (*A)[JLD] = S[rr & 1];
+      double (*B)[JLD] = S[(rr & 1) ^ 1];
+      const double (*R)[3] = rc[rr & 1];
+      const double cb = R[be][0], sb = R[be][1], cm1 = R[be][2];
+      for (int q = 0; q < nblk; ++q) {
+        const CirclePair &p = q ? pc : pa;
+        const double ca = R[p.k][0], sa = R[p.k][1];
+        double b00 = A[p.x][pb.x], b01 = A[p.x][pb.y], b10 = A[p.y][pb.x], b11 = A[p.y][pb.y];
+        rotate_block(b00, b01, b10, b11, ca, sa, cb, sb);
+        B[p.x][pb.x] = b00;
+        B[p.x][pb.y] = b01;
+        B[p.y][pb.x] = b10;
+        B[p.y][pb.y] = b11;
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        if (q >= vn) break;  // the whole wave
+        const int row = row0 + 2 * q;
+        const double dp = row == pb.x ? 1.0 : 0.0, dq = row == pb.y ? 1.0 : 0.0;
+        const double x = (cb * vx[q] - sb * vy[q]) + (cm1 * dp - sb * dq);
+        const double y = (sb * vx[q] + cb * vy[q]) + (sb * dp + cm1 * dq);
+        const double nx = from_next(x), ny = from_previous(be == 0 ? x : y);
+        vx[q] = be == JB - 1 ? y : nx;
+        vy[q] = be == 0 ? y : ny;
+      }
+      pa.next();
+      pb.next();
+      pc.next();
+      __syncthreads();
     }
-    // E: columns p, q of every row, eight per thread
-    for (int e = tid; e < JB * JP; e += JPT) {
-      const int be = e / JP, row = e % JP;
-      const int2 pq = rpq[be];
-      const double c = rc[be], s = rs[be], cm1 = rcm1[be];
-      const double dp = row == pq.x ? 1.0 : 0.0, dq = row == pq.y ? 1.0 : 0.0;
-      const double vx = V[row][pq.x], vy = V[row][pq.y];
-      V[row][pq.x] = (c * vx - s * vy) + (cm1 * dp - s * dq);
-      V[row][pq.y] = (s * vx + c * vy) + (s * dp + cm1 * dq);
+    // every column is back in its first slot
+    double *Eo = E_out + (long long)blockIdx.x * JP * JP;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      if (q >= vn) break;
+      Eo[(row0 + 2 * q) * JP + pb.x] = vx[q];
+      Eo[(row0 + 2 * q) * JP + pb.y] = vy[q];
     }
-    __syncthreads();
   }
   if (tid < JB && nrot) atomicAdd(&nrot_block, nrot);
-  double *Eo = E_out + (long long)blockIdx.x * JP * JP;
-  for (int e = tid; e < JP * JP; e += JPT) Eo[e] = V[e / JP][e % JP];
   __syncthreads();
   if (tid == 0) {
     active[blockIdx.x] = nrot_block > 0;
