@@ -54,15 +54,26 @@ __device__ __forceinline__ int pair_index(int2 IJ, int t) {
 // its mirror.  The logical 64 x 64 tile with the rows of pair R and the
 // columns of pair K is moved as four 32 x 32 sub-blocks; consecutive threads
 // touch consecutive addresses in both orientations.
+template <int NT>  // threads
 __device__ __forceinline__ void load_pair_tile(const double *__restrict__ C, long long ldc, int2 R,
                                                int2 K, double (*T)[JLD]) {
-  for (int e = threadIdx.x; e < JP * JP; e += blockDim.x) {
-    const int sub = e / (JB * JB), w = e % (JB * JB);
+  constexpr int PER = JP * JP / NT;
+  double x[PER];  // every load in flight before the first store to LDS
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int e = i * NT + (int)threadIdx.x, sub = e / (JB * JB), w = e % (JB * JB);
+    const int rb = sub >> 1 ? R.y : R.x, cb = sub & 1 ? K.y : K.x;
+    const int u = w / JB, v = w % JB, lo = min(rb, cb), hi = max(rb, cb);
+    x[i] = C[(long long)(lo * JB + u) * ldc + hi * JB + v];
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int e = i * NT + (int)threadIdx.x, sub = e / (JB * JB), w = e % (JB * JB);
     const int sa = sub >> 1, sc = sub & 1;
     const int rb = sa ? R.y : R.x, cb = sc ? K.y : K.x;
     const int u = w / JB, v = w % JB;
-    if (rb <= cb) T[sa * JB + u][sc * JB + v] = C[(long long)(rb * JB + u) * ldc + cb * JB + v];
-    else T[sa * JB + v][sc * JB + u] = C[(long long)(cb * JB + u) * ldc + rb * JB + v];
+    if (rb <= cb) T[sa * JB + u][sc * JB + v] = x[i];
+    else T[sa * JB + v][sc * JB + u] = x[i];
   }
 }
 
@@ -71,7 +82,8 @@ __device__ __forceinline__ void load_pair_tile(const double *__restrict__ C, lon
 // is left to its mirror and the two diagonal 32-blocks are written symmetrised.
 __device__ __forceinline__ void store_pair_tile(double *__restrict__ C, long long ldc, int2 R,
                                                 int2 K, bool same, const double (*T)[JLD]) {
-  for (int e = threadIdx.x; e < JP * JP; e += blockDim.x) {
+#pragma unroll 4
+  for (int e = threadIdx.x; e < JP * JP; e += 256) {
     const int sub = e / (JB * JB), w = e % (JB * JB);
     const int sa = sub >> 1, sc = sub & 1;
     const int rb = sa ? R.y : R.x, cb = sc ? K.y : K.x;
@@ -283,7 +295,7 @@ jacobi_pair_kernel(const double *__restrict__ C, long long ldc, int nb, int r, d
   __shared__ int nrot_block;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int2 IJ = circle_pair(nb, r, blockIdx.x);
-  load_pair_tile(C, ldc, IJ, IJ, S[0]);
+  load_pair_tile<JPT>(C, ldc, IJ, IJ, S[0]);
   if (tid == 0) nrot_block = 0;
   __syncthreads();
   // a submatrix already diagonal to the threshold needs no sweep: E = 0
@@ -408,51 +420,55 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // Wave w owns the 32 x 32 quadrant (w / 2, w % 2) as 2 x 2 MFMA tiles.  Operand
 // layout: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; element r of
 // lane l's accumulator is D[4 r + l / 16][l % 16].
-__device__ __forceinline__ void prod_tile_e(const double (*X)[JLD], const double *__restrict__ E,
+struct EFragment {  // a wave's operand fragments of E for all 16 steps
+  double e[JP / 4][2];
+  __device__ __forceinline__ void load(const double *__restrict__ E, int quadrant, int lane) {
+#pragma unroll
+    for (int s = 0; s < JP / 4; ++s)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) e[s][t] = E[(4 * s + (lane >> 4)) * JP + quadrant + 16 * t + (lane & 15)];
+  }
+};
+
+__device__ __forceinline__ void prod_tile_e(const double (*X)[JLD], const EFragment &E,
                                             int wave, int lane, d4 acc[2][2]) {
   const int li = lane & 15, lk = lane >> 4;
-  const int qr = (wave >> 1) * 32, qc = (wave & 1) * 32;
+  const int qr = (wave >> 1) * 32;
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int u = 0; u < 2; ++u) acc[t][u] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int k0 = 0; k0 < JP; k0 += 4) {
-    double a[2], b[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      a[t] = X[qr + 16 * t + li][k0 + lk];
-      b[t] = E[(k0 + lk) * JP + qc + 16 * t + li];
-    }
+  for (int s = 0; s < JP / 4; ++s) {
+    double a[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) a[t] = X[qr + 16 * t + li][4 * s + lk];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int u = 0; u < 2; ++u)
-        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], b[u], acc[t][u], 0, 0, 0);
+        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], E.e[s][u], acc[t][u], 0, 0, 0);
   }
 }
 
-__device__ __forceinline__ void prod_et_tile(const double *__restrict__ E, const double (*X)[JLD],
+__device__ __forceinline__ void prod_et_tile(const EFragment &E, const double (*X)[JLD],
                                              int wave, int lane, d4 acc[2][2]) {
   const int li = lane & 15, lk = lane >> 4;
-  const int qr = (wave >> 1) * 32, qc = (wave & 1) * 32;
+  const int qc = (wave & 1) * 32;
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int u = 0; u < 2; ++u) acc[t][u] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int k0 = 0; k0 < JP; k0 += 4) {
-    double a[2], b[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      a[t] = E[(k0 + lk) * JP + qr + 16 * t + li];
-      b[t] = X[k0 + lk][qc + 16 * t + li];
-    }
+  for (int s = 0; s < JP / 4; ++s) {
+    double b[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) b[t] = X[4 * s + lk][qc + 16 * t + li];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int u = 0; u < 2; ++u)
-        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], b[u], acc[t][u], 0, 0, 0);
+        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(E.e[s][t], b[u], acc[t][u], 0, 0, 0);
   }
 }
 
@@ -486,8 +502,11 @@ jacobi_apply_kernel(double *__restrict__ C, long long ldc, int nb, int r,
     if (P > Q || (!active[P] && !active[Q])) return;
     if (tid == 0) atomicAdd(&work[0], 1);
     const int2 IP = circle_pair(nb, r, P), IQ = circle_pair(nb, r, Q);
-    const double *EQ = Ep + (long long)Q * JP * JP, *EP = Ep + (long long)P * JP * JP;
-    load_pair_tile(C, ldc, IP, IQ, X);
+    // both rotations' fragments are on their way while the tile is loaded
+    EFragment EQ, EP;
+    EQ.load(Ep + (long long)Q * JP * JP, (wave & 1) * 32, lane);
+    EP.load(Ep + (long long)P * JP * JP, (wave >> 1) * 32, lane);
+    load_pair_tile<256>(C, ldc, IP, IQ, X);
     __syncthreads();
     prod_tile_e(X, EQ, wave, lane, acc);  // T = C_PQ E_Q
     double own[2][2][4], tpart[2][2][4];
@@ -529,10 +548,21 @@ jacobi_apply_kernel(double *__restrict__ C, long long ldc, int nb, int r,
   if (tid == 0) atomicAdd(&work[1], 1);
   const int y0 = yt * JP;
   const int2 IQ = circle_pair(nb, r, Q);
-  const double *EQ = Ep + (long long)Q * JP * JP;
-  for (int e = tid; e < JP * JP; e += 256) {
-    const int a = e / JP, c = e % JP;
-    X[a][c] = (y0 + a < n_aux) ? Y[(long long)(y0 + a) * ldy + pair_index(IQ, c)] : 0.0;
+  EFragment EQ;
+  EQ.load(Ep + (long long)Q * JP * JP, (wave & 1) * 32, lane);
+  {
+    constexpr int PER = JP * JP / 256;
+    double y[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = i * 256 + tid, a = min(e / JP, n_aux - 1 - y0), c = e % JP;
+      y[i] = Y[(long long)(y0 + a) * ldy + pair_index(IQ, c)];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = i * 256 + tid, a = e / JP, c = e % JP;
+      X[a][c] = y0 + a < n_aux ? y[i] : 0.0;
+    }
   }
   __syncthreads();
   prod_tile_e(X, EQ, wave, lane, acc);  // Y_tile E_Q
