@@ -1356,9 +1356,7 @@ void run_cumulant(const gwc_cumulant_args *a, double *A_out, double *z_out, hipS
                           dz.as<double>(), s);
   launch_cumulant_time(dnu.as<double>(), dc.as<double>(), a->n_real, nt, dt, a->e_qp,
                        a->omega_out_min, a->eta, dA.as<double2>(), s);
-  double2 *res = nullptr;
-  launch_fft_inverse(dA.as<double2>(), dB.as<double2>(), log2n, &res, s);
-  launch_extract_spectrum(res, a->n_out, dAout.as<double>(), s);
+  launch_fft_spectrum(dA.as<double2>(), dB.as<double2>(), log2n, a->n_out, dAout.as<double>(), s);
   HIPCHECK(hipGetLastError());
   copy_out(A_out, dAout.p, (size_t)a->n_out * sizeof(double), s);
   if (z_out) copy_out(z_out, dz.p, 2 * sizeof(double), s);

@@ -150,9 +150,9 @@ void launch_cumulant_weights(const double *omega_real, const double *im_sigma, i
 void launch_cumulant_time(const double *nu, const double *c, int n_real, int n_t, double dt,
                           double e_qp, double omega0, double eta, double2 *Gt,
                           hipStream_t stream);
-void launch_fft_inverse(double2 *buf_a, double2 *buf_b, int log2n, double2 **result,
-                        hipStream_t stream);
-void launch_extract_spectrum(const double2 *Gw, int n_out, double *A_out, hipStream_t stream);
+// A[l] = -Im(sum_k buf_a[k] e^{2 pi i k l / n}) / pi, l < n_out; n = 2^log2n >= 16.
+void launch_fft_spectrum(double2 *buf_a, double2 *buf_b, int log2n, int n_out, double *A_out,
+                         hipStream_t stream);
 
 // Peak-rate probes (diagnostics): kind 0 FP64 MFMA, 1 BF16 MFMA, 2 FP16 MFMA
 // (TFLOP/s), 3 HBM copy (GB/s, read + write).

@@ -126,9 +126,7 @@ void run_cumulant_noalloc(const gwc_cumulant_args *a, double *A_out, double *z_o
   const double dt = 2.0 * PI_D / ((double)nt * a->d_omega);
   gwc::launch_cumulant_weights(w, im, a->n_real, a->eps_n, nu, c, z, s);
   gwc::launch_cumulant_time(nu, c, a->n_real, nt, dt, a->e_qp, a->omega_out_min, a->eta, Ga, s);
-  double2 *res = nullptr;
-  gwc::launch_fft_inverse(Ga, Gb, log2n, &res, s);
-  gwc::launch_extract_spectrum(res, a->n_out, Aout, s);
+  gwc::launch_fft_spectrum(Ga, Gb, log2n, a->n_out, Aout, s);
   check(hipGetLastError(), "kernel launch");
   check(hipMemcpyAsync(A_out, Aout, (size_t)a->n_out * sizeof(double), hipMemcpyDefault, s),
         "copying A out");
