@@ -20,6 +20,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <deque>
 #include <memory>
 #include <mutex>
@@ -172,10 +173,12 @@ class DeviceCache {
     std::lock_guard<std::mutex> lock(mu_);
     return idle_bytes_;
   }
-  // Takes back a block last used on stream s.
-  void put(void *p, size_t cls, hipStream_t s) {
+  // Takes back a block last used on stream s (`idle`: that stream has finished).
+  void put(void *p, size_t cls, hipStream_t s, bool idle) {
     hipEvent_t ev = nullptr;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess || hipEventRecord(ev, s) != hipSuccess) {
+    if (idle) {
+      // the block may go to any stream at once
+    } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess || hipEventRecord(ev, s) != hipSuccess) {
       (void)hipGetLastError();
       if (ev) (void)hipEventDestroy(ev);
       ev = nullptr;
@@ -248,6 +251,19 @@ DeviceCache &device_cache() {
   return caches[dev >= 0 && dev < CACHE_DEVICES ? dev : 0];
 }
 
+// Marks the end of a call that has synchronised its stream: temporaries that go
+// out of scope between synced() and the end of the CallScope (declared before
+// them) return to the cache without an event each, which cost about 5 us a buffer.
+thread_local bool t_stream_idle = false;
+struct CallScope {
+  const bool outer = t_stream_idle;
+  CallScope() { t_stream_idle = false; }
+  CallScope(const CallScope &) = delete;
+  CallScope &operator=(const CallScope &) = delete;
+  ~CallScope() { t_stream_idle = outer; }
+  void synced() { t_stream_idle = true; }
+};
+
 // A temporary of one call, used on stream s and returned to the cache at
 // scope exit (in stream order).
 struct DevBuf {
@@ -260,7 +276,7 @@ struct DevBuf {
   DevBuf &operator=(const DevBuf &) = delete;
   ~DevBuf() { release(); }
   void release() {
-    if (p) cache->put(p, cls, s);
+    if (p) cache->put(p, cls, s, t_stream_idle);
     p = nullptr;
   }
   void alloc(size_t bytes) {
@@ -277,20 +293,36 @@ struct DevBuf {
   }
 };
 
-// Long-lived allocation (resident systems).
+// Allocation of a system: its own (resident systems), or a block of the cache
+// (the system of one call, `pooled` before alloc).
 struct PersistBuf {
   void *p = nullptr;
-  size_t bytes = 0;
+  size_t bytes = 0, cls = 0;
+  DeviceCache *cache = nullptr;
+  hipStream_t s = nullptr;
   PersistBuf() = default;
   PersistBuf(const PersistBuf &) = delete;
   PersistBuf &operator=(const PersistBuf &) = delete;
-  ~PersistBuf() {
-    if (p) (void)hipFree(p);
+  ~PersistBuf() { release(); }
+  void pooled(hipStream_t stream) {
+    cache = &device_cache();
+    s = stream;
+  }
+  void release() {
+    if (p && cache) cache->put(p, cls, s, t_stream_idle);
+    else if (p) (void)hipFree(p);
+    p = nullptr;
   }
   void alloc(size_t b) {
-    if (p) (void)hipFree(p);
-    p = nullptr;
+    release();
     if (b == 0) b = 16;
+    if (cache) {
+      cls = cache_class(b);
+      p = cache->get(cls, s);
+      if (!p) fail(GWC_ERR_OUT_OF_MEMORY, "allocation of %zu bytes failed", b);
+      bytes = b;
+      return;
+    }
     hipError_t e = hipMalloc(&p, b);
     if (e != hipSuccess) {
       p = nullptr;
@@ -329,6 +361,108 @@ std::vector<T> to_host(const T *p, size_t count, hipStream_t s) {
   }
   return v;
 }
+
+// Small arrays of a call brought to the host together: device arrays are
+// gathered into one block and copied with one synchronisation (each by itself
+// cost 15 us), host arrays are copied at once.
+struct GatherArgs {
+  static constexpr int MAX = 12;
+  const int *src[MAX];
+  long long words[MAX], at[MAX];
+  int count;
+};
+__global__ void __launch_bounds__(256) gather_kernel(GatherArgs g, int *__restrict__ out) {
+  const int k = blockIdx.y;
+  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < g.words[k]; i += 256LL * gridDim.x)
+    out[g.at[k] + i] = g.src[k][i];
+}
+
+class HostFetch {
+ public:
+  explicit HostFetch(hipStream_t s) : s_(s) { g_.count = 0; }
+  template <class T>
+  void add(std::vector<T> &dst, const T *src, size_t count) {
+    dst.resize(count);
+    if (count == 0) return;
+    if (!is_device_ptr(src)) {
+      std::copy(src, src + count, dst.begin());
+      return;
+    }
+    if (g_.count == GatherArgs::MAX) run();
+    g_.src[g_.count] = reinterpret_cast<const int *>(src);
+    g_.words[g_.count] = (long long)(count * sizeof(T) / sizeof(int));
+    g_.at[g_.count] = total_;
+    total_ += (g_.words[g_.count] + 1) / 2 * 2;
+    most_ = std::max(most_, g_.words[g_.count]);
+    dst_[g_.count++] = dst.data();
+  }
+  void run() {
+    if (g_.count == 0) return;
+    DevBuf d(s_);
+    d.alloc((size_t)total_ * sizeof(int));
+    const unsigned bx = (unsigned)std::min<long long>((most_ + 255) / 256, 1024);
+    gather_kernel<<<dim3(bx, (unsigned)g_.count), 256, 0, s_>>>(g_, d.as<int>());
+    HIPCHECK(hipGetLastError());
+    std::vector<int> h((size_t)total_);
+    HIPCHECK(hipMemcpyAsync(h.data(), d.p, h.size() * sizeof(int), hipMemcpyDeviceToHost, s_));
+    HIPCHECK(hipStreamSynchronize(s_));
+    for (int k = 0; k < g_.count; ++k)
+      std::memcpy(dst_[k], h.data() + g_.at[k], (size_t)g_.words[k] * sizeof(int));
+    g_.count = 0;
+    total_ = most_ = 0;
+  }
+
+ private:
+  hipStream_t s_;
+  GatherArgs g_;
+  void *dst_[GatherArgs::MAX];
+  long long total_ = 0, most_ = 0;
+};
+
+// Host arrays of a call sent to the device in one copy.
+struct Staged {
+  std::vector<char> host;  // kept until the call has synchronised
+  DevBuf dev;
+  explicit Staged(hipStream_t s) : dev(s) {}
+  template <class T>
+  size_t add(const std::vector<T> &v) {
+    const size_t at = (host.size() + 15) / 16 * 16;
+    host.resize(at + v.size() * sizeof(T));
+    if (!v.empty()) std::memcpy(host.data() + at, v.data(), v.size() * sizeof(T));
+    return at;
+  }
+  void send(hipStream_t s) {
+    dev.alloc(host.size());
+    if (!host.empty()) HIPCHECK(hipMemcpyAsync(dev.p, host.data(), host.size(), hipMemcpyHostToDevice, s));
+  }
+  template <class T>
+  const T *at(size_t off) const {
+    return reinterpret_cast<const T *>(dev.as<char>() + off);
+  }
+};
+
+// An output of a call: the caller's own array where that is on the device, else
+// a temporary copied there.
+struct OutBuf {
+  DevBuf tmp;
+  void *user = nullptr, *dev = nullptr;
+  size_t bytes = 0;
+  explicit OutBuf(hipStream_t s) : tmp(s) {}
+  double *open(double *out, size_t count) {
+    user = out;
+    bytes = count * sizeof(double);
+    if (out && is_device_ptr(out)) {
+      dev = out;
+    } else {
+      tmp.alloc(bytes);
+      dev = tmp.p;
+    }
+    return static_cast<double *>(dev);
+  }
+  void close(hipStream_t s) {
+    if (user && dev != user) HIPCHECK(hipMemcpyAsync(user, dev, bytes, hipMemcpyDefault, s));
+  }
+};
 
 template <class T, class Buf>
 T *upload(Buf &buf, const std::vector<T> &v, hipStream_t s) {
@@ -410,6 +544,11 @@ struct ResidentSystem {
   int N = 0, no = 0, nv = 0, nb = 0, n_ov = 0, n_aux_pad = 0, ldl = 0;
   std::vector<double> eps, occ;  // host copies
   PersistBuf d_eps, d_Moo, d_Mov, d_L, d_tiles;
+  // the RI coefficients: the copies above, or the caller's device arrays for
+  // the system of one call, whose finiteness is then still to be read from flag
+  const double *Moo = nullptr, *Mov = nullptr;
+  PersistBuf flag;
+  bool one_call = false, unchecked = false;
   int n_tiles = 0;
   std::mutex mixed_mutex;
   MixedOperands mixed[4];  // by precision (1, 2, 3)
@@ -431,18 +570,67 @@ size_t resident_bytes(const ResidentSystem &rs) {
   return b;
 }
 
-ResidentSystem *create_resident(const gwc_system *sys, hipStream_t s) {
+// eps and occ brought along by the caller's fetch (may be empty).
+struct SystemHead {
+  std::vector<double> eps, occ;
+};
+
+static void check_system_sizes(const gwc_system *sys) {
   if (!sys) fail(GWC_ERR_INVALID_ARG, "NULL system");
   const int N = sys->n_aux, no = sys->n_occ, nv = sys->n_virt;
   if (N < 1 || no < 1 || nv < 1) fail(GWC_ERR_SHAPE, "n_aux, n_occ, n_virt must be >= 1");
   if ((long long)no * nv > (1LL << 30) || N > (1 << 16))
     fail(GWC_ERR_SHAPE, "system too large (n_aux %d, n_occ*n_virt %lld)", N, (long long)no * nv);
   if (!sys->eps || !sys->occ || !sys->M_oo || !sys->M_ov) fail(GWC_ERR_INVALID_ARG, "NULL input array");
+}
+
+// Reports non-finite RI coefficients found on the device (the system of one
+// call leaves reading the flag to the first synchronisation that is due anyway).
+static void check_finite(ResidentSystem &rs, hipStream_t s) {
+  if (!rs.unchecked) return;
+  int flag = 0;
+  HIPCHECK(hipMemcpyAsync(&flag, rs.flag.p, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHECK(hipStreamSynchronize(s));
+  rs.unchecked = false;
+  if (flag) fail(GWC_ERR_NONFINITE, "non-finite value in M_oo or M_ov");
+}
+
+// L packed for the Pi builds, and their tile list.
+static void pack_l(ResidentSystem &rs, hipStream_t s) {
+  if (rs.d_L.p) return;
+  rs.d_L.alloc((size_t)rs.n_aux_pad * rs.ldl * sizeof(double));
+  launch_pack_l(rs.Mov, rs.N, rs.n_ov, rs.d_L.as<double>(), rs.n_aux_pad, rs.ldl, s);
+  std::vector<int2> tiles;
+  const int nt = rs.n_aux_pad / PI_TILE;
+  for (int i = 0; i < nt; ++i)
+    for (int j = i; j < nt; ++j) tiles.push_back(make_int2(i, j));
+  upload(rs.d_tiles, tiles, s);
+  rs.n_tiles = (int)tiles.size();
+  HIPCHECK(hipGetLastError());
+  HIPCHECK(hipStreamSynchronize(s));
+}
+
+// `one_call`: a system that lives for one call, in cached blocks, and reads the
+// coefficients where they are if they are on the device (`in_place`).
+static ResidentSystem *make_system(const gwc_system *sys, hipStream_t s, bool one_call, bool in_place,
+                                   SystemHead *head) {
+  check_system_sizes(sys);
+  const int N = sys->n_aux, no = sys->n_occ, nv = sys->n_virt;
   std::unique_ptr<ResidentSystem> rs(new ResidentSystem());
+  rs->one_call = one_call;
+  if (one_call)
+    for (PersistBuf *b : {&rs->d_eps, &rs->d_Moo, &rs->d_Mov, &rs->d_L, &rs->d_tiles, &rs->flag}) b->pooled(s);
   rs->N = N; rs->no = no; rs->nv = nv; rs->nb = no + nv; rs->n_ov = no * nv;
   const int nb = rs->nb;
-  rs->eps = to_host(sys->eps, nb, s);
-  rs->occ = to_host(sys->occ, nb, s);
+  if (head && (int)head->eps.size() == nb && (int)head->occ.size() == nb) {
+    rs->eps = std::move(head->eps);
+    rs->occ = std::move(head->occ);
+  } else {
+    HostFetch fetch(s);
+    fetch.add(rs->eps, sys->eps, nb);
+    fetch.add(rs->occ, sys->occ, nb);
+    fetch.run();
+  }
   if (!all_finite(rs->eps) || !all_finite(rs->occ)) fail(GWC_ERR_NONFINITE, "non-finite value in eps or occ");
   for (int m = 0; m < nb; ++m)
     if (rs->occ[m] != (m < no ? 2.0 : 0.0))
@@ -454,35 +642,31 @@ ResidentSystem *create_resident(const gwc_system *sys, hipStream_t s) {
     fail(GWC_ERR_NONPOSITIVE_GAP, "highest occupied %g >= lowest virtual %g", max_occ, min_virt);
 
   const size_t n_oo = (size_t)N * no * no, n_ovt = (size_t)N * no * nv;
-  rs->d_Moo.alloc(n_oo * sizeof(double));
-  rs->d_Mov.alloc(n_ovt * sizeof(double));
-  HIPCHECK(hipMemcpyAsync(rs->d_Moo.p, sys->M_oo, n_oo * sizeof(double), hipMemcpyDefault, s));
-  HIPCHECK(hipMemcpyAsync(rs->d_Mov.p, sys->M_ov, n_ovt * sizeof(double), hipMemcpyDefault, s));
-  DevBuf dflag(s);
-  dflag.alloc(sizeof(int));
-  HIPCHECK(hipMemsetAsync(dflag.p, 0, sizeof(int), s));
-  launch_nonfinite(rs->d_Moo.as<double>(), (long long)n_oo, dflag.as<int>(), s);
-  launch_nonfinite(rs->d_Mov.as<double>(), (long long)n_ovt, dflag.as<int>(), s);
-  int flag = 0;
-  HIPCHECK(hipMemcpyAsync(&flag, dflag.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
-  if (flag) fail(GWC_ERR_NONFINITE, "non-finite value in M_oo or M_ov");
-  upload(rs->d_eps, rs->eps, s);
-
+  auto stage = [&](PersistBuf &buf, const double *src, size_t count) -> const double * {
+    if (in_place && is_device_ptr(src)) return src;
+    buf.alloc(count * sizeof(double));
+    HIPCHECK(hipMemcpyAsync(buf.p, src, count * sizeof(double), hipMemcpyDefault, s));
+    return buf.as<double>();
+  };
+  rs->Moo = stage(rs->d_Moo, sys->M_oo, n_oo);
+  rs->Mov = stage(rs->d_Mov, sys->M_ov, n_ovt);
+  rs->flag.alloc(sizeof(int));
+  launch_zero_counters(rs->flag.as<int>(), 1, s);
+  launch_nonfinite(rs->Moo, (long long)n_oo, rs->flag.as<int>(), s);
+  launch_nonfinite(rs->Mov, (long long)n_ovt, rs->flag.as<int>(), s);
+  rs->unchecked = true;
   rs->n_aux_pad = (int)round_up(N, L_ROW_ALIGN);
   rs->ldl = (int)round_up(rs->n_ov, L_COL_ALIGN);
-  rs->d_L.alloc((size_t)rs->n_aux_pad * rs->ldl * sizeof(double));
-  launch_pack_l(rs->d_Mov.as<double>(), N, rs->n_ov, rs->d_L.as<double>(), rs->n_aux_pad, rs->ldl, s);
-  std::vector<int2> tiles;
-  const int nt = rs->n_aux_pad / PI_TILE;
-  for (int i = 0; i < nt; ++i)
-    for (int j = i; j < nt; ++j) tiles.push_back(make_int2(i, j));
-  upload(rs->d_tiles, tiles, s);
-  rs->n_tiles = (int)tiles.size();
+  upload(rs->d_eps, rs->eps, s);
   HIPCHECK(hipGetLastError());
-  HIPCHECK(hipStreamSynchronize(s));
+  if (!one_call) {
+    check_finite(*rs, s);
+    pack_l(*rs, s);
+  }
   return rs.release();
 }
+
+ResidentSystem *create_resident(const gwc_system *sys, hipStream_t s) { return make_system(sys, s, false, false, nullptr); }
 
 void destroy_resident(ResidentSystem *rs) { delete rs; }
 
@@ -522,9 +706,12 @@ const MixedOperands &mixed_operands(ResidentSystem &rs, int prec, hipStream_t s,
   MixedOperands &m = rs.mixed[prec];
   if (built) *built = 0;
   if (m.ready) return m;
+  pack_l(rs, s);
   const int rows_pad = (int)round_up(rs.N, MX_TILE_COLS);
   const int ldlk = mixed_ldl(prec, rs.ldl);
   const size_t elems = (size_t)rows_pad * ldlk;
+  if (rs.one_call)
+    for (PersistBuf *b : {&m.Lf, &m.Bh, &m.Bl, &m.cs, &m.ics, &m.acol, &m.tiles}) b->pooled(s);
   m.Lf.alloc(elems * mixed_a_bytes(prec));
   m.Bh.alloc(elems * mixed_b_bytes(prec));
   m.Bl.alloc(elems * mixed_b_bytes(prec));
@@ -593,6 +780,8 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
                    size_t batch_bytes, Factorization fact = default_factorization()) {
   const size_t T = tl.size();
   if (T == 0) return;
+  CallScope scope;
+  pack_l(rs, s);
   const int N = rs.N;
   const int n = N + R;
   const int ldg = n;
@@ -603,7 +792,7 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
   const int F = plan.F;
   const size_t mat_elems = (size_t)n * ldg;
 
-  DevBuf dG(s), dchr(s), dchi(s), dz(s), dn(s), dm(s), dob(s), dos(s), dbb(s), dst(s), dscr(s), dts(s);
+  DevBuf dG(s), dchr(s), dchi(s), dbb(s), dst(s), dscr(s), dts(s);
   DevBuf dcf(s);
   dG.alloc(plan.mat_bytes * F);
   if (precision != GWC_PREC_FP64) dcf.alloc((size_t)F * 2 * rs.ldl * sizeof(float));
@@ -611,11 +800,13 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
   dts.alloc((size_t)F * sizeof(float));
   dchr.alloc((size_t)F * rs.ldl * sizeof(double));
   dchi.alloc((size_t)F * rs.ldl * sizeof(double));
-  const double2 *z_d = upload(dz, tl.z, s);
-  const int *n_d = upload(dn, tl.n, s);
-  const int *m_d = upload(dm, tl.m, s);
-  const long long *ob_d = upload(dob, tl.out_base, s);
-  const int *os_d = upload(dos, tl.out_stride, s);
+  Staged lists(s);
+  const size_t oz = lists.add(tl.z), on = lists.add(tl.n), om = lists.add(tl.m), oob = lists.add(tl.out_base),
+               oos = lists.add(tl.out_stride);
+  lists.send(s);
+  const double2 *z_d = lists.at<double2>(oz);
+  const int *n_d = lists.at<int>(on), *m_d = lists.at<int>(om), *os_d = lists.at<int>(oos);
+  const long long *ob_d = lists.at<long long>(oob);
   dbb.alloc((size_t)F * R * sizeof(double));
   dst.alloc(T * sizeof(int));
 
@@ -643,7 +834,7 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
       fl *= (double)N * (N + 1) * (double)rs.no * rs.nv;
       pending.push_back({precision == GWC_PREC_FP64 ? 0 : 2, ea, timing_mark(s), fl});
     }
-    launch_border(rs.d_Moo.as<double>(), rs.d_Mov.as<double>(), N, rs.no, rs.nv, n_d + t0, m_d + t0,
+    launch_border(rs.Moo, rs.Mov, N, rs.no, rs.nv, n_d + t0, m_d + t0,
                   Fb, R, dG.as<double2>(), (long long)mat_elems, ldg, dbb.as<double>(), s);
     hipEvent_t eb = timing ? timing_mark(s) : nullptr;
     if (fact == FACT_LU) {
@@ -689,6 +880,7 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
     }
   }
   status_all.insert(status_all.end(), st.begin(), st.end());
+  scope.synced();
 }
 
 // ---------------------------------------------------------------------------
@@ -699,10 +891,7 @@ struct Spectral {
   std::vector<int> column;  // by state: its first vector, or -1
   DevBuf band, Ut, flag;
   std::vector<PendingTiming> pending;
-  // host sources of the uploads, kept until the call has synchronised
-  std::vector<int> perm;
-  std::vector<double> diag2;
-  std::deque<std::vector<SpectralTask>> tasks;
+  std::deque<std::vector<SpectralTask>> tasks;  // uploaded, kept until the call has synchronised
   explicit Spectral(hipStream_t s) : band(s), Ut(s), flag(s) {}
 };
 
@@ -755,7 +944,21 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   return t_reduce < t_build;
 }
 
-void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int *d_core, Spectral &sp, hipStream_t s) {
+// Transitions by ascending Delta, and Delta^2 in that order.
+void spectral_order(const ResidentSystem &rs, std::vector<int> &perm, std::vector<double> &diag2) {
+  const int no = rs.no, nv = rs.nv, n = rs.n_ov;
+  std::vector<double> delta(n);
+  perm.resize(n);
+  diag2.resize(n);
+  for (int i = 0; i < no; ++i)
+    for (int a = 0; a < nv; ++a) delta[(size_t)i * nv + a] = rs.eps[no + a] - rs.eps[i];
+  for (int k = 0; k < n; ++k) perm[k] = k;
+  std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) { return delta[x] < delta[y]; });
+  for (int k = 0; k < n; ++k) diag2[k] = delta[perm[k]] * delta[perm[k]];
+}
+
+void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int *d_core, const int *d_perm,
+                    const double *d_diag2, Spectral &sp, hipStream_t s) {
   const int no = rs.no, nv = rs.nv, n = rs.n_ov, N = rs.N;
   const SpectralSizes z = spectral_sizes(rs, (int)core.size());
   const int np = z.np;
@@ -764,19 +967,7 @@ void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int 
   sp.nb = rs.nb;
   sp.column.assign(no, -1);
   for (size_t c = core.size(); c-- > 0;) sp.column[core[c]] = (int)c * rs.nb;
-  // transitions by ascending Delta
-  std::vector<int> &perm = sp.perm;
-  std::vector<double> &diag2 = sp.diag2, delta(n);
-  perm.resize(n);
-  diag2.resize(n);
-  for (int i = 0; i < no; ++i)
-    for (int a = 0; a < nv; ++a) delta[(size_t)i * nv + a] = rs.eps[no + a] - rs.eps[i];
-  for (int k = 0; k < n; ++k) perm[k] = k;
-  std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) { return delta[x] < delta[y]; });
-  for (int k = 0; k < n; ++k) diag2[k] = delta[perm[k]] * delta[perm[k]];
-  DevBuf dperm(s), ddiag(s), dA(s), dV(s), dB(s), dQ(s), dY(s), dY2(s), dX(s), dW(s), dW2(s), dXp(s), dBk(s), dpart(s), dsm(s);
-  const int *d_perm = upload(dperm, perm, s);
-  const double *d_diag2 = upload(ddiag, diag2, s);
+  DevBuf dA(s), dV(s), dB(s), dQ(s), dY(s), dY2(s), dX(s), dW(s), dW2(s), dXp(s), dBk(s), dpart(s), dsm(s);
   dA.alloc((size_t)np * lda * sizeof(double));
   dV.alloc((size_t)N * np * sizeof(double));
   dB.alloc((size_t)N * z.Rp * sizeof(double));
@@ -795,8 +986,8 @@ void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int 
   sp.Ut.alloc((size_t)z.R * np * sizeof(double));
   sp.flag.alloc(2 * sizeof(int));
   launch_zero_counters(sp.flag.as<int>(), 2, s);
-  launch_spectral_operand(rs.d_Mov.as<double>(), rs.d_eps.as<double>(), d_perm, N, no, nv, z.pad, np, dV.as<double>(), s);
-  launch_spectral_pairs(rs.d_Moo.as<double>(), rs.d_Mov.as<double>(), N, no, nv, d_core, z.R, z.Rp, dB.as<double>(), s);
+  launch_spectral_operand(rs.Mov, rs.d_eps.as<double>(), d_perm, N, no, nv, z.pad, np, dV.as<double>(), s);
+  launch_spectral_pairs(rs.Moo, rs.Mov, N, no, nv, d_core, z.R, z.Rp, dB.as<double>(), s);
   hipEvent_t ea = g_timing ? timing_mark(s) : nullptr;
   launch_spectral_matrix(dV.as<double>(), np, dB.as<double>(), z.Rp, N, d_diag2, z.pad, dA.as<double>(), lda, s);
   const SpectralWork w{dQ.as<double>(), {dY.as<double>(), dY2.as<double>()}, dX.as<double>(),
@@ -850,7 +1041,8 @@ struct SigmaInputs {
 };
 
 SigmaInputs check_sigma_args(int n_occ, int n_basis, const gwc_sigma_args *args,
-                             const gwc_sigma_out *out, hipStream_t s) {
+                             const gwc_sigma_out *out, hipStream_t s, const gwc_system *sys = nullptr,
+                             SystemHead *head = nullptr) {
   if (!args) fail(GWC_ERR_INVALID_ARG, "NULL args");
   const int nc = args->n_core, ni = args->n_imag, nr = args->n_real;
   if (nc < 1 || ni < 1 || nr < 1) fail(GWC_ERR_SHAPE, "n_core, n_imag, n_real must be >= 1");
@@ -863,12 +1055,21 @@ SigmaInputs check_sigma_args(int n_occ, int n_basis, const gwc_sigma_args *args,
   if (out && args->mode == GWC_MODE_FULL && !out->sigma_c)
     fail(GWC_ERR_INVALID_ARG, "sigma_c is required in FULL mode");
   SigmaInputs in;
-  in.core = to_host(args->core_idx, nc, s);
-  in.wi = to_host(args->omega_imag, ni, s);
-  in.wwi = to_host(args->w_imag, ni, s);
-  in.wr = to_host(args->omega_real, (size_t)nc * nr, s);
   in.vxc.assign(nc, 0.0);
-  if (args->vxc) in.vxc = to_host(args->vxc, nc, s);
+  {
+    HostFetch fetch(s);
+    fetch.add(in.core, args->core_idx, nc);
+    fetch.add(in.wi, args->omega_imag, ni);
+    fetch.add(in.wwi, args->w_imag, ni);
+    fetch.add(in.wr, args->omega_real, (size_t)nc * nr);
+    if (args->vxc) fetch.add(in.vxc, args->vxc, nc);
+    if (head && sys->n_occ >= 1 && sys->n_virt >= 1 && (long long)sys->n_occ * sys->n_virt <= (1LL << 30) &&
+        sys->eps && sys->occ) {
+      fetch.add(head->eps, sys->eps, n_basis);
+      fetch.add(head->occ, sys->occ, n_basis);
+    }
+    fetch.run();
+  }
   if (!all_finite(in.wi) || !all_finite(in.wwi) || !all_finite(in.wr) || !all_finite(in.vxc) ||
       !std::isfinite(args->eta))
     fail(GWC_ERR_NONFINITE, "non-finite value in grids, eta or vxc");
@@ -1206,21 +1407,31 @@ size_t predict_sigma_bytes(const ResidentSystem &rs, const gwc_sigma_args *args,
 // value that is not finite), and the outputs are then to be computed by Pi builds.
 static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const SigmaInputs &in, gwc_sigma_out *out,
                          hipStream_t s, size_t batch_bytes, bool spectral) {
+  CallScope scope;
   const int N = rs.N, nb = rs.nb;
   const int nc = args->n_core, ni = args->n_imag, nr = args->n_real;
   const bool full = args->mode == GWC_MODE_FULL;
+  if (!spectral) check_finite(rs, s);
   const MixedOperands *mx = nullptr;
   if (args->precision != GWC_PREC_FP64) mx = &mixed_operands(rs, args->precision, s, nullptr);
 
-  DevBuf dcore(s), dwi(s), dwwi(s), dwr(s), dvxc(s);
-  const int *d_core = upload(dcore, in.core, s);
-  const double *d_wi = upload(dwi, in.wi, s);
-  const double *d_wwi = upload(dwwi, in.wwi, s);
-  const double *d_wr = upload(dwr, in.wr, s);
-  const double *d_vxc = upload(dvxc, in.vxc, s);
+  // the call's lists, sent in one copy
+  TaskList tr;
+  std::vector<double> ftask, diag2;
+  std::vector<int> cj_off, tdec, perm;
+  build_residue_tasks(rs, args, in, tr, ftask, cj_off, tdec);
+  if (spectral) spectral_order(rs, perm, diag2);
+  Staged lists(s);
+  const size_t o_core = lists.add(in.core), o_wi = lists.add(in.wi), o_wwi = lists.add(in.wwi), o_wr = lists.add(in.wr),
+               o_vxc = lists.add(in.vxc), o_f = lists.add(ftask), o_cjo = lists.add(cj_off), o_dec = lists.add(tdec),
+               o_perm = lists.add(perm), o_diag2 = lists.add(diag2);
+  lists.send(s);
+  const int *d_core = lists.at<int>(o_core);
+  const double *d_wi = lists.at<double>(o_wi), *d_wwi = lists.at<double>(o_wwi), *d_wr = lists.at<double>(o_wr),
+               *d_vxc = lists.at<double>(o_vxc);
   std::vector<int> status;
   Spectral spec(s), *sp = spectral ? &spec : nullptr;
-  if (sp) spectral_build(rs, in.core, d_core, *sp, s);
+  if (sp) spectral_build(rs, in.core, d_core, lists.at<int>(o_perm), lists.at<double>(o_diag2), *sp, s);
 
   // ---- imaginary axis: W_imag[c][m][k]
   DevBuf dWi(s);
@@ -1240,10 +1451,6 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
   }
 
   // ---- residues
-  TaskList tr;
-  std::vector<double> ftask;
-  std::vector<int> cj_off, tdec;
-  build_residue_tasks(rs, args, in, tr, ftask, cj_off, tdec);
   DevBuf dWr(s);
   dWr.alloc(std::max<size_t>(tr.size(), 1) * sizeof(double2));
   if (in.wac)
@@ -1257,34 +1464,29 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
 
   // ---- exchange, quadrature, assembly
   const int npts = nr + 1;
-  DevBuf dsx(s), dI(s), dft(s), dcjo(s), dcjs(s), dsig(s), dimd(s), dse(s), deq(s);
-  dsx.alloc(nc * sizeof(double));
-  launch_sigma_x(rs.d_Moo.as<double>(), N, rs.no, d_core, nc, dsx.as<double>(), s);
+  DevBuf dI(s);
+  OutBuf osig(s), oimd(s), ose(s), osx(s), oeq(s);
+  double *dsig = osig.open(full ? out->sigma_c : nullptr, (size_t)nc * nr * 2);
+  double *dimd = oimd.open(out->im_sigma_dec, (size_t)nc * nr);
+  double *dse = ose.open(out->sigma_c_eps, (size_t)nc * 2);
+  double *dsx = osx.open(out->sigma_x, nc);
+  double *deq = oeq.open(out->e_qp, nc);
+  launch_sigma_x(rs.Moo, N, rs.no, d_core, nc, dsx, s);
   dI.alloc((size_t)nc * npts * sizeof(double));
   launch_quadrature(dWi.as<double2>(), rs.d_eps.as<double>(), nb, d_wi, d_wwi, ni, d_wr, nr, d_core,
                     nc, full ? npts : 1, dI.as<double>(), s);
-  const double *d_f = upload(dft, ftask, s);
-  const int *d_cjo = upload(dcjo, cj_off, s);
-  const int *d_tdec = upload(dcjs, tdec, s);
-  dsig.alloc((size_t)nc * nr * 2 * sizeof(double));
-  dimd.alloc((size_t)nc * nr * sizeof(double));
-  dse.alloc((size_t)nc * 2 * sizeof(double));
-  deq.alloc((size_t)nc * sizeof(double));
-  launch_assemble(dWr.as<double2>(), d_f, d_tdec, d_cjo, dI.as<double>(), nc, nr,
-                  rs.d_eps.as<double>(), d_core, dsx.as<double>(), d_vxc, full ? 1 : 0,
-                  dsig.as<double>(), dimd.as<double>(), dse.as<double>(), deq.as<double>(), s);
+  launch_assemble(dWr.as<double2>(), lists.at<double>(o_f), lists.at<int>(o_dec), lists.at<int>(o_cjo),
+                  dI.as<double>(), nc, nr, rs.d_eps.as<double>(), d_core, dsx, d_vxc, full ? 1 : 0, dsig, dimd, dse,
+                  deq, s);
   HIPCHECK(hipGetLastError());
-  if (full) copy_out(out->sigma_c, dsig.p, (size_t)nc * nr * 2 * sizeof(double), s);
-  copy_out(out->im_sigma_dec, dimd.p, (size_t)nc * nr * sizeof(double), s);
-  copy_out(out->sigma_c_eps, dse.p, (size_t)nc * 2 * sizeof(double), s);
-  copy_out(out->sigma_x, dsx.p, (size_t)nc * sizeof(double), s);
-  copy_out(out->e_qp, deq.p, (size_t)nc * sizeof(double), s);
+  for (OutBuf *o : {&osig, &oimd, &ose, &osx, &oeq}) o->close(s);
   int unusable = 0;
   if (sp) {
     launch_nonfinite(dWi.as<double>(), (long long)nc * nb * ni * 2, sp->flag.as<int>() + 1, s);
     launch_nonfinite(dWr.as<double>(), (long long)tr.size() * 2, sp->flag.as<int>() + 1, s);
     HIPCHECK(hipMemcpyAsync(&unusable, sp->flag.as<int>() + 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipStreamSynchronize(s));
+    if (!rs.unchecked) HIPCHECK(hipStreamSynchronize(s));
+    check_finite(rs, s);
     timing_resolve(sp->pending);
     if (unusable) return false;
   }
@@ -1292,7 +1494,7 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
   std::vector<int> qp_it;
   if (in.qp) {
     std::vector<double> sx(nc);
-    HIPCHECK(hipMemcpyAsync(sx.data(), dsx.p, nc * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipMemcpyAsync(sx.data(), dsx, nc * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
     run_qp_newton(rs, mx, args, in, dWi.as<double2>(), d_wi, d_wwi, sx, e_newton, qp_it, status, s,
                   batch_bytes, sp);
@@ -1301,19 +1503,43 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
     copy_out(out->qp_iterations, qp_it.data(), (size_t)nc * sizeof(int), s);
   }
   HIPCHECK(hipStreamSynchronize(s));
+  scope.synced();
   return true;
 }
 
-void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *out, hipStream_t s,
-               size_t batch_bytes) {
-  if (!out) fail(GWC_ERR_INVALID_ARG, "NULL out");
-  const SigmaInputs in = check_sigma_args(rs.no, rs.nb, args, out, s);
+static void run_sigma_checked(ResidentSystem &rs, const gwc_sigma_args *args, const SigmaInputs &in,
+                              gwc_sigma_out *out, hipStream_t s, size_t batch_bytes) {
   const size_t reduction = batch_bytes ? batch_bytes : default_batch_bytes(~size_t(0));
   if (batch_bytes == 0) batch_bytes = default_batch_bytes();
   if (spectral_route(rs, args, reduction) && run_sigma_by(rs, args, in, out, s, batch_bytes, true)) return;
   (void)run_sigma_by(rs, args, in, out, s, batch_bytes, false);
 }
 
+void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *out, hipStream_t s,
+               size_t batch_bytes) {
+  if (!out) fail(GWC_ERR_INVALID_ARG, "NULL out");
+  run_sigma_checked(rs, args, check_sigma_args(rs.no, rs.nb, args, out, s), out, s, batch_bytes);
+}
+
+// The self-energy of a system given for this call alone.
+static void run_sigma_once(const gwc_system *sys, const gwc_sigma_args *args, gwc_sigma_out *out, hipStream_t s) {
+  CallScope scope;
+  // argument checks that need no device come first
+  SystemHead head;
+  const SigmaInputs in = check_sigma_args(sys->n_occ, sys->n_occ + sys->n_virt, args, out, s, sys, &head);
+  // outputs laid over the coefficients are written before the last read of these
+  bool in_place = true;
+  const size_t oo = (size_t)sys->n_aux * sys->n_occ * sys->n_occ, ov = (size_t)sys->n_aux * sys->n_occ * sys->n_virt;
+  const size_t nc = args->n_core, pts = nc * args->n_real;
+  const struct { const double *p; size_t n; } outs[] = {{out->sigma_c, 2 * pts}, {out->im_sigma_dec, pts},
+      {out->sigma_c_eps, 2 * nc}, {out->sigma_x, nc}, {out->e_qp, nc}, {out->e_qp_newton, nc}};
+  for (const auto &o : outs)
+    if (o.p && ((o.p < sys->M_oo + oo && sys->M_oo < o.p + o.n) || (o.p < sys->M_ov + ov && sys->M_ov < o.p + o.n)))
+      in_place = false;
+  std::unique_ptr<ResidentSystem> rs(make_system(sys, s, true, in_place, &head));
+  run_sigma_checked(*rs, args, in, out, s, 0);
+  scope.synced();
+}
 size_t predict_cumulant_bytes(int n_real, int n_t, int n_out) {
   return (size_t)n_real * 4 * sizeof(double) + 2 * (size_t)n_t * sizeof(double2) +
          (size_t)n_out * sizeof(double) + 4096;
@@ -1332,8 +1558,14 @@ void run_cumulant(const gwc_cumulant_args *a, double *A_out, double *z_out, hipS
     fail(GWC_ERR_NONFINITE, "non-finite scalar argument");
   if (!(a->eta > 0.0)) fail(GWC_ERR_INVALID_ARG, "eta must be > 0");
   if (!(a->d_omega > 0.0)) fail(GWC_ERR_INVALID_ARG, "d_omega must be > 0");
-  const std::vector<double> w = to_host(a->omega_real, a->n_real, s);
-  const std::vector<double> im = to_host(a->im_sigma, a->n_real, s);
+  CallScope scope;
+  std::vector<double> w, im;
+  {
+    HostFetch fetch(s);
+    fetch.add(w, a->omega_real, a->n_real);
+    fetch.add(im, a->im_sigma, a->n_real);
+    fetch.run();
+  }
   if (!all_finite(w) || !all_finite(im)) fail(GWC_ERR_NONFINITE, "non-finite grid or Im Sigma");
   for (int j = 1; j < a->n_real; ++j)
     if (!(w[j] > w[j - 1])) fail(GWC_ERR_INVALID_ARG, "omega_real must increase");
@@ -1343,24 +1575,23 @@ void run_cumulant(const gwc_cumulant_args *a, double *A_out, double *z_out, hipS
   const double PI_D = 3.14159265358979323846;
   const double dt = 2.0 * PI_D / ((double)nt * a->d_omega);
 
-  DevBuf dw(s), dim(s), dnu(s), dc(s), dz(s), dA(s), dB(s), dAout(s);
-  const double *d_w = upload(dw, w, s);
-  const double *d_im = upload(dim, im, s);
-  dnu.alloc(a->n_real * sizeof(double));
-  dc.alloc(a->n_real * sizeof(double));
-  dz.alloc(2 * sizeof(double));
+  DevBuf dw(s), dim(s), dnuc(s), dA(s), dB(s);
+  OutBuf oA(s), oz(s);
+  const double *d_w = is_device_ptr(a->omega_real) ? a->omega_real : upload(dw, w, s);
+  const double *d_im = is_device_ptr(a->im_sigma) ? a->im_sigma : upload(dim, im, s);
+  dnuc.alloc(2 * (size_t)a->n_real * sizeof(double));
+  double *dnu = dnuc.as<double>(), *dc = dnu + a->n_real;
   dA.alloc((size_t)nt * sizeof(double2));
   dB.alloc((size_t)nt * sizeof(double2));
-  dAout.alloc((size_t)a->n_out * sizeof(double));
-  launch_cumulant_weights(d_w, d_im, a->n_real, a->eps_n, dnu.as<double>(), dc.as<double>(),
-                          dz.as<double>(), s);
-  launch_cumulant_time(dnu.as<double>(), dc.as<double>(), a->n_real, nt, dt, a->e_qp,
-                       a->omega_out_min, a->eta, dA.as<double2>(), s);
-  launch_fft_spectrum(dA.as<double2>(), dB.as<double2>(), log2n, a->n_out, dAout.as<double>(), s);
+  double *dAout = oA.open(A_out, a->n_out), *dz = oz.open(z_out, 2);
+  launch_cumulant_weights(d_w, d_im, a->n_real, a->eps_n, dnu, dc, dz, s);
+  launch_cumulant_time(dnu, dc, a->n_real, nt, dt, a->e_qp, a->omega_out_min, a->eta, dA.as<double2>(), s);
+  launch_fft_spectrum(dA.as<double2>(), dB.as<double2>(), log2n, a->n_out, dAout, s);
   HIPCHECK(hipGetLastError());
-  copy_out(A_out, dAout.p, (size_t)a->n_out * sizeof(double), s);
-  if (z_out) copy_out(z_out, dz.p, 2 * sizeof(double), s);
+  oA.close(s);
+  oz.close(s);
   HIPCHECK(hipStreamSynchronize(s));
+  scope.synced();
 }
 
 // Fully analytic G0W0 (kernels_analytic.hip): Casida matrix, block-Jacobi
@@ -1431,7 +1662,7 @@ int rpa_solve(ResidentSystem &rs, hipStream_t s, DevBuf &dY, DevBuf &dOm, DevBuf
   const int *d_perm = upload(dperm, perm, s);
   const double *d_diag2 = upload(ddiag, diag2, s);
   // C = Vt^T Vt + diag(Delta^2) over the padded order (the padding stays zero)
-  launch_casida_operands(rs.d_Mov.as<double>(), rs.d_eps.as<double>(), d_perm, N, no, nv, n_pad,
+  launch_casida_operands(rs.Mov, rs.d_eps.as<double>(), d_perm, N, no, nv, n_pad,
                          dVt.as<double>(), Y, s);
   launch_gemm_tn(dVt.as<double>(), ld, dVt.as<double>(), ld, n_pad, n_pad, N, C, ld, d_diag2, n, s);
   HIPCHECK(hipGetLastError());
@@ -1506,7 +1737,7 @@ void run_analytic(ResidentSystem &rs, const gwc_analytic_args *args, gwc_analyti
   const int cols = nc * nbas, npts = nr + 1;
   dBp.alloc((size_t)N * cols * sizeof(double));
   dQ.alloc((size_t)cols * n * sizeof(double));
-  launch_pack_pairs(rs.d_Moo.as<double>(), rs.d_Mov.as<double>(), N, no, nv, d_core, nc,
+  launch_pack_pairs(rs.Moo, rs.Mov, N, no, nv, d_core, nc,
                     dBp.as<double>(), s);
   launch_gemm_tn(dBp.as<double>(), cols, Y, ld, cols, n, N, dQ.as<double>(), n, nullptr, 0, s);
   dpart.alloc((size_t)pole_sum_blocks(n) * nc * npts * sizeof(double2));
@@ -1514,7 +1745,7 @@ void run_analytic(ResidentSystem &rs, const gwc_analytic_args *args, gwc_analyti
   launch_pole_sum(dQ.as<double>(), n, dOm.as<double>(), n, rs.d_eps.as<double>(), no, nbas, d_core,
                   nc, d_wr, nr, args->eta, 0, nullptr, dpart.as<double2>(), dsig.as<double2>(), s);
   dsx.alloc(nc * sizeof(double));
-  launch_sigma_x(rs.d_Moo.as<double>(), N, no, d_core, nc, dsx.as<double>(), s);
+  launch_sigma_x(rs.Moo, N, no, d_core, nc, dsx.as<double>(), s);
   dsc.alloc((size_t)nc * nr * 2 * sizeof(double));
   dse.alloc((size_t)nc * 2 * sizeof(double));
   deq.alloc(nc * sizeof(double));
@@ -1609,7 +1840,7 @@ void run_evgw0(ResidentSystem &rs, const gwc_evgw_args *args, gwc_evgw_out *out,
     DevBuf dBp(s);
     dBp.alloc((size_t)N * rows * sizeof(double));
     dR2.alloc((size_t)rows * n * sizeof(double));
-    launch_pack_all_pairs(rs.d_Moo.as<double>(), rs.d_Mov.as<double>(), dvv.as<double>(), N, no, nv,
+    launch_pack_all_pairs(rs.Moo, rs.Mov, dvv.as<double>(), N, no, nv,
                           dBp.as<double>(), s);
     launch_gemm_tn(dBp.as<double>(), rows, dY.as<double>(), ld, (int)rows, n, N, dR2.as<double>(), n,
                    nullptr, 0, s);
@@ -1619,7 +1850,7 @@ void run_evgw0(ResidentSystem &rs, const gwc_evgw_args *args, gwc_evgw_out *out,
   dY.release();
   dvv.release();
   dsx.alloc((size_t)nbas * sizeof(double));
-  launch_exchange_all(rs.d_Moo.as<double>(), rs.d_Mov.as<double>(), N, no, nv, dsx.as<double>(), s);
+  launch_exchange_all(rs.Moo, rs.Mov, N, no, nv, dsx.as<double>(), s);
 
   // outer iteration on the energies in G
   DevBuf de(s), denew(s), dsteps(s);
@@ -1710,10 +1941,7 @@ int gwc_sigma_core(const gwc_system *sys, const gwc_sigma_args *args, gwc_sigma_
   return guarded([&] {
     if (!sys || !args || !out) fail(GWC_ERR_INVALID_ARG, "NULL system, args or out");
     hipStream_t s = (hipStream_t)hip_stream;
-    // argument checks that need no device come first
-    gwc::validate_sigma_args(sys->n_occ, sys->n_occ + sys->n_virt, args, out, s);
-    std::unique_ptr<gwc::ResidentSystem> rs(gwc::create_resident(sys, s));
-    gwc::run_sigma(*rs, args, out, s, 0);
+    gwc::run_sigma_once(sys, args, out, s);
     return GWC_OK;
   });
 }
@@ -1754,8 +1982,11 @@ int gwc_sigma_analytic(const gwc_system *sys, const gwc_analytic_args *args, gwc
     hipStream_t s = (hipStream_t)hip_stream;
     // argument checks that need no device come first
     (void)gwc::check_analytic_args(sys->n_occ, (long long)sys->n_occ * sys->n_virt, args, out, s);
-    std::unique_ptr<gwc::ResidentSystem> rs(gwc::create_resident(sys, s));
+    CallScope scope;
+    std::unique_ptr<gwc::ResidentSystem> rs(gwc::make_system(sys, s, true, false, nullptr));
+    gwc::check_finite(*rs, s);
     gwc::run_analytic(*rs, args, out, s);
+    scope.synced();
     return GWC_OK;
   });
 }
@@ -1767,8 +1998,11 @@ int gwc_evgw0(const gwc_system *sys, const gwc_evgw_args *args, gwc_evgw_out *ou
     hipStream_t s = (hipStream_t)hip_stream;
     (void)gwc::check_evgw_args(sys->n_occ, sys->n_occ + sys->n_virt,
                                (long long)sys->n_occ * sys->n_virt, args, out, s);
-    std::unique_ptr<gwc::ResidentSystem> rs(gwc::create_resident(sys, s));
+    CallScope scope;
+    std::unique_ptr<gwc::ResidentSystem> rs(gwc::make_system(sys, s, true, false, nullptr));
+    gwc::check_finite(*rs, s);
     gwc::run_evgw0(*rs, args, out, s);
+    scope.synced();
     return GWC_OK;
   });
 }
