@@ -18,8 +18,8 @@
 //
 // Right-looking, 64-column steps, per step and batch of matrices:
 //   D  one workgroup per matrix: the 64 x 64 diagonal block A11 = L11 D1 L11^T
-//      in LDS (64 dependent rank-1 steps), then L11^-1 (unit lower) to the
-//      scratch and D1^-1 to the matrix's row of pivots' inverses;
+//      and L11^-1 (unit lower, to the scratch), 16 pivots at a time in one
+//      wave's registers; D1^-1 to the matrix's row of pivots' inverses;
 //   T  one workgroup per (matrix, 64-row block below the panel): W = A21 L11^-T
 //      on MFMA from the block staged in LDS, stored transposed in the row part
 //      (the upper triangle, otherwise unused): W^T = D1 L21^T, so that
@@ -45,22 +45,6 @@ constexpr int NB = 64;
 constexpr int NXCD = 8;
 constexpr int LDLT_GROUP = 4;
 
-__device__ __forceinline__ double2 zmul(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ double2 zsub(double2 a, double2 b) {
-  return make_double2(a.x - b.x, a.y - b.y);
-}
-__device__ __forceinline__ double2 zinv(double2 d) {
-  // 1/d with scaling by the larger component (Smith)
-  if (fabs(d.x) >= fabs(d.y)) {
-    const double r = d.y / d.x, den = d.x + d.y * r;
-    return make_double2(1.0 / den, -r / den);
-  }
-  const double r = d.x / d.y, den = d.x * r + d.y;
-  return make_double2(r / den, -1.0 / den);
-}
-
 // Workgroup -> (matrix, item), all items of a matrix on one XCD.
 __device__ __forceinline__ bool xcd_item(int wg, int items, int F, int &f, int &item) {
   const int x = wg % NXCD, j = wg / NXCD;
@@ -69,88 +53,169 @@ __device__ __forceinline__ bool xcd_item(int wg, int items, int F, int &f, int &
   return f < F;
 }
 
-// D: one workgroup (256 threads) per matrix.  X = the lower triangle of the
-// kb x kb diagonal block (identity beyond kb), stored packed in LDS.  Step t: every row i > t takes
-// X[i][j] -= (X[i][t] / d_t) X[j][t] for t < j <= i; the columns are scaled
-// by 1/d_t after the last step (a step reads column t and writes only the
-// columns right of it, so one barrier per step suffices).  Thread tid owns
-// row tid / 4 and the columns j = tid % 4 (mod 4); the four threads of a row
-// are in one wave.  Afterwards X holds L11 (unit, strictly lower) and D1
-// (diagonal); D1^-1 goes to dinv_g[f N + K0 + t] and L11^-1 (the LU's
-// right-looking in-place inversion, one barrier per step as well: step t
-// reads row t and writes only rows below it, and a row's multiplier is read
-// by the row's own wave before one of its threads overwrites it) to the
-// scratch, zero-padded beyond kb.
-__global__ void __launch_bounds__(256)
+__device__ __forceinline__ double bcast(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+// 1/d, scaled by a power of two against overflow; the reciprocal by Newton
+// steps from the hardware's estimate (short dependent chain).
+__device__ __forceinline__ double2 zinv_fast(double2 d) {
+  const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(d.x), fabs(d.y)));
+  const double x = ldexp(d.x, -e), y = ldexp(d.y, -e), q = fma(x, x, y * y);
+  double r = __builtin_amdgcn_rcp(q);
+  r = fma(fma(-q, r, 1.0), r, r);
+  r = fma(fma(-q, r, 1.0), r, r);
+  r = fma(fma(-q, r, 1.0), r, r);
+  return make_double2(ldexp(x * r, -e), ldexp(-y * r, -e));
+}
+
+// C -= M^T B of 16 x 16 tiles (C = -M^T B where `clear`), complex, on MFMA:
+// rows t of M (stride NB) and B (stride ldb), C row-major.
+__device__ __forceinline__ void rank_tile(double2 *C, bool clear, const double2 *M, const double2 *B, int ldb, int li,
+                                          int lk) {
+  d4 cr, ci;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const double2 x = clear ? make_double2(0.0, 0.0) : C[(4 * r + lk) * 16 + li];
+    cr[r] = x.x;
+    ci[r] = x.y;
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int t = 4 * s + lk;
+    const double2 x = M[t * NB + li], y = B[t * ldb + li];
+    cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.x, y.x, cr, 0, 0, 0);
+    cr = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.y, cr, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.x, y.y, ci, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, y.x, ci, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) C[(4 * r + lk) * 16 + li] = make_double2(cr[r], ci[r]);
+}
+
+// D: one workgroup (4 waves) per matrix.  The kb x kb diagonal block (identity
+// beyond kb) as 16 x 16 tiles of its upper triangle in LDS.  Stage h: wave 0
+// takes the rows of block h into registers, one column per lane, and
+// eliminates their 16 pivots; a pivot's multipliers are its row over d (the
+// block is symmetric), broadcast from the lanes that hold them.  The lanes left
+// of the block hold the rows of L11^-1 found so far (they take the same row
+// operations).  Then wave 0 inverts the block's unit lower triangle while the
+// others subtract the rows' product from the tiles below, on MFMA; the tiles of
+// L11^-1 move into the slots of the eliminated row, and its finished rows go to
+// the scratch.  D1^-1 goes to dinv_g[f N + K0 + t].  Bound by the pivots' chain
+// of dependent steps.  (64 steps with a barrier each, twice, before.)
+__global__ void __launch_bounds__(256, 2)
 ldlt_diag_kernel(const double2 *__restrict__ G, long long gs, int ldg, int N, int K0,
                  double2 *__restrict__ linv_g, double2 *__restrict__ dinv_g, int *__restrict__ status) {
-  // the lower triangle only, row by row (33 KB: four workgroups per CU)
-  __shared__ double2 Xp[NB * (NB + 1) / 2];
-  __shared__ double2 Dinv[NB];
-  __shared__ int zero;
-  auto X = [&](int r, int c) -> double2 & { return Xp[(r * (r + 1) >> 1) + c]; };
-  const int f = blockIdx.x, tid = threadIdx.x;
+  constexpr int TB = 16, NT = NB / TB;
+  __shared__ double2 X[NT * (NT + 1) / 2][TB * TB];
+  __shared__ double2 U[TB][NB], Mul[TB][NB], Ek[TB][TB];
+  const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
   const double2 *A = G + (long long)f * gs;
   const int kb = min(NB, N - K0);
-  if (tid == 0) zero = 0;
+  // slot of the tile of blocks i <= j (and of L11^-1's tile (j, i))
+  auto slot = [](int i, int j) { return i * NT - i * (i - 1) / 2 + j - i; };
   {
-    // all of a thread's loads in flight before its first LDS store
-    constexpr int PER = NB * NB / 256;
+    // all of a thread's loads in flight before its first LDS store; every load
+    // from an element inside the block, of the stored lower triangle
+    constexpr int PER = NT * (NT + 1) / 2;
     double2 v[PER];
+    const int r = tid >> 4, c = tid & 15;
+    int q = 0;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      // every load unconditional, from an element inside the block (a load
-      // under a branch would be waited for before the other branch's write)
-      const int idx = q * 256 + tid, i = idx / NB, j = idx - i * NB;
-      const int ic = min(i, kb - 1), jc = min(j, ic);
-      const double2 a = A[(long long)(K0 + ic) * ldg + K0 + jc];
-      v[q] = (i < kb && j <= i) ? a : make_double2(i == j ? 1.0 : 0.0, 0.0);
-    }
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int idx = q * 256 + tid, i = idx / NB, j = idx - i * NB;
-      if (j <= i) X(i, j) = v[q];
-    }
+      for (int j = i; j < NT; ++j, ++q) {
+        const int row = min(max(TB * i + r, TB * j + c), kb - 1), col = min(min(TB * i + r, TB * j + c), kb - 1);
+        v[q] = A[(long long)(K0 + row) * ldg + K0 + col];
+      }
+    q = 0;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = i; j < NT; ++j, ++q) {
+        const int gi = TB * i + r, gj = TB * j + c;
+        X[q][tid] = gi < kb && gj < kb ? v[q] : make_double2(gi == gj ? 1.0 : 0.0, 0.0);
+      }
   }
-  __syncthreads();
-  const int i = tid >> 2, j0 = tid & 3;
-  for (int t = 0; t < kb; ++t) {
-    const double2 d = X(t, t);
-    const bool dz = d.x == 0.0 && d.y == 0.0;
-    const double2 inv = dz ? make_double2(0.0, 0.0) : zinv(d);
-    if (tid == 0) {
-      if (dz) zero = 1;
-      Dinv[t] = inv;
-    }
-    if (i > t) {
-      const double2 l = zmul(X(i, t), inv);
-      int j = t + 1 + ((j0 - (t + 1)) & 3);
-      for (; j <= i; j += 4) X(i, j) = zsub(X(i, j), zmul(l, X(j, t)));
-    }
-    __syncthreads();
-  }
-  // L11: column t scaled by 1/d_t (the multipliers the steps used); D1^-1
-  for (int t = j0; t < i && t < kb; t += 4) X(i, t) = zmul(X(i, t), Dinv[t]);
-  if (tid < kb) dinv_g[(long long)f * N + K0 + tid] = Dinv[tid];
-  __syncthreads();
-  if (tid < NB) X(tid, tid) = make_double2(1.0, 0.0);
-  __syncthreads();
-  // L11^-1 in place: at step t every row i > t takes X[i][j] -= L[i][t] X[t][j]
-  // for j < t and X[i][t] = -L[i][t] (row t of X is final by then)
-  for (int t = 0; t < NB - 1; ++t) {
-    if (i > t) {
-      const double2 l = X(i, t);
-      for (int j = j0; j < t; j += 4) X(i, j) = zsub(X(i, j), zmul(l, X(t, j)));
-      if ((t & 3) == j0) X(i, t) = make_double2(-l.x, -l.y);
-    }
-    __syncthreads();
-  }
-  // L11^-1 is unit lower triangular: zeros above the diagonal and beyond kb
   double2 *Li = linv_g + (long long)f * NB * NB;
+  const int stages = (kb + TB - 1) / TB;
+  for (int e = stages * TB * NB + tid; e < NB * NB; e += 256) Li[e] = make_double2(0.0, 0.0);
+  bool zero = false;
+  for (int h = 0; h < stages; ++h) {
+    __syncthreads();
+    if (wave == 0) {
+      const int jb = lane >> 4, p0 = TB * h;
+      const double2 *src = X[jb < h ? slot(jb, h) : slot(h, jb)] + li;
+      double mr[TB], mi[TB];
+      double2 dv = make_double2(0.0, 0.0);
 #pragma unroll
-  for (int q = 0; q < NB * NB / 256; ++q) {
-    const int idx = q * 256 + tid, r = idx / NB, c = idx - r * NB;
-    Li[idx] = (r < kb && c <= r) ? X(r, c) : make_double2(0.0, 0.0);
+      for (int t = 0; t < TB; ++t) {
+        const double2 x = src[t * TB];
+        mr[t] = x.x;
+        mi[t] = x.y;
+      }
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        const double2 d = make_double2(bcast(mr[t], p0 + t), bcast(mi[t], p0 + t));
+        const bool dz = d.x == 0.0 && d.y == 0.0;
+        zero = zero || dz;
+        double2 inv = zinv_fast(d);
+        if (dz) inv = make_double2(0.0, 0.0);
+        if (lane == t) dv = inv;
+        const double lr = mr[t] * inv.x - mi[t] * inv.y, lm = mr[t] * inv.y + mi[t] * inv.x;
+        U[t][lane] = make_double2(mr[t], mi[t]);
+        Mul[t][lane] = make_double2(lr, lm);
+#pragma unroll
+        for (int i = t + 1; i < TB; ++i) {
+          const double a = bcast(lr, p0 + i), b = bcast(lm, p0 + i);
+          mr[i] = fma(b, mi[t], fma(-a, mr[t], mr[i]));
+          mi[i] = fma(-b, mr[t], fma(-a, mi[t], mi[i]));
+        }
+      }
+      if (lane < TB && p0 + lane < kb) dinv_g[(long long)f * N + K0 + p0 + lane] = dv;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // the diagonal tile of L11^-1, a column per lane (four copies)
+      double er[TB], ei[TB];
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        er[t] = li == t ? 1.0 : 0.0;
+        ei[t] = 0.0;
+      }
+#pragma unroll
+      for (int t = 0; t < TB - 1; ++t)
+#pragma unroll
+        for (int i = t + 1; i < TB; ++i) {
+          const double2 l = Mul[t][TB * h + i];
+          er[i] = fma(l.y, ei[t], fma(-l.x, er[t], er[i]));
+          ei[i] = fma(-l.y, er[t], fma(-l.x, ei[t], ei[i]));
+        }
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+        if (lane < TB) Ek[t][lane] = make_double2(er[t], ei[t]);
+    } else {
+      // rows below: tiles (i, j), i > h, with j >= i of the block and j < h of L11^-1
+      int q = 0;
+      for (int i = h + 1; i < NT; ++i)
+        for (int j = 0; j < NT; ++j) {
+          if (j >= h && j < i) continue;
+          if (q++ % 3 != wave - 1) continue;
+          rank_tile(X[j < i ? slot(j, i) : slot(i, j)], false, &Mul[0][TB * i], &U[0][TB * j], NB, li, lk);
+        }
+    }
+    __syncthreads();
+    // and j = h, with the rows of L11^-1 that are now final
+    for (int i = h + 1 + wave; i < NT; i += 4) rank_tile(X[slot(h, i)], true, &Mul[0][TB * i], &Ek[0][0], TB, li, lk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 4 * q + wave, row = TB * h + r, c = lane;
+      const double2 x = c < TB * h ? U[r][c] : Ek[r][c & 15];
+      Li[row * NB + c] = row < kb && c <= row ? x : make_double2(0.0, 0.0);
+    }
   }
   if (tid == 0 && zero) status[f] = 1;
 }
