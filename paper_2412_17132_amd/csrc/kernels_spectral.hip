@@ -119,17 +119,15 @@ __device__ __forceinline__ bool last_arrival(int *ticket, int count, int *shared
   return *shared_flag != 0;
 }
 
-// 1 / x and 1 / sqrt(x) by Newton steps from the hardware's estimates (2^-14
-// and better): two steps reach rounding, and their chain is short.
+// 1 / x and 1 / sqrt(x) by Newton steps from the hardware's estimates (2^-24):
+// two steps reach rounding, and their chain is short.
 __device__ __forceinline__ double fast_rcp(double x) {
   double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
   r = fma(fma(-x, r, 1.0), r, r);
   return fma(fma(-x, r, 1.0), r, r);
 }
 __device__ __forceinline__ double fast_rsqrt(double x) {
   double r = __builtin_amdgcn_rsq(x);
-  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
   r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
   return fma(0.5 * r, fma(-x * r, r, 1.0), r);
 }
@@ -1253,7 +1251,7 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
       double lr, lm;
       if (COMPLEX) {
         const double di = bcast(mi[t], t);
-        const double q = 1.0 / (dr * dr + di * di);
+        const double q = fast_rcp(fma(dr, dr, di * di));
         const double ir = dr * q, ii = -di * q;
         lr = mr[t] * ir - mi[t] * ii;
         lm = mr[t] * ii + mi[t] * ir;
@@ -1266,7 +1264,7 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
           mi[i] = fma(-b, mr[t], fma(-a, mi[t], mi[i]));
         }
       } else {
-        lr = mr[t] * (1.0 / dr);
+        lr = mr[t] * fast_rcp(dr);
         lm = 0.0;
         wr += mr[t] * lr;
 #pragma unroll
