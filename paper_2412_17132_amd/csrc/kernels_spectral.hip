@@ -45,6 +45,7 @@
 // Two Cholesky passes orthogonalise a panel of condition up to 3e6; beyond that
 // (dependent columns) a flag is raised and the caller screens by Pi builds.
 #include <algorithm>
+#include <utility>
 
 #include "gwc_internal.h"
 
@@ -59,6 +60,7 @@ constexpr int SB = SPECTRAL_BAND;
 constexpr int SLD = SB + 1;   // LDS row stride of 32-wide rows
 constexpr int PROWS = 256;    // panel rows per workgroup of panel_gram
 constexpr int XROWS = 128;    // rows per workgroup of panel_xsum
+constexpr int XTHREADS = 512;
 constexpr int UT = 64;        // tile of the rank update and the transition matrix
 constexpr int ULD = SB + 2;   // LDS row stride of its operands (no bank conflicts)
 // Rows from which panels go in pairs: the second panel's own products cost about
@@ -84,6 +86,25 @@ __device__ __forceinline__ double bcast(double v, int lane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
   return __hiloint2double(hi, lo);
+}
+
+// The value of lane C of each row of 16 lanes.
+template <int C>
+__device__ __forceinline__ double row_bcast(double v) {
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + C, 0xf, 0xf, true));
+}
+template <int I>
+struct Index {
+  static constexpr int value = I;
+};
+template <class F, int... I>
+__device__ __forceinline__ void for_each_index(F &&f, std::integer_sequence<int, I...>) {
+  (f(Index<I>{}), ...);
+}
+// f(Index<0>) ... f(Index<N - 1>)
+template <int N, class F>
+__device__ __forceinline__ void for_each_index(F &&f) {
+  for_each_index(f, std::make_integer_sequence<int, N>{});
 }
 
 // Orders a wave's LDS accesses across its lanes.
@@ -147,62 +168,91 @@ __device__ __forceinline__ d4 prod32(const double (*A)[SLD], const double (*B)[S
   return x + y;
 }
 
-// sum_w p[w stride], in order, with up to 16 loads in flight.
-__device__ __forceinline__ double ordered_sum(const double *p, long long stride, int count) {
-  double x = 0.0;
+// sum_w p[w stride + e], in order, for the N values e = first, first + step, ...,
+// with up to 16 loads of each in flight.
+template <int N>
+__device__ __forceinline__ void ordered_sums(const double *p, int first, int step, long long stride, int count,
+                                             double (&x)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) x[n] = 0.0;
   for (int w0 = 0; w0 < count; w0 += 16) {
-    double v[16];
+    double v[N][16];
 #pragma unroll
-    for (int w = 0; w < 16; ++w) v[w] = get_through(p + (long long)min(w0 + w, count - 1) * stride);
+    for (int w = 0; w < 16; ++w)
 #pragma unroll
-    for (int w = 0; w < 16; ++w) x += w0 + w < count ? v[w] : 0.0;
+      for (int n = 0; n < N; ++n) v[n][w] = get_through(p + (long long)min(w0 + w, count - 1) * stride + first + n * step);
+#pragma unroll
+    for (int w = 0; w < 16; ++w)
+#pragma unroll
+      for (int n = 0; n < N; ++n) x[n] += w0 + w < count ? v[n][w] : 0.0;
   }
-  return x;
 }
 
+// The 32 x 32 factorisations below are chains of 32 dependent pivots on one
+// wave, 16 at a time: a lane of each row of 16 holds a column of the 16 x 16
+// diagonal block (the four rows copies of it), so that a pivot's column reaches
+// the others by DPP in the instruction that uses it, and the off-diagonal block
+// is split over the rows; the trailing block takes one MFMA product.  (Rows in
+// lanes, eight columns at a time and readlane broadcasts before: Cholesky 8.4 ->
+// 3.4 us, LU 9.0 -> 4.5, U^-1 and T 6.8 -> 2.7 us.)
+
 // Cholesky factor of the symmetric 32 x 32 G in place (lower triangle), by one
-// wave: lane i holds row i, eight columns at a time in registers; a step's
-// column is broadcast lane by lane.  True when a pivot is not above 1e-13 of
+// wave, and its reciprocal diagonal.  True when a pivot is not above 1e-13 of
 // its diagonal element.
-__device__ bool chol32(double (*G)[SLD], double *rd, int lane) {
-  const int i = lane & (SB - 1);
-  const double gd = G[i][i];
+__device__ __forceinline__ bool chol32(double (*G)[SLD], double *rd, int lane) {
+  const int li = lane & 15, lk = lane >> 4;
+  const double g0 = G[li][li], g1 = G[16 + li][16 + li];
   bool bad = false;
 #pragma unroll 1
-  for (int kb = 0; kb < SB; kb += 8) {
-    double p[8];
+  for (int h = 0; h < 2; ++h) {
+    const int o = 16 * h;
+    double p[16], q[4], dg = 1.0;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) p[c] = G[i][kb + c];
-#pragma unroll 4
-    for (int t = 0; t < kb; ++t) {
-      const double l = G[i][t];
+    for (int i = 0; i < 16; ++i) p[i] = G[o + i][o + li];
 #pragma unroll
-      for (int c = 0; c < 8; ++c) p[c] = fma(-l, bcast(l, kb + c), p[c]);
+    for (int k = 0; k < 4; ++k) q[k] = G[16 + 4 * k + lk][o + li];
+    for_each_index<16>([&](auto ic) {
+      constexpr int c = decltype(ic)::value;
+      const double d = row_bcast<c>(p[c]);
+      if (li == c) dg = d;
+      const double t = li > c ? -p[c] * fast_rcp(d) : 0.0;
+#pragma unroll
+      for (int i = c + 1; i < 16; ++i) p[i] = fma(row_bcast<c>(p[i]), t, p[i]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q[k] = fma(row_bcast<c>(q[k]), t, q[k]);
+    });
+    bad = bad || !(dg > 1e-13 * (h ? g1 : g0));
+    const double r = fast_rsqrt(dg);
+    if (lane < 16) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) G[o + i][o + li] = i >= li ? p[i] * r : 0.0;
+      rd[o + li] = r;
+    }
+    if (h) break;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      G[16 + 4 * k + lk][li] = q[k] * r;
+      G[4 * k + lk][16 + li] = 0.0;
+    }
+    wave_sync();
+    d4 x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = G[16 + 4 * k + lk][16 + li];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double l = G[16 + li][4 * s + lk];
+      x = mfma(-l, l, x);
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      double d = bcast(p[c], kb + c);
-      if (!(d > 1e-13 * bcast(gd, kb + c))) {
-        bad = true;
-        d = 1.0;
-      }
-      const double r = fast_rsqrt(d);
-      const double l = p[c] * r;
-      p[c] = l;
-      if (i == kb + c) rd[kb + c] = r;
-#pragma unroll
-      for (int e = c + 1; e < 8; ++e) p[e] = fma(-l, bcast(l, kb + e), p[e]);
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      if (lane < SB) G[i][kb + c] = i >= kb + c ? p[c] : 0.0;
+    for (int k = 0; k < 4; ++k) G[16 + 4 * k + lk][16 + li] = x[k];
+    wave_sync();
   }
-  return bad;
+  return __any(bad);
 }
 
 // X = L^-1 (lower triangular) of a Cholesky factor, by one wave: lane i holds
 // row i of X^T, i.e. column i of X, and takes L's rows by broadcast.
-__device__ void invert_lower32(const double (*L)[SLD], const double *rd, double (*XT)[SLD], int lane) {
+__device__ __forceinline__ void invert_lower32(const double (*L)[SLD], const double *rd, double (*XT)[SLD], int lane) {
   const int i = lane & (SB - 1);
 #pragma unroll 1
   for (int j = 0; j < SB; ++j) {
@@ -214,96 +264,118 @@ __device__ void invert_lower32(const double (*L)[SLD], const double *rd, double 
 }
 
 // H - S = Y1 U without pivoting, S_jj = -sign of the pivot (so |U_jj| >= 1 for
-// orthonormal columns), in place; returns lane j's S_jj.
-__device__ double lu32(double (*H)[SLD], double *rdu, int lane) {
-  const int i = lane & (SB - 1);
-  double mysign = 1.0;
+// orthonormal columns), in place by one wave; S_jj to sg, 1 / U_jj to rdu.
+__device__ __forceinline__ void lu32(double (*H)[SLD], double *rdu, double *sg, int lane) {
+  const int li = lane & 15, lk = lane >> 4;
 #pragma unroll 1
-  for (int kb = 0; kb < SB; kb += 8) {
-    double p[8];
+  for (int h = 0; h < 2; ++h) {
+    const int o = 16 * h;
+    // the diagonal block, the block below it (a quarter a row of lanes), the block beside it
+    double p[16], q[4], w[16], sign = 1.0, rp = 1.0;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) p[c] = H[i][kb + c];
-#pragma unroll 4
-    for (int t = 0; t < kb; ++t) {
-      const double l = i > t ? H[i][t] : 0.0;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) p[c] = fma(-l, bcast(p[c], t), p[c]);
+    for (int i = 0; i < 16; ++i) {
+      p[i] = H[o + i][o + li];
+      w[i] = H[i][16 + li];
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int t = kb + c;
-      const double x = bcast(p[c], t);
-      const double s = x >= 0.0 ? -1.0 : 1.0;
-      const double inv = fast_rcp(x - s);
-      const double l = i > t ? p[c] * inv : 0.0;
-      if (i == t) {
-        mysign = s;
-        rdu[t] = inv;
-        p[c] = x - s;
-      } else if (i > t) {
-        p[c] = l;
+    for (int k = 0; k < 4; ++k) q[k] = H[16 + 4 * k + lk][o + li];
+    for_each_index<16>([&](auto ic) {
+      constexpr int c = decltype(ic)::value;
+      const double x = row_bcast<c>(p[c]), s = x >= 0.0 ? -1.0 : 1.0, d = x - s, inv = fast_rcp(d);
+      if (li == c) {
+        sign = s;
+        rp = inv;
+        p[c] = d;
+      }
+      const double t = li > c ? -p[c] * inv : 0.0, u = -w[c] * inv;
+#pragma unroll
+      for (int i = c + 1; i < 16; ++i) {
+        const double l = row_bcast<c>(p[i]);
+        p[i] = fma(l, t, p[i]);
+        w[i] = fma(l, u, w[i]);
+        asm volatile("" : "+v"(w[i]));  // now, or every l stays in registers for later
       }
 #pragma unroll
-      for (int e = c + 1; e < 8; ++e) p[e] = fma(-l, bcast(p[e], t), p[e]);
+      for (int k = 0; k < 4; ++k) q[k] = fma(row_bcast<c>(q[k]), t, q[k]);
+    });
+    if (lane < 16) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) H[o + i][o + li] = i > li ? p[i] * rp : p[i];
+      rdu[o + li] = rp;
+      sg[o + li] = sign;
     }
+    if (h) break;
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
-      if (lane < SB) H[i][kb + c] = p[c];
-  }
-  return mysign;
-}
-
-// X = U^-1 (upper triangular, U in H on and above the diagonal), by one wave:
-// lane i holds row i of X, eight columns at a time, U's rows by broadcast.
-__device__ void invert_upper32(const double (*H)[SLD], const double *rdu, double (*X)[SLD], int lane) {
-  const int i = lane & (SB - 1);
-#pragma unroll 1
-  for (int jb = 0; jb < SB; jb += 8) {
-    double p[8];
+    for (int i = 0; i < 16; ++i)
+      if (lk == 1) H[i][16 + li] = w[i];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) p[c] = i == jb + c ? 1.0 : 0.0;
-#pragma unroll 4
-    for (int t = 0; t < jb; ++t) {
-      const double x = X[i][t];
+    for (int k = 0; k < 4; ++k) H[16 + 4 * k + lk][li] = q[k] * rp;
+    wave_sync();
+    d4 x;
 #pragma unroll
-      for (int c = 0; c < 8; ++c) p[c] = fma(-x, H[t][jb + c], p[c]);
-    }
+    for (int k = 0; k < 4; ++k) x[k] = H[16 + 4 * k + lk][16 + li];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      p[c] = jb + c >= i ? p[c] * rdu[jb + c] : 0.0;
+    for (int s = 0; s < 4; ++s) x = mfma(-H[16 + li][4 * s + lk], H[4 * s + lk][16 + li], x);
 #pragma unroll
-      for (int e = c + 1; e < 8; ++e) p[e] = fma(-p[c], H[jb + c][jb + e], p[e]);
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      if (lane < SB) X[i][jb + c] = p[c];
+    for (int k = 0; k < 4; ++k) H[16 + 4 * k + lk][16 + li] = x[k];
+    wave_sync();
   }
 }
 
-// T = -U S Y1^-T (upper triangular) from lu32's factors in H.
-__device__ void tfactor32(const double (*H)[SLD], double (*T)[SLD], double mysign, int lane) {
-  const int i = lane & (SB - 1);
-#pragma unroll 1
-  for (int jb = 0; jb < SB; jb += 8) {
-    double p[8];
+// X = U^-1 and Z = Y1^-1 from lu32's factors in H, by four waves: each inverts
+// one 16 x 16 diagonal block (U's transposed), a column a lane, then two of them
+// form the off-diagonal blocks.  Ends with a barrier.
+__device__ __forceinline__ void invert_factors32(const double (*H)[SLD], const double *rdu, double (*X)[SLD], double (*Z)[SLD],
+                                 int lane, int wave) {
+  const int li = lane & 15, lk = lane >> 4, o = 16 * (wave & 1);
+  const bool up = wave >> 1;
+  double l[16], x[16];
+  const double rp = up ? rdu[o + li] : 1.0;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) p[c] = jb + c >= i ? -H[i][jb + c] * bcast(mysign, jb + c) : 0.0;
-#pragma unroll 4
-    for (int t = 0; t < jb; ++t) {
-      const double x = T[i][t], y = H[i][t];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) p[c] = fma(-x, bcast(y, jb + c), p[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const double y = H[i][jb + c];
-#pragma unroll
-      for (int e = c + 1; e < 8; ++e) p[e] = fma(-p[c], bcast(y, jb + e), p[e]);
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      if (lane < SB) T[i][jb + c] = p[c];
+  for (int i = 0; i < 16; ++i) {
+    l[i] = up ? H[o + li][o + i] : H[o + i][o + li];
+    x[i] = i == li ? 1.0 : 0.0;
   }
+  for_each_index<16>([&](auto it) {
+    constexpr int t = decltype(it)::value;
+    x[t] *= row_bcast<t>(rp);
+#pragma unroll
+    for (int i = t + 1; i < 16; ++i) {
+      x[i] = fma(row_bcast<t>(l[i]), -x[t], x[i]);
+      asm volatile("" : "+v"(l[i]), "+v"(x[i]));  // in this order: later steps' broadcasts would fill the registers
+    }
+  });
+  if (lane < 16) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (up) X[o + li][o + i] = x[i];
+      else Z[o + i][o + li] = x[i];
+    }
+  } else if (lane < 32 && o) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (up) X[16 + i][li] = 0.0;
+      else Z[i][16 + li] = 0.0;
+    }
+  }
+  __syncthreads();
+  if (wave < 2) {
+    // X01 = -X00 (U01 X11), Z10 = -Z11 (L10 Z00), the inner product through its place
+    double(*D)[SLD] = wave ? Z : X;
+    const int ro = wave ? 16 : 0, co = 16 - ro;  // the block's first row and column
+    d4 y{0.0, 0.0, 0.0, 0.0}, z = y;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) y = mfma(H[ro + li][co + 4 * s + lk], D[co + 4 * s + lk][co + li], y);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) D[ro + 4 * r + lk][co + li] = y[r];
+    wave_sync();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) z = mfma(-D[ro + li][ro + 4 * s + lk], D[ro + 4 * s + lk][co + li], z);
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) D[ro + 4 * r + lk][co + li] = z[r];
+  }
+  __syncthreads();
 }
 
 }  // namespace
@@ -440,16 +512,16 @@ __device__ __forceinline__ void gram_combine(double *buf, const d4 &g00, const d
 // the inactive columns bw ..
 __device__ __forceinline__ void gram_collect(const double *part, int stride, int count, int bw, double (*G)[SLD]) {
   const int tid = threadIdx.x, i = tid >> 4, j = tid & 15;
-  const double s0 = ordered_sum(part + tid, stride, count), s1 = ordered_sum(part + 256 + tid, stride, count),
-               s2 = ordered_sum(part + 512 + tid, stride, count);
-  G[i][j] = (i == j && i >= bw) ? 1.0 : s0;
-  G[i][16 + j] = s1;
-  G[16 + j][i] = s1;
-  G[16 + i][16 + j] = (i == j && 16 + i >= bw) ? 1.0 : s2;
+  double s[3];
+  ordered_sums(part, tid, 256, stride, count, s);
+  G[i][j] = (i == j && i >= bw) ? 1.0 : s[0];
+  G[i][16 + j] = s[1];
+  G[16 + j][i] = s[1];
+  G[16 + i][16 + j] = (i == j && 16 + i >= bw) ? 1.0 : s[2];
 }
 
 // G = L1 L1^T by one workgroup; buf holds SB SLD doubles.
-__device__ void panel_factor(const double *part, int count, int bw, double *buf, PanelSmall *sm, int *flag) {
+__device__ __forceinline__ void panel_factor(const double *part, int count, int bw, double *buf, PanelSmall *sm, int *flag) {
   __shared__ double rdsh[SB];
   double(*G)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
   const int tid = threadIdx.x;
@@ -499,7 +571,9 @@ panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, int bw, Pa
 }
 
 // Q = P L1^-T, one row per thread, and the partial sums of Q^T Q; for a pair's
-// second panel also of Wa^T Q and Ya^T Q.
+// second panel also of Wa^T Q and Ya^T Q.  Latency: the panel and L1 are loaded
+// in one batch and L1's elements reach the rows' threads by DPP, from registers
+// (24 -> 10.7 us at 5859 rows; four batches and scalar loads of L1 before).
 template <bool SECOND>
 __global__ void __launch_bounds__(PROWS)
 panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const PanelSmall *__restrict__ sm,
@@ -509,21 +583,46 @@ panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const
   double(*S)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
   const int row0 = blockIdx.x * PROWS;
-#pragma unroll 8
+  // R1's row j at lane li: columns li (ra, j < 16) and 16 + li (rb)
+  double q[SB], ra[16], rb[SB];
+  const int c0 = tid % SB;
+#pragma unroll
   for (int it = 0; it < SB; ++it) {
-    const int e = it * PROWS + tid, r = e / SB, c = e % SB;
-    S[r][c] = (row0 + r < m && c < bw) ? P[(long long)(row0 + r) * ldp + c] : 0.0;
+    const int r = it * (PROWS / SB) + tid / SB;
+    q[it] = (row0 + r < m && c0 < bw) ? P[(long long)(row0 + r) * ldp + c0] : 0.0;
   }
+#pragma unroll
+  for (int j = 0; j < 16; ++j) ra[j] = sm->R1[j * SB + li];
+#pragma unroll
+  for (int j = 0; j < SB; ++j) rb[j] = sm->R1[j * SB + 16 + li];
+  const double rda = sm->rd1[li], rdb = sm->rd1[16 + li];
+#pragma unroll
+  for (int it = 0; it < SB; ++it) S[it * (PROWS / SB) + tid / SB][c0] = q[it];
   __syncthreads();
-  double q[SB];
 #pragma unroll
   for (int j = 0; j < SB; ++j) q[j] = S[tid][j];
-#pragma unroll
-  for (int j = 0; j < SB; ++j) {
-    q[j] *= sm->rd1[j];
-#pragma unroll
-    for (int k = j + 1; k < SB; ++k) q[k] = fma(-q[j], sm->R1[j * SB + k], q[k]);
-  }
+  for_each_index<16>([&](auto ij) {
+    constexpr int j = decltype(ij)::value;
+    q[j] *= row_bcast<j>(rda);
+    const double x = -q[j];
+    for_each_index<15 - j>([&](auto ik) {
+      constexpr int k = j + 1 + decltype(ik)::value;
+      q[k] = fma(row_bcast<k>(ra[j]), x, q[k]);
+    });
+    for_each_index<16>([&](auto ik) {
+      constexpr int k = decltype(ik)::value;
+      q[16 + k] = fma(row_bcast<k>(rb[j]), x, q[16 + k]);
+    });
+  });
+  for_each_index<16>([&](auto ij) {
+    constexpr int j = decltype(ij)::value;
+    q[16 + j] *= row_bcast<j>(rdb);
+    const double x = -q[16 + j];
+    for_each_index<15 - j>([&](auto ik) {
+      constexpr int k = j + 1 + decltype(ik)::value;
+      q[16 + k] = fma(row_bcast<k>(rb[16 + j]), x, q[16 + k]);
+    });
+  });
 #pragma unroll
   for (int j = 0; j < SB; ++j) S[tid][j] = q[j];
   __syncthreads();
@@ -594,7 +693,7 @@ panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const
 // (see the head of this file), by one workgroup, and V1, V2 of a pair's second
 // panel; buf holds 4 SB SLD + SB doubles.
 template <bool SECOND>
-__device__ void panel_reconstruct(const double *__restrict__ Q, const double *part, int count, int bw,
+__device__ __forceinline__ void panel_reconstruct(const double *__restrict__ Q, const double *part, int count, int bw,
                                   const double *__restrict__ Ya, const double *__restrict__ Wa, double *buf,
                                   PanelSmall *__restrict__ sm, int *flag, double *__restrict__ Bk) {
   constexpr int PART = SECOND ? Q_PART2 : Q_PART;
@@ -656,27 +755,27 @@ __device__ void panel_reconstruct(const double *__restrict__ Q, const double *pa
 #pragma unroll
   for (int r = 0; r < 4; ++r) H[i0 + 4 * r][j0] -= h[r];
   __syncthreads();
-  // wave 0: S, Y1 and U, then T; wave 1: U^-1
-  if (wave == 0) {
-    const double mysign = lu32(H, rdsh, lane);
-    if (lane < SB) sg[lane] = mysign;
-  }
+  if (wave == 0) lu32(H, rdsh, sg, lane);  // S, Y1 and U
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int e = q * 256 + tid;
     L[e / SB][e % SB] = phi[q];
   }
   __syncthreads();
-  if (wave == 0) tfactor32(H, T, sg[lane & (SB - 1)], lane);
-  if (wave == 1) invert_upper32(H, rdsh, G, lane);
-  __syncthreads();
+  invert_factors32(H, rdsh, G, T, lane, wave);  // U^-1 and Y1^-1
   const d4 pu = prod32<false, false>(L, G, wave, li, lk);
+  d4 tf{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const int i = 16 * (wave >> 1) + li, k = 4 * s + lk;
+    tf = mfma(k >= i ? -H[i][k] * sg[k] : 0.0, T[j0][k], tf);
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = i0 + 4 * r, j = j0, e = i * SB + j;
     sm->M2[e] = j < bw ? G[i][j] - pu[r] : 0.0;
     sm->SU[e] = j < bw ? sg[i] * G[i][j] : 0.0;
-    sm->T[e] = (i < bw && j < bw) ? T[i][j] : 0.0;
+    sm->T[e] = (i <= j && j < bw) ? tf[r] : 0.0;
     // column j of the panel is column SB - bw + j of its block
     if (j < bw) Bk[i * SB + SB - bw + j] = i <= j ? sg[i] * b[r] : 0.0;
     else Bk[i * SB + j - bw] = 0.0;
@@ -695,11 +794,13 @@ __device__ void panel_reconstruct(const double *__restrict__ Q, const double *pa
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       const double *Z = p ? Ya : Wa;
+      double c[4];
+      ordered_sums(part + 768 + p * SB * SB, tid, 256, PART, count, c);
       __syncthreads();
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int e = q * 256 + tid;
-        T[e / SB][e % SB] = ordered_sum(part + 768 + p * SB * SB + e, PART, count);
+        T[e / SB][e % SB] = c[q];
         L[e / SB][e % SB] = Z[e];
       }
       __syncthreads();
@@ -714,10 +815,11 @@ __device__ void panel_reconstruct(const double *__restrict__ Q, const double *pa
 // Xq = A22^T Q over the columns from A (A22's own, then u's): workgroup
 // (32 columns, split s), its four waves on consecutive parts of the split's
 // rows, summed in order.  A's rows are read 16 doubles a quarter wave.
-// Workgroup 0 does the panel's small matrices instead: about 25 us of
-// dependent steps, hidden behind the product.
+// Workgroup 0 does the panel's small matrices instead: about 13 us of
+// dependent steps, hidden behind the product.  (Three workgroups a CU: its
+// registers are bounded by what the product needs.)
 template <bool SECOND>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 3)
 panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int bw, int splits,
                const double *__restrict__ Q, double *__restrict__ Xpart, const double *__restrict__ part,
                int parts2, const double *__restrict__ Ya, const double *__restrict__ Wa,
@@ -773,9 +875,10 @@ panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int b
   }
 }
 
-// Y, X and E2 (see the head of this file), 128 rows per workgroup, 32 a wave.
+// Y, X and E2 (see the head of this file), 128 rows per workgroup, 16 a wave
+// (eight waves of 16: 21 us at 5859 rows, four of 32: 25).
 template <bool SECOND>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(XTHREADS)
 panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__restrict__ A, long long lda, int m,
                   int mx, const double *__restrict__ Q, const double *__restrict__ Ya,
                   const double *__restrict__ Wa, const PanelSmall *__restrict__ sm_in, PanelSmall *__restrict__ sm,
@@ -788,8 +891,8 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
   const int row0 = blockIdx.x * XROWS;
 #pragma unroll 4
-  for (int it = 0; it < XROWS * SB / 256; ++it) {
-    const int e = it * 256 + tid, r = e / SB, c = e % SB;
+  for (int it = 0; it < XROWS * SB / XTHREADS; ++it) {
+    const int e = it * XTHREADS + tid, r = e / SB, c = e % SB;
     const long long o = row0 + r < mx ? (long long)row0 * SB + e : 0;
     double v[SPECTRAL_MAX_SPLITS], x = 0.0;
 #pragma unroll
@@ -800,14 +903,12 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
     Xs[r][c] = x;
     Ys[r][c] = row0 + r < m ? y : 0.0;
   }
-  // this wave's 32 rows: m, mx are multiples of 32
-  const int wr = 32 * wave, row = row0 + wr;
+  // this wave's 16 rows: m, mx are multiples of 32
+  const int wr = 16 * wave, row = row0 + wr;
   const bool in = row < mx, mat = row < m;
-  double st[2][8];  // the first SB rows of A22 at this wave's columns
+  double st[8];  // the first SB rows of A22 at this wave's columns
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) st[a][s] = in ? -A[(long long)(4 * s + lk) * lda + row + 16 * a + li] : 0.0;
+  for (int s = 0; s < 8; ++s) st[s] = in ? -A[(long long)(4 * s + lk) * lda + row + li] : 0.0;
   double m2[2][8], su[2][8];
 #pragma unroll
   for (int b = 0; b < 2; ++b)
@@ -817,65 +918,50 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
       su[b][s] = sm_in->SU[(4 * s + lk) * SB + 16 * b + li];
     }
   __syncthreads();
-  d4 x[2][2], y[2][2];
+  d4 x[2], y[2];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < 2; ++b) {
+    x[b] = d4{0.0, 0.0, 0.0, 0.0};
+    y[b] = x[b];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      x[a][b] = d4{0.0, 0.0, 0.0, 0.0};
-      y[a][b] = x[a][b];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int i = wr + 16 * a + li, k = 4 * s + lk;
-        x[a][b] = mfma(Xs[i][k], m2[b][s], x[a][b]);
-        x[a][b] = mfma(st[a][s], su[b][s], x[a][b]);
-        y[a][b] = mfma(Ys[i][k], m2[b][s], y[a][b]);
-      }
+    for (int s = 0; s < 8; ++s) {
+      const int i = wr + li, k = 4 * s + lk;
+      x[b] = mfma(Xs[i][k], m2[b][s], x[b]);
+      x[b] = mfma(st[s], su[b][s], x[b]);
+      y[b] = mfma(Ys[i][k], m2[b][s], y[b]);
     }
+  }
   if (SECOND) {
     // what the first panel's update would have taken from A22
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const int k = 4 * s + lk;
-      double v1[2], v2[2];
+      const long long o = (long long)(row + li) * SB + k;
+      const double wa = in ? -Wa[o] : 0.0, ya = mat ? -Ya[o] : 0.0;
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        v1[b] = sm_in->V1[k * SB + 16 * b + li];
-        v2[b] = sm_in->V2[k * SB + 16 * b + li];
-      }
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const long long o = (long long)(row + 16 * a + li) * SB + k;
-        const double wa = in ? -Wa[o] : 0.0, ya = mat ? -Ya[o] : 0.0;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          x[a][b] = mfma(wa, v2[b], x[a][b]);
-          x[a][b] = mfma(ya, v1[b], x[a][b]);
-        }
+        x[b] = mfma(wa, sm_in->V2[k * SB + 16 * b + li], x[b]);
+        x[b] = mfma(ya, sm_in->V1[k * SB + 16 * b + li], x[b]);
       }
     }
   }
-  if (row == 0) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) y[a][b][r] -= sm_in->SU[(16 * a + 4 * r + lk) * SB + 16 * b + li];
-  }
-  wave_sync();  // each wave reads and writes its own rows of Xs and Ys
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
+  if (row < SB) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = 16 * a + 4 * r + lk, j = 16 * b + li;
-        if (in) X[(long long)(row + i) * SB + j] = x[a][b][r];
-        if (mat) Y[(long long)(row + i) * SB + j] = y[a][b][r];
-        Xs[wr + i][j] = x[a][b][r];
-        Ys[wr + i][j] = mat ? y[a][b][r] : 0.0;
-      }
+      for (int r = 0; r < 4; ++r) y[b][r] -= sm_in->SU[(row + 4 * r + lk) * SB + 16 * b + li];
+  }
+  wave_sync();  // each wave reads and writes its own rows of Xs and Ys
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 4 * r + lk, j = 16 * b + li;
+      if (in) X[(long long)(row + i) * SB + j] = x[b][r];
+      if (mat) Y[(long long)(row + i) * SB + j] = y[b][r];
+      Xs[wr + i][j] = x[b][r];
+      Ys[wr + i][j] = mat ? y[b][r] : 0.0;
+    }
   if (row0 >= m) return;  // the whole workgroup: rows of u only
   __syncthreads();
   d4 acc[2][2];
@@ -884,7 +970,7 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int s = 0; s < XROWS / 16; ++s) {
+  for (int s = 0; s < 4; ++s) {
     const int k = wr + 4 * s + lk;
     const double y0 = Ys[k][li], y1 = Ys[k][16 + li], x0 = Xs[k][li], x1 = Xs[k][16 + li];
     acc[0][0] = mfma(y0, x0, acc[0][0]);
@@ -901,31 +987,43 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
       for (int r = 0; r < 4; ++r) buf[wave * SB * SB + (16 * a + 4 * r + lk) * SB + 16 * b + li] = acc[a][b][r];
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = q * 256 + tid;
-    put_through(part + (long long)blockIdx.x * SB * SB + e,
-                ((buf[e] + buf[SB * SB + e]) + buf[2 * SB * SB + e]) + buf[3 * SB * SB + e]);
+  for (int q = 0; q < SB * SB / XTHREADS; ++q) {
+    const int e = q * XTHREADS + tid;
+    double v = buf[e];
+#pragma unroll
+    for (int w = 1; w < XTHREADS / 64; ++w) v += buf[w * SB * SB + e];
+    put_through(part + (long long)blockIdx.x * SB * SB + e, v);
   }
   const int count = (m + XROWS - 1) / XROWS;
   if (!last_arrival(ticket, count, &last)) return;
   double(*M)[SLD] = Xs;
   double(*T)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + SB * SLD);
   double(*MT)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + 2 * SB * SLD);
+  constexpr int PER = SB * SB / XTHREADS;
+  double t[PER], c[PER];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = q * 256 + tid;
-    M[e / SB][e % SB] = ordered_sum(part + e, SB * SB, count);
-    T[e / SB][e % SB] = sm_in->T[e];
+  for (int q = 0; q < PER; ++q) t[q] = sm_in->T[q * XTHREADS + tid];
+  ordered_sums(part, tid, XTHREADS, SB * SB, count, c);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int e = q * XTHREADS + tid;
+    M[e / SB][e % SB] = c[q];
+    T[e / SB][e % SB] = t[q];
   }
   __syncthreads();
+  // a tile a wave for the first four
   const int i0 = 16 * (wave >> 1) + lk, j0 = 16 * (wave & 1) + li;
-  const d4 mt = prod32<false, false>(M, T, wave, li, lk);
+  if (wave < 4) {
+    const d4 mt = prod32<false, false>(M, T, wave, li, lk);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) MT[i0 + 4 * r][j0] = mt[r];
+    for (int r = 0; r < 4; ++r) MT[i0 + 4 * r][j0] = mt[r];
+  }
   __syncthreads();
-  const d4 e2 = prod32<true, false>(T, MT, wave, li, lk);
+  if (wave < 4) {
+    const d4 e2 = prod32<true, false>(T, MT, wave, li, lk);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) sm->E2[(i0 + 4 * r) * SB + j0] = 0.5 * e2[r];
+    for (int r = 0; r < 4; ++r) sm->E2[(i0 + 4 * r) * SB + j0] = 0.5 * e2[r];
+  }
 }
 
 // W = X T - Y E2 for the m matrix rows, W = X T for the rows of u; 16 rows a wave.
@@ -1376,11 +1474,11 @@ void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, c
     if (second) {
       panel_q_kernel<true><<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, Ya, Wa, w.Q, w.part);
       panel_x_kernel<true><<<gx, 256, 0, s>>>(A22, lda, m, mx, bw, splits, w.Q, w.Xpart, w.part, ng, Ya, Wa, sm, w.flag, Bk);
-      panel_xsum_kernel<true><<<gs, 256, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, Ya, Wa, sm, sm, w.X, Y, w.part, w.ticket);
+      panel_xsum_kernel<true><<<gs, XTHREADS, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, Ya, Wa, sm, sm, w.X, Y, w.part, w.ticket);
     } else {
       panel_q_kernel<false><<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, nullptr, nullptr, w.Q, w.part);
       panel_x_kernel<false><<<gx, 256, 0, s>>>(A22, lda, m, mx, bw, splits, w.Q, w.Xpart, w.part, ng, nullptr, nullptr, sm, w.flag, Bk);
-      panel_xsum_kernel<false><<<gs, 256, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, nullptr, nullptr, sm, sm, w.X, Y, w.part, w.ticket);
+      panel_xsum_kernel<false><<<gs, XTHREADS, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, nullptr, nullptr, sm, sm, w.X, Y, w.part, w.ticket);
     }
     panel_w_kernel<<<(mx + 63) / 64, 256, 0, s>>>(w.X, Y, m, mx, sm, W);
     const double *y0 = second ? Ya : Y, *w0 = second ? Wa : W, *y1 = second ? Y : nullptr, *w1 = second ? W : nullptr;
