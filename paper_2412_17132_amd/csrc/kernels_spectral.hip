@@ -34,10 +34,14 @@
 //                  M2 = (1 - Phi) U^-1, SU = S U^-1, Xq summed over its splits;
 //                  Y^T X, and in the last workgroup E2 = T^T (Y^T X) T / 2;
 //   panel_w        W = X T - Y E2;
-//   panel_update   A22 -= Y W^T + W Y^T (tiles on or above the diagonal, each
-//                  written with its mirror), u -= Y (u^T Y T)^T; the tiles that
+//   panel_update   A22 -= Y W^T + W Y^T, u -= Y (u^T Y T)^T; the tiles that
 //                  hold the next panel also form its G, and the last of them
 //                  the Cholesky factor, while the others go on.
+// Of the matrix only the 32 x 32 blocks on and above the diagonal are kept up to
+// date; panels are read as rows, and panel_x takes A22's columns below the
+// diagonal from its rows.  (With the mirrors written and read instead: update
+// 84 -> 71 ms of a reduction of order 16524, panel_x 94 -> 87; 7.4 -> 6.0 ms and
+// no change at 5859.)
 // Panels go in pairs: after the first of a pair only the columns of the second
 // (and u's rows beside them) are updated, the second takes what is missing of
 // A22 in its products (A22 Y = A Y - Ya (Wa^T Y) - Wa (Ya^T Y)), and one update
@@ -431,8 +435,8 @@ static unsigned triangle_tiles(int nt) { return (unsigned)((nt + 1) / 2) * (unsi
 
 // out[i][j] = sum_P A[P][i] B[P][j], 64 x 64 tiles, one 32 x 32 quadrant per
 // wave on MFMA; the operands are rows of A and B (16 consecutive doubles a
-// quarter wave), read through the L1.  SYM: A = B, tiles i <= j with their
-// mirror, and diag2[i - pad] is added on the diagonal.  Sizes are multiples of 32.
+// quarter wave), read through the L1.  SYM: A = B, tiles i <= j, and
+// diag2[i - pad] is added on the diagonal.  Sizes are multiples of 32.
 template <bool SYM>
 __global__ void __launch_bounds__(256)
 spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__restrict__ B, int ldb,
@@ -484,7 +488,6 @@ spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__rest
         double x = acc[a][b][r];
         if (SYM && i == j && i >= pad) x += diag2[i - pad];
         out[(long long)i * ldo + j] = x;
-        if (SYM && ti != tj) out[(long long)j * ldo + i] = x;
       }
 }
 
@@ -550,11 +553,11 @@ panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, int bw, Pa
   double(*S)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
   const int row0 = blockIdx.x * PROWS;
-#pragma unroll 8
-  for (int it = 0; it < SB; ++it) {
-    const int e = it * PROWS + tid, r = e / SB, c = e % SB;
-    S[r][c] = (row0 + r < m && c < bw) ? P[(long long)(row0 + r) * ldp + c] : 0.0;
-  }
+  double q[SB];
+#pragma unroll
+  for (int c = 0; c < SB; ++c) q[c] = (row0 + tid < m && c < bw) ? P[(long long)c * ldp + row0 + tid] : 0.0;
+#pragma unroll
+  for (int c = 0; c < SB; ++c) S[tid][c] = q[c];
   __syncthreads();
   d4 g00{0.0, 0.0, 0.0, 0.0}, g01 = g00, g11 = g00;
 #pragma unroll 4
@@ -585,22 +588,13 @@ panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const
   const int row0 = blockIdx.x * PROWS;
   // R1's row j at lane li: columns li (ra, j < 16) and 16 + li (rb)
   double q[SB], ra[16], rb[SB];
-  const int c0 = tid % SB;
 #pragma unroll
-  for (int it = 0; it < SB; ++it) {
-    const int r = it * (PROWS / SB) + tid / SB;
-    q[it] = (row0 + r < m && c0 < bw) ? P[(long long)(row0 + r) * ldp + c0] : 0.0;
-  }
+  for (int c = 0; c < SB; ++c) q[c] = (row0 + tid < m && c < bw) ? P[(long long)c * ldp + row0 + tid] : 0.0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) ra[j] = sm->R1[j * SB + li];
 #pragma unroll
   for (int j = 0; j < SB; ++j) rb[j] = sm->R1[j * SB + 16 + li];
   const double rda = sm->rd1[li], rdb = sm->rd1[16 + li];
-#pragma unroll
-  for (int it = 0; it < SB; ++it) S[it * (PROWS / SB) + tid / SB][c0] = q[it];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < SB; ++j) q[j] = S[tid][j];
   for_each_index<16>([&](auto ij) {
     constexpr int j = decltype(ij)::value;
     q[j] *= row_bcast<j>(rda);
@@ -839,9 +833,11 @@ panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int b
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  // rows above the columns' diagonal block and it: A[k][c0 + j]
+  const int kd = min(k1, c0 + SB);
   const double *pa = A + (long long)(k0 + lk) * lda + c0 + li;
   const double *py = Q + (long long)(k0 + lk) * SB + li;
-  for (int k = k0; k < k1; k += 32) {
+  for (int k = k0; k < kd; k += 32) {
     double a0[8], a1[8], y0[8], y1[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -858,6 +854,33 @@ panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int b
       acc[0][1] = mfma(a0[s], y1[s], acc[0][1]);
       acc[1][0] = mfma(a1[s], y0[s], acc[1][0]);
       acc[1][1] = mfma(a1[s], y1[s], acc[1][1]);
+    }
+  }
+  // and below, from the stored triangle: A[c0 + j][k], two neighbours of k a lane
+  const int kl = max(k0, c0 + SB);
+  pa = A + (long long)(c0 + li) * lda + kl + 2 * lk;
+  py = Q + (long long)(kl + 2 * lk) * SB + li;
+  for (int k = kl; k < k1; k += 32) {
+    d2 a0[4], a1[4];
+    double y0[8], y1[8];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      a0[s] = *reinterpret_cast<const d2 *>(pa + 8 * s);
+      a1[s] = *reinterpret_cast<const d2 *>(pa + 16 * lda + 8 * s);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        y0[2 * s + e] = py[(8 * s + e) * SB];
+        y1[2 * s + e] = py[(8 * s + e) * SB + 16];
+      }
+    }
+    pa += 32;
+    py += 32 * SB;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      acc[0][0] = mfma(a0[s / 2][s % 2], y0[s], acc[0][0]);
+      acc[0][1] = mfma(a0[s / 2][s % 2], y1[s], acc[0][1]);
+      acc[1][0] = mfma(a1[s / 2][s % 2], y0[s], acc[1][0]);
+      acc[1][1] = mfma(a1[s / 2][s % 2], y1[s], acc[1][1]);
     }
   }
 #pragma unroll
@@ -1064,13 +1087,12 @@ panel_w_kernel(const double *__restrict__ X, const double *__restrict__ Y, int m
 }
 
 // A22 -= Y W^T + W Y^T for one panel or both of a pair, on 64 x 64 tiles on or
-// above the diagonal, the others from their mirror; and u -= Y Wu^T on the
-// columns behind the matrix (the workgroups from n_mat on).  m, mx multiples of
-// 32.  STRIP: only the first SB rows and their mirror (a pair's second panel).
-// The first row of tiles (the first workgroups) holds the next panel
-// transposed, A22[:SB, SB:], and forms its G.  A wave owns a quadrant of the
-// tile, loads its old values first, and writes the mirror through LDS so that
-// both copies go out in whole lines.
+// above the diagonal; and u -= Y Wu^T on the columns behind the matrix (the
+// workgroups from n_mat on).  m, mx multiples of 32.  STRIP: only the first SB
+// rows (a pair's second panel).  The first row of tiles (the first workgroups)
+// holds the next panel transposed, A22[:SB, SB:], and forms its G.  A wave owns
+// a quadrant of the tile (idle below the diagonal) and loads its old values
+// first.
 template <bool STRIP>
 __global__ void __launch_bounds__(256)
 panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const double *__restrict__ Ya,
@@ -1083,7 +1105,7 @@ panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
   const int nt = (m + UT - 1) / UT, mrow = STRIP ? SB : m;
   int i0, j0, jend;
-  bool mirror = false, next = false;
+  bool next = false;
   const bool mat = (int)blockIdx.x < n_mat;
   if (mat) {
     int ti = 0, tj = blockIdx.x;
@@ -1091,7 +1113,6 @@ panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const 
     i0 = ti * UT;
     j0 = tj * UT;
     jend = m;
-    mirror = STRIP || ti != tj;
     next = ti == 0 && m > SB;
   } else {
     const int q = blockIdx.x - n_mat, tj = STRIP ? q : q / nt;
@@ -1100,7 +1121,7 @@ panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const 
     jend = mx;
   }
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  const bool in = i0 + wr < mrow && j0 + wc < jend;  // the whole quadrant
+  const bool in = i0 + wr < mrow && j0 + wc < jend && i0 + wr <= j0 + wc;  // the whole quadrant
   double *At = A + (long long)(i0 + wr) * lda + j0 + wc;
   double old[2][2][4];
   if (in) {
@@ -1154,7 +1175,6 @@ panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const 
       acc[1][1] = mfma(a1, b1, acc[1][1]);
     }
   }
-  if (STRIP && j0 + wc == 0) mirror = false;  // the diagonal block
   if (in) {
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -1166,23 +1186,6 @@ panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const 
           At[(long long)(16 * a + 4 * r + lk) * lda + 16 * b + li] = x;
           old[a][b][r] = x;
         }
-  }
-  __syncthreads();  // the operands have been read
-  if (in && mirror) {
-    double *Tq = (wave & 1 ? Rs : Ls) + (wave >> 1) * SB * SLD;  // this quadrant, transposed
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Tq[(16 * b + li) * SLD + 16 * a + 4 * r + lk] = old[a][b][r];
-    wave_sync();
-    double *Am = A + (long long)(j0 + wc) * lda + i0 + wr;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int j = 2 * q + (lane >> 5), i = lane & 31;
-      Am[(long long)j * lda + i] = Tq[j * SLD + i];
-    }
   }
   if (!next) return;  // the whole workgroup
   // Ls[c][j] = A22[c][j0 + j] for c < SB, zero outside the panel
@@ -1461,7 +1464,7 @@ void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, c
     else second = false;
     // a pair saves a pass over A22 and costs about 60 us of products of its own
     pair = !(k & 1) && k + 1 < panels && m >= PAIR_ROWS;
-    const double *P = A + (long long)r0 * lda + c0 + off;
+    const double *P = A + (long long)(c0 + off) * lda + r0;  // transposed
     double *A22 = A + (long long)r0 * lda + r0;
     // rows of the first panel's Y and W from this panel's first row on
     const double *Ya = w.Y[0] + SB * SB, *Wa = w.W[0] + SB * SB;
