@@ -64,7 +64,7 @@ constexpr int SB = SPECTRAL_BAND;
 constexpr int SLD = SB + 1;   // LDS row stride of 32-wide rows
 constexpr int PROWS = 256;    // panel rows per workgroup of panel_gram
 constexpr int XROWS = 128;    // rows per workgroup of panel_xsum
-constexpr int XTHREADS = 512;
+constexpr int XTHREADS = 1024;
 constexpr int UT = 64;        // tile of the rank update and the transition matrix
 constexpr int ULD = SB + 2;   // LDS row stride of its operands (no bank conflicts)
 // Rows from which panels go in pairs: the second panel's own products cost about
@@ -433,55 +433,76 @@ __device__ __forceinline__ bool triangle_tile(int wg, int nt, int &i, int &j) {
 }
 static unsigned triangle_tiles(int nt) { return (unsigned)((nt + 1) / 2) * (unsigned)(nt + 1); }
 
-// out[i][j] = sum_P A[P][i] B[P][j], 64 x 64 tiles, one 32 x 32 quadrant per
-// wave on MFMA; the operands are rows of A and B (16 consecutive doubles a
-// quarter wave), read through the L1.  SYM: A = B, tiles i <= j, and
-// diag2[i - pad] is added on the diagonal.  Sizes are multiples of 32.
-template <bool SYM>
-__global__ void __launch_bounds__(256)
+// out[i][j] = sum_P A[P][i] B[P][j] on MFMA, a square of 16 W columns per wave,
+// four waves a workgroup; the operands are rows of A and B (16 consecutive
+// doubles a quarter wave), read through the L1 a batch of 32 / W rows ahead.
+// SYM: A = B, tiles i <= j, and diag2[i - pad] is added on the diagonal.  Sizes
+// are multiples of 32.  Bound by the matrix cores where W = 4 (half the operand
+// loads a product), which needs many tiles to fill the chip.
+template <bool SYM, int W>
+__global__ void __launch_bounds__(256, W == 4 ? 2 : 4)
 spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__restrict__ B, int ldb,
                      int M, int N, int K, const double *__restrict__ diag2, int pad,
                      double *__restrict__ out, long long ldo) {
+  constexpr int WT = 16 * W, TILE = 2 * WT, S = 8 / W;
   int ti, tj;
   if (SYM) {
-    if (!triangle_tile(blockIdx.x, (M + UT - 1) / UT, ti, tj)) return;
+    if (!triangle_tile(blockIdx.x, (M + TILE - 1) / TILE, ti, tj)) return;
   } else {
-    const int nj = (N + UT - 1) / UT;
+    const int nj = (N + TILE - 1) / TILE;
     ti = blockIdx.x / nj;
     tj = blockIdx.x - ti * nj;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
-  const int i0 = ti * UT + (wave >> 1) * 32, j0 = tj * UT + (wave & 1) * 32;
-  if (i0 >= M || j0 >= N) return;  // the whole wave
-  d4 acc[2][2];
+  const int i0 = ti * TILE + (wave >> 1) * WT, j0 = tj * TILE + (wave & 1) * WT;
+  if (i0 >= M || j0 >= N || (SYM && i0 > j0)) return;  // the whole wave
+  d4 acc[W][W];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < W; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
-  const double *pa = A + i0 + li, *pb = B + j0 + li;
-  int k = 0;
-#pragma unroll 4
-  for (; k + 4 <= K; k += 4) {
-    const double *ra = pa + (long long)(k + lk) * lda, *rb = pb + (long long)(k + lk) * ldb;
-    const double a0 = ra[0], a1 = ra[16], b0 = rb[0], b1 = rb[16];
-    acc[0][0] = mfma(a0, b0, acc[0][0]);
-    acc[0][1] = mfma(a0, b1, acc[0][1]);
-    acc[1][0] = mfma(a1, b0, acc[1][0]);
-    acc[1][1] = mfma(a1, b1, acc[1][1]);
+    for (int b = 0; b < W; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  // columns of the wave's square beyond the matrix are read from its last 32
+  int ca[W], cb[W];
+#pragma unroll
+  for (int a = 0; a < W; ++a) {
+    ca[a] = min(i0 + 16 * a, M - 16) + li;
+    cb[a] = min(j0 + 16 * a, N - 16) + li;
   }
-  if (k < K) {
-    const bool in = k + lk < K;
-    const double *ra = pa + (long long)(in ? k + lk : k) * lda, *rb = pb + (long long)(in ? k + lk : k) * ldb;
-    const double a0 = in ? ra[0] : 0.0, a1 = in ? ra[16] : 0.0, b0 = in ? rb[0] : 0.0, b1 = in ? rb[16] : 0.0;
-    acc[0][0] = mfma(a0, b0, acc[0][0]);
-    acc[0][1] = mfma(a0, b1, acc[0][1]);
-    acc[1][0] = mfma(a1, b0, acc[1][0]);
-    acc[1][1] = mfma(a1, b1, acc[1][1]);
+  double va[2][S][W], vb[2][S][W];
+  auto fetch = [&](int k, double(&x)[S][W], double(&y)[S][W]) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int r = k + 4 * s + lk;
+      const bool in = r < K;
+      const double *ra = A + (long long)(in ? r : 0) * lda, *rb = B + (long long)(in ? r : 0) * ldb;
+#pragma unroll
+      for (int a = 0; a < W; ++a) {
+        const double p = ra[ca[a]], q = rb[cb[a]];
+        x[s][a] = in ? p : 0.0;
+        y[s][a] = in ? q : 0.0;
+      }
+    }
+  };
+  auto product = [&](const double(&x)[S][W], const double(&y)[S][W]) {
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int a = 0; a < W; ++a)
+#pragma unroll
+        for (int b = 0; b < W; ++b) acc[a][b] = mfma(x[s][a], y[s][b], acc[a][b]);
+  };
+  fetch(0, va[0], vb[0]);
+  for (int k = 0; k < K; k += 8 * S) {
+    fetch(k + 4 * S, va[1], vb[1]);
+    product(va[0], vb[0]);
+    fetch(k + 8 * S, va[0], vb[0]);
+    product(va[1], vb[1]);
   }
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < W; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < W; ++b) {
+      if (i0 + 16 * a >= M || j0 + 16 * b >= N) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = i0 + 16 * a + 4 * r + lk, j = j0 + 16 * b + li;
@@ -489,6 +510,7 @@ spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__rest
         if (SYM && i == j && i >= pad) x += diag2[i - pad];
         out[(long long)i * ldo + j] = x;
       }
+    }
 }
 
 // Sum of the per-wave Gram tiles (0,0), (0,1), (1,1) through LDS: element
@@ -898,8 +920,9 @@ panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int b
   }
 }
 
-// Y, X and E2 (see the head of this file), 128 rows per workgroup, 16 a wave
-// (eight waves of 16: 21 us at 5859 rows, four of 32: 25).
+// Y, X and E2 (see the head of this file), 128 rows per workgroup, a 16 x 16
+// tile of both a wave, so that a workgroup's loads are one batch (16 waves:
+// 19.9 us at 5859 rows; eight of 16 rows: 21; four of 32: 25).
 template <bool SECOND>
 __global__ void __launch_bounds__(XTHREADS)
 panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__restrict__ A, long long lda, int m,
@@ -913,7 +936,7 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
   double(*Ys)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + XROWS * SLD);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
   const int row0 = blockIdx.x * XROWS;
-#pragma unroll 4
+#pragma unroll
   for (int it = 0; it < XROWS * SB / XTHREADS; ++it) {
     const int e = it * XTHREADS + tid, r = e / SB, c = e % SB;
     const long long o = row0 + r < mx ? (long long)row0 * SB + e : 0;
@@ -926,33 +949,24 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
     Xs[r][c] = x;
     Ys[r][c] = row0 + r < m ? y : 0.0;
   }
-  // this wave's 16 rows: m, mx are multiples of 32
-  const int wr = 16 * wave, row = row0 + wr;
+  // this wave's 16 x 16 tile of X and of Y: m, mx are multiples of 32
+  const int wr = 16 * (wave >> 1), wc = 16 * (wave & 1), row = row0 + wr;
   const bool in = row < mx, mat = row < m;
-  double st[8];  // the first SB rows of A22 at this wave's columns
+  double st[8], m2[8], su[8];  // st: the first SB rows of A22 at the tile's rows
 #pragma unroll
-  for (int s = 0; s < 8; ++s) st[s] = in ? -A[(long long)(4 * s + lk) * lda + row + li] : 0.0;
-  double m2[2][8], su[2][8];
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      m2[b][s] = sm_in->M2[(4 * s + lk) * SB + 16 * b + li];
-      su[b][s] = sm_in->SU[(4 * s + lk) * SB + 16 * b + li];
-    }
+  for (int s = 0; s < 8; ++s) {
+    st[s] = in ? -A[(long long)(4 * s + lk) * lda + row + li] : 0.0;
+    m2[s] = sm_in->M2[(4 * s + lk) * SB + wc + li];
+    su[s] = sm_in->SU[(4 * s + lk) * SB + wc + li];
+  }
   __syncthreads();
-  d4 x[2], y[2];
+  d4 x{0.0, 0.0, 0.0, 0.0}, x2 = x, y = x;
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    x[b] = d4{0.0, 0.0, 0.0, 0.0};
-    y[b] = x[b];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int i = wr + li, k = 4 * s + lk;
-      x[b] = mfma(Xs[i][k], m2[b][s], x[b]);
-      x[b] = mfma(st[s], su[b][s], x[b]);
-      y[b] = mfma(Ys[i][k], m2[b][s], y[b]);
-    }
+  for (int s = 0; s < 8; ++s) {
+    const int i = wr + li, k = 4 * s + lk;
+    x = mfma(Xs[i][k], m2[s], x);
+    x2 = mfma(st[s], su[s], x2);
+    y = mfma(Ys[i][k], m2[s], y);
   }
   if (SECOND) {
     // what the first panel's update would have taken from A22
@@ -961,78 +975,51 @@ panel_xsum_kernel(const double *__restrict__ Xpart, int splits, const double *__
       const int k = 4 * s + lk;
       const long long o = (long long)(row + li) * SB + k;
       const double wa = in ? -Wa[o] : 0.0, ya = mat ? -Ya[o] : 0.0;
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        x[b] = mfma(wa, sm_in->V2[k * SB + 16 * b + li], x[b]);
-        x[b] = mfma(ya, sm_in->V1[k * SB + 16 * b + li], x[b]);
-      }
+      x = mfma(wa, sm_in->V2[k * SB + wc + li], x);
+      x2 = mfma(ya, sm_in->V1[k * SB + wc + li], x2);
     }
   }
+  x += x2;
   if (row < SB) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) y[b][r] -= sm_in->SU[(row + 4 * r + lk) * SB + 16 * b + li];
+    for (int r = 0; r < 4; ++r) y[r] -= sm_in->SU[(row + 4 * r + lk) * SB + wc + li];
   }
-  wave_sync();  // each wave reads and writes its own rows of Xs and Ys
+  __syncthreads();
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = 4 * r + lk, j = 16 * b + li;
-      if (in) X[(long long)(row + i) * SB + j] = x[b][r];
-      if (mat) Y[(long long)(row + i) * SB + j] = y[b][r];
-      Xs[wr + i][j] = x[b][r];
-      Ys[wr + i][j] = mat ? y[b][r] : 0.0;
-    }
+  for (int r = 0; r < 4; ++r) {
+    const int i = 4 * r + lk, j = wc + li;
+    if (in) X[(long long)(row + i) * SB + j] = x[r];
+    if (mat) Y[(long long)(row + i) * SB + j] = y[r];
+    Xs[wr + i][j] = x[r];
+    Ys[wr + i][j] = mat ? y[r] : 0.0;
+  }
   if (row0 >= m) return;  // the whole workgroup: rows of u only
   __syncthreads();
-  d4 acc[2][2];
+  // Y^T X: tile wave % 4 over the rows 32 (wave / 4) ..
+  d4 acc{0.0, 0.0, 0.0, 0.0};
+  const int ta = 16 * ((wave >> 1) & 1);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int k = wr + 4 * s + lk;
-    const double y0 = Ys[k][li], y1 = Ys[k][16 + li], x0 = Xs[k][li], x1 = Xs[k][16 + li];
-    acc[0][0] = mfma(y0, x0, acc[0][0]);
-    acc[0][1] = mfma(y0, x1, acc[0][1]);
-    acc[1][0] = mfma(y1, x0, acc[1][0]);
-    acc[1][1] = mfma(y1, x1, acc[1][1]);
+  for (int s = 0; s < 8; ++s) {
+    const int k = 32 * (wave >> 2) + 4 * s + lk;
+    acc = mfma(Ys[k][ta + li], Xs[k][wc + li], acc);
   }
   __syncthreads();
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) buf[wave * SB * SB + (16 * a + 4 * r + lk) * SB + 16 * b + li] = acc[a][b][r];
+  for (int r = 0; r < 4; ++r) buf[(wave >> 2) * SB * SB + (ta + 4 * r + lk) * SB + wc + li] = acc[r];
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < SB * SB / XTHREADS; ++q) {
-    const int e = q * XTHREADS + tid;
-    double v = buf[e];
-#pragma unroll
-    for (int w = 1; w < XTHREADS / 64; ++w) v += buf[w * SB * SB + e];
-    put_through(part + (long long)blockIdx.x * SB * SB + e, v);
-  }
+  put_through(part + (long long)blockIdx.x * SB * SB + tid,
+              ((buf[tid] + buf[SB * SB + tid]) + buf[2 * SB * SB + tid]) + buf[3 * SB * SB + tid]);
   const int count = (m + XROWS - 1) / XROWS;
   if (!last_arrival(ticket, count, &last)) return;
   double(*M)[SLD] = Xs;
   double(*T)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + SB * SLD);
   double(*MT)[SLD] = reinterpret_cast<double(*)[SLD]>(buf + 2 * SB * SLD);
-  constexpr int PER = SB * SB / XTHREADS;
-  double t[PER], c[PER];
-#pragma unroll
-  for (int q = 0; q < PER; ++q) t[q] = sm_in->T[q * XTHREADS + tid];
-  ordered_sums(part, tid, XTHREADS, SB * SB, count, c);
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = q * XTHREADS + tid;
-    M[e / SB][e % SB] = c[q];
-    T[e / SB][e % SB] = t[q];
-  }
+  static_assert(XTHREADS == SB * SB && XROWS == 128, "an element a thread, eight tiles of rows");
+  double c[1];
+  const double tv = sm_in->T[tid];
+  ordered_sums(part, tid, 0, SB * SB, count, c);
+  M[tid / SB][tid % SB] = c[0];
+  T[tid / SB][tid % SB] = tv;
   __syncthreads();
   // a tile a wave for the first four
   const int i0 = 16 * (wave >> 1) + lk, j0 = 16 * (wave & 1) + li;
@@ -1447,10 +1434,15 @@ void launch_spectral_pairs(const double *M_oo, const double *M_ov, int n_aux, in
 
 void launch_spectral_matrix(const double *V, int np, const double *Bp, int Rp, int n_aux, const double *diag2,
                             int pad, double *A, long long lda, hipStream_t s) {
-  const int nt = (np + UT - 1) / UT;
-  spectral_gemm_kernel<true><<<triangle_tiles(nt), 256, 0, s>>>(V, np, V, np, np, np, n_aux, diag2, pad, A, lda);
-  spectral_gemm_kernel<false><<<nt * ((Rp + UT - 1) / UT), 256, 0, s>>>(V, np, Bp, Rp, np, Rp, n_aux, nullptr, 0,
-                                                                      A + np, lda);
+  const int nt = (np + UT - 1) / UT, nt2 = (np + 2 * UT - 1) / (2 * UT);
+  // 128 x 128 tiles from where they are twice what runs at once (512): at order
+  // 16544 15.5 -> 11.0 ms, at 5888 1.03 -> 0.85 ms, at 1056 0.053 against 0.079.
+  if (np >= 4096)
+    spectral_gemm_kernel<true, 4><<<triangle_tiles(nt2), 256, 0, s>>>(V, np, V, np, np, np, n_aux, diag2, pad, A, lda);
+  else
+    spectral_gemm_kernel<true, 2><<<triangle_tiles(nt), 256, 0, s>>>(V, np, V, np, np, np, n_aux, diag2, pad, A, lda);
+  spectral_gemm_kernel<false, 2><<<nt * ((Rp + UT - 1) / UT), 256, 0, s>>>(V, np, Bp, Rp, np, Rp, n_aux, nullptr, 0,
+                                                                          A + np, lda);
 }
 
 void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, const SpectralWork &w, hipStream_t s) {
