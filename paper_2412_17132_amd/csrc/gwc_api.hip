@@ -1015,16 +1015,16 @@ void spectral_screen(Spectral &sp, const TaskList &tl, int R, double2 *W_out, hi
   if (T == 0) return;
   sp.tasks.emplace_back();
   std::vector<SpectralTask> &tasks = sp.tasks.back();
-  bool real = true;
+  const bool real = std::all_of(tl.z.begin(), tl.z.end(), [](const double2 &z) { return z.x == 0.0; });
+  const int most = real ? SPECTRAL_MAX_RHS : 1;
   for (size_t t = 0; t < T; ++t) {
     const double x = tl.z[t].x, y = tl.z[t].y;
-    real = real && x == 0.0;
     SpectralTask k{(x - y) * (x + y), 2.0 * x * y, tl.out_base[t], tl.out_stride[t], sp.column[tl.n[t]] + std::max(tl.m[t], 0), 1};
-    for (int r = 0; r < R; r += SPECTRAL_MAX_RHS) {
+    for (int r = 0; r < R; r += most) {
       SpectralTask q = k;
       q.out_base += (long long)r * k.out_stride;
       q.col += r;
-      q.nrhs = std::min(SPECTRAL_MAX_RHS, R - r);
+      q.nrhs = std::min(most, R - r);
       tasks.push_back(q);
     }
   }

@@ -115,7 +115,7 @@ constexpr int SPECTRAL_MAX_RHS = 16;
 struct SpectralTask {
   double z2_re, z2_im;  // z^2
   long long out_base;
-  int out_stride, col, nrhs;  // vectors col .. col + nrhs - 1, nrhs <= SPECTRAL_MAX_RHS
+  int out_stride, col, nrhs;  // vectors col .. col + nrhs - 1: nrhs <= SPECTRAL_MAX_RHS, 1 off the imaginary axis
 };
 struct SpectralWork {  // doubles unless stated
   double *Q, *Y[2];    // np x SPECTRAL_BAND

@@ -111,6 +111,16 @@ __device__ __forceinline__ void for_each_index(F &&f) {
   for_each_index(f, std::make_integer_sequence<int, N>{});
 }
 
+// The sum over the four rows of 16 lanes.
+__device__ __forceinline__ double row_sum(double v) {
+  auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
 // Orders a wave's LDS accesses across its lanes.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1246,10 +1256,11 @@ spectral_transpose_kernel(const double *__restrict__ A, long long lda, int np, i
     if (r0 + q + y < R) Ut[(long long)(r0 + q + y) * np + i0 + x] = t[x][q + y];
 }
 
-// W = u^T (z^2 - C)^-1 u of a task's one to 16 vectors u by elimination of the
-// band, one wave per task.
+// W = u^T (z^2 - C)^-1 u of a task's one to 16 vectors u (one where COMPLEX) by
+// elimination of the band, two waves per task: one from the first row down, the other from the
+// last row up, to the two blocks in the middle, which the first finishes.
 //
-// Step p eliminates 16 rows.  Their 48 columns inside the band and 16 vectors
+// A step eliminates 16 rows.  Their 48 columns inside the band and 16 vectors
 // sit one column per lane (rows in registers); a pivot's multipliers are the
 // pivot row scaled by 1/d (the matrix is symmetric), broadcast from the lanes
 // that hold them.  z^2 - C has the imaginary part 2 x eta 1, or is definite on
@@ -1257,35 +1268,48 @@ spectral_transpose_kernel(const double *__restrict__ A, long long lda, int np, i
 // two blocks and their vectors is a product of the eliminated rows, on MFMA
 // (accumulators initialised with the band itself); the layouts change through
 // the wave's LDS.  COMPLEX = false is the imaginary axis (z^2 = -w^2, real).
+// Bound by the steps' chains where there are fewer tasks than fill the chip
+// (order 5859, 1029 complex tasks: 5.1 -> 2.6 ms against one wave a task and sixteen columns), by
+// instructions beyond that.
 template <bool COMPLEX>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(128, COMPLEX ? 2 : 3)
 spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut, int np, int nb16,
                   const SpectralTask *__restrict__ tasks, double2 *__restrict__ W_out) {
   constexpr int C2 = COMPLEX ? 2 : 1;
-  __shared__ double row[16 * 64 * C2];  // eliminated rows, [t][column]
-  __shared__ double mul[16 * 32 * C2];  // the same times 1/d_t, columns 16 .. 47
+  __shared__ double rows[2][16 * 64 * C2];  // eliminated rows, [t][column]
+  __shared__ double2 invs[2][16];           // 1/d_t
   const SpectralTask task = tasks[blockIdx.x];
-  const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const bool up = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double *const row = rows[up];
+  double2 *const dinv = invs[up];
   const double zr = task.z2_re, zi = COMPLEX ? task.z2_im : 0.0;
-  const double *u = Ut + (long long)(task.col + min(li, task.nrhs - 1)) * np;
+  const double *u = Ut + (long long)(task.col + (COMPLEX ? 0 : min(li, task.nrhs - 1))) * np;
   const bool urow = li < task.nrhs;
 
-  // tile `which` of block p in accumulator layout: element r is [4 r + lk][li]
-  auto tile = [&](int p, int which) {
-    const double *b = band + (long long)p * 768 + which * 256 + lane;
-    return d4{b[0], b[64], b[128], b[192]};
+  // Blocks p and p + `which` of the wave's order, in accumulator layout: element
+  // r is [4 r + lk][li].  The upward wave's indices run backwards: its diagonal
+  // tiles are turned by 180 degrees, the others transposed as well.
+  auto tile_of = [&](bool back, int p, int which) {
+    const double *b = band + (long long)(back ? nb16 - 1 - p - which : p) * 768 + which * 256 +
+                      (!back ? lane : which ? 16 * (15 - li) + 15 - lk : 255 - lane);
+    const int st = !back ? 64 : which ? -4 : -64;
+    return d4{b[0], b[st], b[2 * st], b[3 * st]};
   };
-  auto vec = [&](int p) {
-    d4 v{0.0, 0.0, 0.0, 0.0};
-    if (p < nb16) {
+  auto tile = [&](int p, int which) { return tile_of(up, p, which); };
+  auto vec_of = [&](bool back, int p) {
+    d4 v;
+    const double *x = u + (back ? np - 1 - 16 * p - lk : 16 * p + lk);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const double x = u[16 * p + 4 * r + lk];
-        v[r] = urow ? x : 0.0;
-      }
+    for (int r = 0; r < 4; ++r) {
+      const double y = x[back ? -4 * r : 4 * r];
+      v[r] = urow ? y : 0.0;
     }
     return v;
   };
+  auto vec = [&](int p) { return vec_of(up, p); };
+  // COMPLEX: element li of the one vector's block p
+  auto one_of = [&](bool back, int p) { return u[back ? np - 1 - 16 * p - li : 16 * p + li]; };
   auto shifted_diag = [&](const d4 &d, d4 &re, d4 &im) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -1294,44 +1318,126 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
       im[r] = on ? zi : 0.0;
     }
   };
-  auto put = [&](double *buf, int ld, int c, const d4 &re, const d4 &im) {
+  auto put = [&](double *buf, int c, const d4 &re, const d4 &im) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      double *q = buf + ((4 * r + lk) * ld + c + li) * C2;
+      double *q = buf + ((4 * r + lk) * 64 + c + li) * C2;
       if (COMPLEX) *reinterpret_cast<double2 *>(q) = make_double2(re[r], im[r]);
       else *q = re[r];
     }
   };
+  auto get = [&](const double *buf, int o, double &re, double &im) {
+    if (COMPLEX) {
+      const double2 v = *reinterpret_cast<const double2 *>(buf + o * C2);
+      re = v.x;
+      im = v.y;
+    } else {
+      re = buf[o];
+      im = 0.0;
+    }
+  };
   const d4 zero{0.0, 0.0, 0.0, 0.0};
+  const int half = nb16 / 2 - 1;  // steps of each wave; nb16 is even
   d4 s11r, s11i, s22r, s22i;
   shifted_diag(tile(0, 0), s11r, s11i);
   shifted_diag(tile(1, 0), s22r, s22i);
-  d4 s12r = -tile(0, 1), s12i = zero, f = -tile(0, 2);
-  d4 y1r = vec(0), y1i = zero, y2r = vec(1), y2i = zero;
+  d4 s12r = -tile(0, 1), s12i = zero, f = half > 0 ? -tile(0, 2) : zero;
+  d4 y1 = zero, y2 = zero;
+  double v1r = 0.0, v1i = 0.0, v2r = 0.0, v2i = 0.0;
+  if (COMPLEX) {
+    v1r = one_of(up, 0);
+    v2r = one_of(up, 1);
+    if (lk > 0) {  // the unused columns of the rows' fourth tile
+#pragma unroll
+      for (int t = 0; t < 16; t += 2) *reinterpret_cast<double2 *>(row + ((t + (lk & 1)) * 64 + 48 + li) * C2) = make_double2(0.0, 0.0);
+    }
+  } else {
+    y1 = vec(0);
+    y2 = vec(1);
+  }
+  auto put_one = [&](double *buf, int c, double re, double im) {
+    if (lk == 0) *reinterpret_cast<double2 *>(buf + (li * 64 + c) * C2) = make_double2(re, im);
+  };
   double wr = 0.0, wi = 0.0;
 
 #pragma unroll 1
-  for (int p = 0; p < nb16; ++p) {
+  for (int p = 0; p < half + 2; ++p) {
+    if (p == half) {
+      // the middle blocks: both waves' remainders less the matrix, which both hold
+      if (up) {
+        put(row, 0, s22r, s22i);
+        put(row, 16, s12r, s12i);
+        put(row, 32, s11r, s11i);
+        if (COMPLEX) put_one(row, 48, v2r, v2i);
+        else put(row, 48, y2, zero);
+      }
+      __syncthreads();
+      if (up) {  // the other wave is through with its rows
+        if (COMPLEX) put_one(rows[0], 0, v1r, v1i);
+        else put(rows[0], 0, y1, zero);
+        put(rows[0], 16, d4{wr, 0.0, 0.0, 0.0}, d4{wi, 0.0, 0.0, 0.0});  // not a tile: [lk][16 + li]
+      }
+      __syncthreads();
+      if (up) return;
+      d4 o11r, o11i, o22r, o22i;
+      shifted_diag(tile_of(false, half, 0), o11r, o11i);
+      shifted_diag(tile_of(false, half + 1, 0), o22r, o22i);
+      const d4 o12 = -tile_of(false, half, 1);
+      double ar, ai;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 15 - (4 * r + lk), j = 15 - li;  // where the upward wave has it
+        get(rows[1], i * 64 + j, ar, ai);
+        s11r[r] += ar - o11r[r];
+        s11i[r] += ai - o11i[r];
+        get(rows[1], j * 64 + 16 + i, ar, ai);
+        s12r[r] += ar - o12[r];
+        s12i[r] += ai;
+        get(rows[1], i * 64 + 32 + j, ar, ai);
+        s22r[r] += ar - o22r[r];
+        s22i[r] += ai - o22i[r];
+      }
+      if (COMPLEX) {
+        get(rows[1], (15 - li) * 64 + 48, ar, ai);
+        v1r += ar - one_of(false, half);
+        v1i += ai;
+        get(rows[0], (15 - li) * 64, ar, ai);
+        v2r += ar - one_of(false, half + 1);
+        v2i += ai;
+      } else {
+        const d4 u1 = vec_of(false, half), u2 = vec_of(false, half + 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = 15 - (4 * r + lk);
+          y1[r] += rows[1][i * 64 + 48 + li] - u1[r];
+          y2[r] += rows[0][i * 64 + li] - u2[r];
+        }
+      }
+      get(rows[0], lk * 64 + 16 + li, ar, ai);
+      wr += ar;
+      wi += ai;
+      f = zero;
+      wave_sync();
+    }
     // the next step's fresh tiles
-    const d4 nd = tile(p + 2, 0), ne = tile(p + 1, 1), nf = tile(p + 1, 2), nu = vec(p + 2);
-    put(row, 64, 0, s11r, s11i);
-    put(row, 64, 16, s12r, s12i);
-    put(row, 64, 32, f, zero);
-    put(row, 64, 48, y1r, y1i);
+    d4 nd = zero, ne = zero, nf = zero, nu = zero;
+    double nv = 0.0;
+    if (p < half) {
+      nd = tile(p + 2, 0);
+      ne = tile(p + 1, 1);
+      if (p + 1 < half) nf = tile(p + 1, 2);
+      if (COMPLEX) nv = one_of(up, p + 2);
+      else nu = vec(p + 2);
+    }
+    put(row, 0, s11r, s11i);
+    put(row, 16, s12r, s12i);
+    put(row, 32, f, zero);
+    if (COMPLEX) put_one(row, 48, v1r, v1i);
+    else put(row, 48, y1, zero);
     wave_sync();
     double mr[16], mi[16];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      const double *q = row + (t * 64 + lane) * C2;
-      if (COMPLEX) {
-        const double2 v = *reinterpret_cast<const double2 *>(q);
-        mr[t] = v.x;
-        mi[t] = v.y;
-      } else {
-        mr[t] = *q;
-        mi[t] = 0.0;
-      }
-    }
+    for (int t = 0; t < 16; ++t) get(row, t * 64 + lane, mr[t], mi[t]);
     wave_sync();
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
@@ -1341,6 +1447,7 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
         const double di = bcast(mi[t], t);
         const double q = fast_rcp(fma(dr, dr, di * di));
         const double ir = dr * q, ii = -di * q;
+        if (lane == 0) dinv[t] = make_double2(ir, ii);
         lr = mr[t] * ir - mi[t] * ii;
         lm = mr[t] * ii + mi[t] * ir;
         wr += mr[t] * lr - mi[t] * lm;
@@ -1350,27 +1457,26 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
           const double a = bcast(lr, i), b = bcast(lm, i);
           mr[i] = fma(b, mi[t], fma(-a, mr[t], mr[i]));
           mi[i] = fma(-b, mr[t], fma(-a, mi[t], mi[i]));
+          asm volatile("" : "+v"(mr[i]), "+v"(mi[i]));  // now, or the broadcasts spill
         }
+        *reinterpret_cast<double2 *>(row + (t * 64 + lane) * C2) = make_double2(mr[t], mi[t]);
       } else {
-        lr = mr[t] * fast_rcp(dr);
-        lm = 0.0;
+        const double q = fast_rcp(dr);
+        if (lane == 0) dinv[t].x = q;
+        lr = mr[t] * q;
         wr += mr[t] * lr;
 #pragma unroll
-        for (int i = t + 1; i < 16; ++i) mr[i] = fma(-bcast(lr, i), mr[t], mr[i]);
-      }
-      double *q = row + (t * 64 + lane) * C2;
-      double *g = mul + (t * 32 + lane - 16) * C2;
-      if (COMPLEX) {
-        *reinterpret_cast<double2 *>(q) = make_double2(mr[t], mi[t]);
-        if (lane >= 16 && lane < 48) *reinterpret_cast<double2 *>(g) = make_double2(lr, lm);
-      } else {
-        *q = mr[t];
-        if (lane >= 16 && lane < 48) *g = lr;
+        for (int i = t + 1; i < 16; ++i) {
+          mr[i] = fma(-bcast(lr, i), mr[t], mr[i]);
+          asm volatile("" : "+v"(mr[i]));
+        }
+        row[t * 64 + lane] = mr[t];
       }
     }
     wave_sync();
     // what is left on blocks p + 1, p + 2
-    d4 n11r = s22r, n11i = s22i, n12r = -ne, n12i = zero, n22r, n22i, ny1r = y2r, ny1i = y2i, ny2r = nu, ny2i = zero;
+    d4 n11r = s22r, n11i = s22i, n12r = -ne, n12i = zero, n22r, n22i, ny1 = y2, ny2 = nu;
+    double m1r = 0.0, m1i = 0.0, m2r = 0.0, m2i = 0.0;
     shifted_diag(nd, n22r, n22i);
     auto add = [&](d4 &re, d4 &im, double ar, double ai, double br, double bi) {
       re = mfma(-ar, br, re);
@@ -1380,34 +1486,48 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
         im = mfma(-ai, br, im);
       }
     };
-    auto get = [&](const double *buf, int o, double &re, double &im) {
-      if (COMPLEX) {
-        const double2 v = *reinterpret_cast<const double2 *>(buf + o * C2);
-        re = v.x;
-        im = v.y;
-      } else {
-        re = buf[o];
-        im = 0.0;
-      }
-    };
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int t = 4 * s + lk;
       double a1r, a1i, a2r, a2i, b1r, b1i, b2r, b2i, cr, ci;
-      get(mul, t * 32 + li, a1r, a1i);
-      get(mul, t * 32 + 16 + li, a2r, a2i);
       get(row, t * 64 + 16 + li, b1r, b1i);
       get(row, t * 64 + 32 + li, b2r, b2i);
-      get(row, t * 64 + 48 + li, cr, ci);
+      get(row, t * 64 + 48 + (COMPLEX ? 0 : li), cr, ci);
+      const double2 q = dinv[t];
+      if (COMPLEX) {
+        a1r = b1r * q.x - b1i * q.y;
+        a1i = b1r * q.y + b1i * q.x;
+        a2r = b2r * q.x - b2i * q.y;
+        a2i = b2r * q.y + b2i * q.x;
+      } else {
+        a1r = b1r * q.x;
+        a2r = b2r * q.x;
+        a1i = a2i = 0.0;
+      }
       add(n11r, n11i, a1r, a1i, b1r, b1i);
       add(n12r, n12i, a1r, a1i, b2r, b2i);
       add(n22r, n22i, a2r, a2i, b2r, b2i);
-      add(ny1r, ny1i, a1r, a1i, cr, ci);
-      add(ny2r, ny2i, a2r, a2i, cr, ci);
+      if (COMPLEX) {
+        m1r = fma(a1r, cr, fma(-a1i, ci, m1r));
+        m1i = fma(a1r, ci, fma(a1i, cr, m1i));
+        m2r = fma(a2r, cr, fma(-a2i, ci, m2r));
+        m2i = fma(a2r, ci, fma(a2i, cr, m2i));
+      } else {
+        ny1 = mfma(-a1r, cr, ny1);
+        ny2 = mfma(-a2r, cr, ny2);
+      }
     }
     wave_sync();
     s11r = n11r; s11i = n11i; s12r = n12r; s12i = n12i; s22r = n22r; s22i = n22i;
-    y1r = ny1r; y1i = ny1i; y2r = ny2r; y2i = ny2i;
+    if (COMPLEX) {
+      v1r = v2r - row_sum(m1r);
+      v1i = v2i - row_sum(m1i);
+      v2r = nv - row_sum(m2r);
+      v2i = -row_sum(m2i);
+    } else {
+      y1 = ny1;
+      y2 = ny2;
+    }
     f = -nf;
   }
   if (lane >= 48 && lane - 48 < task.nrhs)
@@ -1492,8 +1612,8 @@ void launch_spectral_pack(const double *A, long long lda, int np, int R, const d
 
 void launch_spectral_w(const double *band, const double *Ut, int np, const SpectralTask *tasks, int n_tasks,
                        bool real, double2 *W_out, hipStream_t s) {
-  if (real) spectral_w_kernel<false><<<n_tasks, 64, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
-  else spectral_w_kernel<true><<<n_tasks, 64, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
+  if (real) spectral_w_kernel<false><<<n_tasks, 128, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
+  else spectral_w_kernel<true><<<n_tasks, 128, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
 }
 
 }  // namespace gwc
