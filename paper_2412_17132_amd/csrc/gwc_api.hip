@@ -814,19 +814,21 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
   const bool timing = g_timing;
   for (size_t t0 = 0; t0 < T; t0 += F) {
     const int Fb = (int)std::min<size_t>(F, T - t0);
+    // on the imaginary axis every imaginary part of 1 - Pi is zero
+    const bool real = std::all_of(tl.z.begin() + t0, tl.z.begin() + t0 + Fb, [](const double2 &z) { return z.x == 0.0; });
     launch_chi(rs.d_eps.as<double>(), rs.no, rs.nv, z_d + t0, Fb, rs.ldl, dchr.as<double>(),
                dchi.as<double>(), s);
     hipEvent_t ea = timing ? timing_mark(s) : nullptr;
     if (precision == GWC_PREC_FP64) {
       launch_pi_build_f64(rs.d_L.as<double>(), rs.ldl, N, dchr.as<double>(), dchi.as<double>(), Fb,
                           rs.d_tiles.as<int2>(), rs.n_tiles, dG.as<double2>(), (long long)mat_elems,
-                          ldg, s);
+                          ldg, real, s);
     } else {
       launch_pi_build_mixed(precision, mx->Lf.p, mx->Bh.p, mx->Bl.p, rs.ldl, N,
                             dchr.as<double>(), dchi.as<double>(),
                             precision != GWC_PREC_BF16X3 ? mx->ics.as<float>() : nullptr,
                             mx->acol.as<float>(), dts.as<float>(), dcf.as<float>(), Fb, mx->tiles.as<int2>(),
-                            mx->n_tiles, dG.as<double2>(), (long long)mat_elems, ldg, s);
+                            mx->n_tiles, dG.as<double2>(), (long long)mat_elems, ldg, real, s);
     }
     if (timing) {
       double fl = 0.0;
@@ -843,7 +845,7 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
     } else {
       HIPCHECK(launch_ldlt_bordered(dG.as<double2>(), (long long)mat_elems, ldg, N, R, Fb,
                                     dbb.as<double>(), ob_d + t0, os_d + t0, W_out, dst.as<int>() + t0,
-                                    dscr.p, s));
+                                    dscr.p, real, s));
     }
     if (timing) {
       // algorithmic flops: LU (8/3) N^3 + 8 N^2 R; LDL^T half the elimination

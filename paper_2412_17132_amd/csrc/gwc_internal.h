@@ -34,7 +34,7 @@ void launch_chi(const double *eps, int n_occ, int n_virt, const double2 *z, int 
                 double *chi_re, double *chi_im, hipStream_t stream);
 void launch_pi_build_f64(const double *Lp, int ldl, int n_aux, const double *chi_re,
                          const double *chi_im, int F, const int2 *tiles, int n_tiles,
-                         double2 *G, long long g_stride, int ldg, hipStream_t stream);
+                         double2 *G, long long g_stride, int ldg, bool real, hipStream_t stream);
 // Mixed-precision Pi build.  Tiles are mixed_tile_rows(prec) x MX_TILE_COLS
 // blocks (128 x 256); the split operands have their rows padded to a multiple
 // of MX_TILE_COLS and their columns to mixed_ldl(prec, ldl) (the form's K
@@ -56,7 +56,7 @@ void launch_pi_build_mixed(int prec, const void *Lf, const void *Bhi, const void
                            int n_aux, const double *chi_re, const double *chi_im,
                            const float *inv_colscale, const float *acol, float *tscale, float *chi_f32,
                            int F, const int2 *tiles, int n_tiles, double2 *G, long long g_stride,
-                           int ldg, hipStream_t stream);
+                           int ldg, bool real, hipStream_t stream);
 void launch_border(const double *M_oo, const double *M_ov, int n_aux, int n_occ, int n_virt,
                    const int *task_n, const int *task_m, int F, int R, double2 *G,
                    long long g_stride, int ldg, double *bb, hipStream_t stream);
@@ -76,7 +76,7 @@ hipError_t launch_lu_bordered(double2 *G, long long g_stride, int ldg, int N, in
 // diagonal of the square range from r0 = c0 to n), the border's W from the
 // Schur complement, and clearing the per-matrix status flags.
 void launch_trailing_update_sym(double2 *G, long long gs, int ldg, int N, int R, int F, int r0,
-                                int c0, int c1, int kstart, int klen, bool lower,
+                                int c0, int c1, int kstart, int klen, bool lower, bool real,
                                 const double2 *dinv, int dinv_ld, hipStream_t s);
 void launch_bordered_finish(const double2 *G, long long gs, int ldg, int N, int R, int F,
                             const double *bb, const long long *out_base, const int *out_stride,
@@ -89,7 +89,7 @@ void launch_zero_status(int *status, int F, hipStream_t s);
 size_t ldlt_scratch_bytes(int F, int N);
 hipError_t launch_ldlt_bordered(double2 *G, long long g_stride, int ldg, int N, int R, int F,
                                 const double *bb, const long long *out_base, const int *out_stride,
-                                double2 *W_out, int *status, void *scratch, hipStream_t stream);
+                                double2 *W_out, int *status, void *scratch, bool real, hipStream_t stream);
 void launch_sigma_x(const double *M_oo, int n_aux, int n_occ, const int *core_idx, int n_core,
                     double *sigma_x, hipStream_t stream);
 void launch_quadrature(const double2 *W_imag, const double *eps, int n_basis,

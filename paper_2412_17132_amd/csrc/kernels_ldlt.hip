@@ -300,6 +300,7 @@ struct LdltLaunch {
   int ldg, N, R, F, fgroups;
   double2 *linv, *dinv;
   int *status;
+  bool real;
   hipStream_t s;
 
   void diag_trsm(int K0) const {
@@ -312,7 +313,7 @@ struct LdltLaunch {
   }
   // rows [r0, n) x columns [c0, c1) -= L[.., K range] W^T[K range, ..]
   void trailing(int r0, int c0, int c1, int kstart, int klen, bool lower) const {
-    launch_trailing_update_sym(G, gs, ldg, N, R, F, r0, c0, c1, kstart, klen, lower, dinv, N, s);
+    launch_trailing_update_sym(G, gs, ldg, N, R, F, r0, c0, c1, kstart, klen, lower, real, dinv, N, s);
   }
 };
 
@@ -325,12 +326,12 @@ size_t ldlt_scratch_bytes(int F, int N) {
 
 hipError_t launch_ldlt_bordered(double2 *G, long long g_stride, int ldg, int N, int R, int F,
                                 const double *bb, const long long *out_base, const int *out_stride,
-                                double2 *W_out, int *status, void *scratch, hipStream_t stream) {
+                                double2 *W_out, int *status, void *scratch, bool real, hipStream_t stream) {
   const int n = N + R;
   double2 *linv = static_cast<double2 *>(scratch);
   double2 *dinv = linv + (size_t)F * NB * NB;
   launch_zero_status(status, F, stream);
-  const LdltLaunch L{G, g_stride, ldg, N, R, F, (F + NXCD - 1) / NXCD, linv, dinv, status, stream};
+  const LdltLaunch L{G, g_stride, ldg, N, R, F, (F + NXCD - 1) / NXCD, linv, dinv, status, real, stream};
   int K0 = 0;
   while (K0 < N) {
     const int g = min(LDLT_GROUP, (N - K0) / NB);

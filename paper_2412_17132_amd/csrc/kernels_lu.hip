@@ -541,7 +541,9 @@ lu_swap_u12_kernel(double2 *__restrict__ G, long long gs, int ldg, int N, int K0
 // SYM: the left operand comes from the row part as well, A[r][k] = A[k][r] d_k
 // with d_k = dinv[f dinv_ld + k] (the symmetric factorisation keeps only
 // W^T = D L^T in the rows of its panels: L[r][k] = W^T[k][r] / D[k]).
-template <bool LOWER, bool SYM>
+// REAL: every imaginary part is zero and stays (the imaginary axis): one product
+// instead of three (order 2100 + 520, 32 matrices: 8.4 -> 5.6 ms).
+template <bool LOWER, bool SYM, bool REAL>
 __global__ void __launch_bounds__(256, 3)
 lu_trailing_kernel(double2 *__restrict__ G, long long gs, int ldg, int N, int R, int F, int row0,
                    int col0, int col_end, int mt_r, int mt_c, int kstart, int klen,
@@ -590,6 +592,7 @@ lu_trailing_kernel(double2 *__restrict__ G, long long gs, int ldg, int N, int R,
       for (int b = 0; b < 2; ++b) {
         const double us = uv[b].x + uv[b].y;
         p1[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(lv[a].x, uv[b].x, p1[a][b], 0, 0, 0);
+        if (REAL) continue;
         p2[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(lv[a].y, uv[b].y, p2[a][b], 0, 0, 0);
         p3[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ls, us, p3[a][b], 0, 0, 0);
       }
@@ -613,7 +616,10 @@ lu_trailing_kernel(double2 *__restrict__ G, long long gs, int ldg, int N, int R,
     if (SYM) {
       const double2 d = dk[kk];
 #pragma unroll
-      for (int a = 0; a < 2; ++a) lv[a] = cmul(lrow[a][(kk >> 2) * ustep], d);
+      for (int a = 0; a < 2; ++a) {
+        const double2 l = lrow[a][(kk >> 2) * ustep];
+        lv[a] = REAL ? make_double2(l.x * d.x, 0.0) : cmul(l, d);
+      }
     } else {
 #pragma unroll
       for (int a = 0; a < 2; ++a) lv[a] = lrow[a][kk];
@@ -681,7 +687,8 @@ lu_trailing_kernel(double2 *__restrict__ G, long long gs, int ldg, int N, int R,
         const double q1 = p1[a][b][r], q2 = p2[a][b][r];
         if (row < n && col < col_end)
           A[(long long)row * ldg + col] =
-              make_double2(x[b][r].x - (q1 - q2), x[b][r].y - (p3[a][b][r] - q1 - q2));
+              REAL ? make_double2(x[b][r].x - q1, x[b][r].y)
+                   : make_double2(x[b][r].x - (q1 - q2), x[b][r].y - (p3[a][b][r] - q1 - q2));
       }
     }
   }
@@ -757,7 +764,7 @@ struct LuLaunch {
     const int n = N + R;
     const int mt_r = (n - r0 + 63) / 64, mt_c = (c1 - c0 + 63) / 64;
     if (mt_r < 1 || mt_c < 1) return;
-    lu_trailing_kernel<false, false><<<NXCD * fgroups * mt_r * mt_c, 256, 0, s>>>(
+    lu_trailing_kernel<false, false, false><<<NXCD * fgroups * mt_r * mt_c, 256, 0, s>>>(
         G, gs, ldg, N, R, F, r0, c0, c1, mt_r, mt_c, kstart, klen, nullptr, 0);
   }
 };
@@ -807,18 +814,17 @@ hipError_t launch_lu_bordered(double2 *G, long long g_stride, int ldg, int N, in
 }
 
 void launch_trailing_update_sym(double2 *G, long long gs, int ldg, int N, int R, int F, int r0,
-                                int c0, int c1, int kstart, int klen, bool lower,
+                                int c0, int c1, int kstart, int klen, bool lower, bool real,
                                 const double2 *dinv, int dinv_ld, hipStream_t s) {
   const int n = N + R;
   const int mt_r = (n - r0 + 63) / 64, mt_c = (c1 - c0 + 63) / 64;
   if (mt_r < 1 || mt_c < 1) return;
   const int fgroups = (F + NXCD - 1) / NXCD;
-  if (lower)
-    lu_trailing_kernel<true, true><<<NXCD * fgroups * (mt_r * (mt_r + 1) / 2), 256, 0, s>>>(
-        G, gs, ldg, N, R, F, r0, c0, c1, mt_r, mt_r, kstart, klen, dinv, dinv_ld);
-  else
-    lu_trailing_kernel<false, true><<<NXCD * fgroups * mt_r * mt_c, 256, 0, s>>>(
-        G, gs, ldg, N, R, F, r0, c0, c1, mt_r, mt_c, kstart, klen, dinv, dinv_ld);
+  auto *kernel = lower ? (real ? lu_trailing_kernel<true, true, true> : lu_trailing_kernel<true, true, false>)
+                       : (real ? lu_trailing_kernel<false, true, true> : lu_trailing_kernel<false, true, false>);
+  const int cols = lower ? mt_r : mt_c;
+  kernel<<<NXCD * fgroups * (lower ? mt_r * (mt_r + 1) / 2 : mt_r * mt_c), 256, 0, s>>>(
+      G, gs, ldg, N, R, F, r0, c0, c1, mt_r, cols, kstart, klen, dinv, dinv_ld);
 }
 
 void launch_bordered_finish(const double2 *G, long long gs, int ldg, int N, int R, int F,

@@ -98,10 +98,12 @@ __device__ __forceinline__ bool pi_item(int wg, int n_tiles, int P, int group, i
 // pi_item.  Wave w of the workgroup owns
 // rows 32*(w/2) .. +32 and columns 32*(w%2) .. +32 of the 64 x 64 tile, i.e. a
 // 2 x 2 block of 16 x 16 MFMA outputs, for PI_FB frequencies, real and
-// imaginary parts: 16 accumulators of 4 doubles per lane.
+// imaginary parts: 16 accumulators of 4 doubles per lane.  REAL (the imaginary
+// axis, chi_im = 0): the imaginary parts are zero without being formed.
 //
 // MFMA operand layout (v_mfma_f64_16x16x4f64): lane l supplies A[l%16][l/16]
 // and B[l/16][l%16]; output element r of lane l is D[4r + l/16][l%16].
+template <bool REAL>
 __global__ void __launch_bounds__(PI_THREADS, 2)
 pi_build_f64_kernel(const double *__restrict__ Lp, int ldl, int n_aux,
                     const double *__restrict__ chi_re, const double *__restrict__ chi_im, int F,
@@ -183,6 +185,7 @@ pi_build_f64_kernel(const double *__restrict__ Lp, int ldl, int n_aux,
         acc[f][0][0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar0, b1, acc[f][0][0][1], 0, 0, 0);
         acc[f][0][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar1, b0, acc[f][0][1][0], 0, 0, 0);
         acc[f][0][1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar1, b1, acc[f][0][1][1], 0, 0, 0);
+        if (REAL) continue;
         acc[f][1][0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai0, b0, acc[f][1][0][0], 0, 0, 0);
         acc[f][1][0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai0, b1, acc[f][1][0][1], 0, 0, 0);
         acc[f][1][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai1, b0, acc[f][1][1][0], 0, 0, 0);
@@ -221,14 +224,15 @@ pi_build_f64_kernel(const double *__restrict__ Lp, int ldl, int n_aux,
 
 void launch_pi_build_f64(const double *Lp, int ldl, int n_aux, const double *chi_re,
                          const double *chi_im, int F, const int2 *tiles, int n_tiles,
-                         double2 *G, long long g_stride, int ldg, hipStream_t stream) {
+                         double2 *G, long long g_stride, int ldg, bool real, hipStream_t stream) {
   // (tile, pair-group) blocks, rounded up to a whole turn of the XCDs
   const int P = (F + PI_FB - 1) / PI_FB;
   const int group = P < 64 ? P : 64;
   const long long blocks = (long long)n_tiles * ((P + group - 1) / group);
   const long long wgs = (blocks + PI_NXCD - 1) / PI_NXCD * PI_NXCD * group;
-  pi_build_f64_kernel<<<(unsigned)wgs, PI_THREADS, 0, stream>>>(Lp, ldl, n_aux, chi_re, chi_im, F, tiles,
-                                                                n_tiles, group, G, g_stride, ldg);
+  auto *kernel = real ? pi_build_f64_kernel<true> : pi_build_f64_kernel<false>;
+  kernel<<<(unsigned)wgs, PI_THREADS, 0, stream>>>(Lp, ldl, n_aux, chi_re, chi_im, F, tiles, n_tiles, group, G,
+                                                   g_stride, ldg);
 }
 
 }  // namespace gwc

@@ -421,7 +421,7 @@ constexpr int MX_BGROUP = 4;
 // (wave-uniform bounds: blocks wholly below the diagonal or past n_aux produce
 // nothing that is stored, and the two waves of a SIMD share its MFMA pipe, so
 // skipping them shortens the tiles that cross the diagonal).
-template <class T>
+template <class T, bool REAL>
 __device__ __forceinline__ void mix_multiply(const MixAReg<T> &lv, const typename Mix<T>::E *Bh,
                                              const typename Mix<T>::E *Bl, const float *C, int lane,
                                              int lq, int b0, int b1, f4 (&accr)[16], f4 (&acci)[16],
@@ -440,7 +440,7 @@ __device__ __forceinline__ void mix_multiply(const MixAReg<T> &lv, const typenam
     // it would then wait for that fetch); the chunk's chi is [K step][Re, Im][32]
     const f8v cr = ld8(C + 64 * st + 8 * lq), ci = ld8(C + 64 * st + 32 + 8 * lq);
     split8<T>(lv.v[st] * cr, arh[st], arl[st]);
-    split8<T>(lv.v[st] * ci, aih[st], ail[st]);
+    if constexpr (!REAL) split8<T>(lv.v[st] * ci, aih[st], ail[st]);
   }
   const E *bh_p = Bh + EPL * lane;
   const E *bl_p = Bl + EPL * lane;
@@ -464,19 +464,19 @@ __device__ __forceinline__ void mix_multiply(const MixAReg<T> &lv, const typenam
         for (int j = 0; j < NG; ++j) {
           const V h = mix_bstep<T>(bh[j], st);
           accr[NG * g + j] = Mix<T>::mfma(arh[st], h, accr[NG * g + j]);
-          acci[NG * g + j] = Mix<T>::mfma(aih[st], h, acci[NG * g + j]);
+          if constexpr (!REAL) acci[NG * g + j] = Mix<T>::mfma(aih[st], h, acci[NG * g + j]);
         }
 #pragma unroll
         for (int j = 0; j < NG; ++j) {
           const V h = mix_bstep<T>(bh[j], st);
           accr[NG * g + j] = Mix<T>::mfma(arl[st], h, accr[NG * g + j]);
-          acci[NG * g + j] = Mix<T>::mfma(ail[st], h, acci[NG * g + j]);
+          if constexpr (!REAL) acci[NG * g + j] = Mix<T>::mfma(ail[st], h, acci[NG * g + j]);
         }
 #pragma unroll
         for (int j = 0; j < NG; ++j) {
           const V l = mix_bstep<T>(bl[j], st);
           accr[NG * g + j] = Mix<T>::mfma(arh[st], l, accr[NG * g + j]);
-          acci[NG * g + j] = Mix<T>::mfma(aih[st], l, acci[NG * g + j]);
+          if constexpr (!REAL) acci[NG * g + j] = Mix<T>::mfma(aih[st], l, acci[NG * g + j]);
         }
       }
     }
@@ -508,6 +508,7 @@ __device__ __forceinline__ f4 mix_mfma128(const i8v &a, const i8v &b, f4 c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
 
+template <bool REAL>
 __device__ __forceinline__ void mix_multiply_pair(
     const MixAReg<e4m3> &la, const MixAReg<e4m3> &lb, const unsigned char *Bh_a,
     const unsigned char *Bl_a, const float *C_a, const unsigned char *Bh_b, const unsigned char *Bl_b,
@@ -518,14 +519,14 @@ __device__ __forceinline__ void mix_multiply_pair(
   constexpr int KC = MixK<e4m3>::KC;
   fetch.part0(an_a, Cn_a, kc_next);
   fetch.part0(an_b, Cn_b, kc_next + KC);
-  uc8 rh[4], rl[4], ih[4], il[4];  // [chunk a step 0, a 1, b 0, b 1]
+  uc8 rh[4], rl[4], ih[4] = {}, il[4] = {};  // [chunk a step 0, a 1, b 0, b 1]
 #pragma unroll
   for (int st = 0; st < 2; ++st) {
     const f8v xa = __builtin_convertvector(la.v[st], f8v), xb = __builtin_convertvector(lb.v[st], f8v);
     split8<e4m3>(xa * ld8(C_a + 64 * st + 8 * lq), rh[st], rl[st]);
-    split8<e4m3>(xa * ld8(C_a + 64 * st + 32 + 8 * lq), ih[st], il[st]);
+    if constexpr (!REAL) split8<e4m3>(xa * ld8(C_a + 64 * st + 32 + 8 * lq), ih[st], il[st]);
     split8<e4m3>(xb * ld8(C_b + 64 * st + 8 * lq), rh[2 + st], rl[2 + st]);
-    split8<e4m3>(xb * ld8(C_b + 64 * st + 32 + 8 * lq), ih[2 + st], il[2 + st]);
+    if constexpr (!REAL) split8<e4m3>(xb * ld8(C_b + 64 * st + 32 + 8 * lq), ih[2 + st], il[2 + st]);
   }
   const i8v AH = mix_cat(rh[0], rh[1], rh[2], rh[3]), AL = mix_cat(rl[0], rl[1], rl[2], rl[3]);
   const i8v IH = mix_cat(ih[0], ih[1], ih[2], ih[3]), IL = mix_cat(il[0], il[1], il[2], il[3]);
@@ -547,17 +548,17 @@ __device__ __forceinline__ void mix_multiply_pair(
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         accr[2 * g + j] = mix_mfma128(AH, bh[j], accr[2 * g + j]);
-        acci[2 * g + j] = mix_mfma128(IH, bh[j], acci[2 * g + j]);
+        if constexpr (!REAL) acci[2 * g + j] = mix_mfma128(IH, bh[j], acci[2 * g + j]);
       }
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         accr[2 * g + j] = mix_mfma128(AL, bh[j], accr[2 * g + j]);
-        acci[2 * g + j] = mix_mfma128(IL, bh[j], acci[2 * g + j]);
+        if constexpr (!REAL) acci[2 * g + j] = mix_mfma128(IL, bh[j], acci[2 * g + j]);
       }
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         accr[2 * g + j] = mix_mfma128(AH, bl[j], accr[2 * g + j]);
-        acci[2 * g + j] = mix_mfma128(IH, bl[j], acci[2 * g + j]);
+        if constexpr (!REAL) acci[2 * g + j] = mix_mfma128(IH, bl[j], acci[2 * g + j]);
       }
     }
   }
@@ -580,7 +581,9 @@ __device__ __forceinline__ bool mx_item(int wg, int n_tiles, int F, int group, i
   return g * group < F && f < F;
 }
 
-template <class T>
+// REAL (the imaginary axis, chi_im = 0): the imaginary parts are zero without
+// being formed (FP8, order 2100, 32 frequencies: 7.2 -> 4.7 ms).
+template <class T, bool REAL>
 __global__ void __launch_bounds__(512, 1)
 pi_build_mixed_async_kernel(const typename MixA<T>::E *__restrict__ Lf,
                             const typename Mix<T>::E *__restrict__ Bhi,
@@ -662,11 +665,11 @@ pi_build_mixed_async_kernel(const typename MixA<T>::E *__restrict__ Lf,
   // of its own): the fetches past the last chunk read the rows' next bytes or
   // zeros into stages that are not multiplied.
 #define MX_MUL(S, R, N, RN, kn, bend) \
-  mix_multiply<T>(R, S.Bh, S.Bl, S.C, lane, lq, b0, bend, accr, acci, fetch, RN, N.Bh, N.Bl, N.C, kn)
+  mix_multiply<T, REAL>(R, S.Bh, S.Bl, S.C, lane, lq, b0, bend, accr, acci, fetch, RN, N.Bh, N.Bl, N.C, kn)
   fetch.all(R0, S0.Bh, S0.Bl, S0.C, 0);
   fetch.all(R1, S1.Bh, S1.Bl, S1.C, KC);
 #define MX_MUL2(SA, SB, RA, RB, NA, NB, RNA, RNB, kn, bend)                                     \
-  mix_multiply_pair(RA, RB, SA.Bh, SA.Bl, SA.C, SB.Bh, SB.Bl, SB.C, lane, lq, b0, bend, accr, acci, \
+  mix_multiply_pair<REAL>(RA, RB, SA.Bh, SA.Bl, SA.C, SB.Bh, SB.Bl, SB.C, lane, lq, b0, bend, accr, acci, \
                     fetch, RNA, RNB, NA.Bh, NA.Bl, NA.C, NB.Bh, NB.Bl, NB.C, kn)
   for (int c = 0; c < nch; c += 4) {
     // a step past the last chunk multiplies nothing (no column block below
@@ -739,7 +742,7 @@ void launch_pi_build_mixed(int prec, const void *Lf, const void *Bhi, const void
                            int n_aux, const double *chi_re, const double *chi_im,
                            const float *inv_colscale, const float *acol, float *tscale, float *chi_f32,
                            int F, const int2 *tiles, int n_tiles, double2 *G, long long g_stride,
-                           int ldg, hipStream_t stream) {
+                           int ldg, bool real, hipStream_t stream) {
   // FP16 and FP8 scale each frequency's A operand by a power of two (undone on
   // the result) and fold the column scales into chi; BF16 needs neither
   const bool scaled = prec == 2 || prec == 3;
@@ -754,18 +757,22 @@ void launch_pi_build_mixed(int prec, const void *Lf, const void *Bhi, const void
   const int group = F < 32 ? F : 32;
   const long long blocks = (long long)n_tiles * ((F + group - 1) / group);
   const long long wgs = (blocks + MX_NXCD - 1) / MX_NXCD * MX_NXCD * group;
+  auto launch = [&](auto kernel, auto *a, auto *b_hi, decltype(b_hi) b_lo, const float *ts) {
+    kernel<<<(unsigned)wgs, 512, 0, stream>>>(a, b_hi, b_lo, ldl, n_aux, chi_f32, ts, tiles, n_tiles, F, group, G,
+                                              g_stride, ldg);
+  };
+  const auto *hi16 = static_cast<const unsigned short *>(Bhi), *lo16 = static_cast<const unsigned short *>(Blo);
+  const auto *hi8 = static_cast<const unsigned char *>(Bhi), *lo8 = static_cast<const unsigned char *>(Blo);
+  const float *a32 = static_cast<const float *>(Lf);
   if (prec == 3)
-    pi_build_mixed_async_kernel<e4m3><<<(unsigned)wgs, 512, 0, stream>>>(
-        static_cast<const _Float16 *>(Lf), static_cast<const unsigned char *>(Bhi), static_cast<const unsigned char *>(Blo), ldl,
-        n_aux, chi_f32, tscale, tiles, n_tiles, F, group, G, g_stride, ldg);
+    launch(real ? pi_build_mixed_async_kernel<e4m3, true> : pi_build_mixed_async_kernel<e4m3, false>,
+           static_cast<const _Float16 *>(Lf), hi8, lo8, tscale);
   else if (prec == 2)
-    pi_build_mixed_async_kernel<_Float16><<<(unsigned)wgs, 512, 0, stream>>>(
-        static_cast<const float *>(Lf), static_cast<const unsigned short *>(Bhi), static_cast<const unsigned short *>(Blo), ldl,
-        n_aux, chi_f32, tscale, tiles, n_tiles, F, group, G, g_stride, ldg);
+    launch(real ? pi_build_mixed_async_kernel<_Float16, true> : pi_build_mixed_async_kernel<_Float16, false>, a32,
+           hi16, lo16, tscale);
   else
-    pi_build_mixed_async_kernel<__bf16><<<(unsigned)wgs, 512, 0, stream>>>(
-        static_cast<const float *>(Lf), static_cast<const unsigned short *>(Bhi), static_cast<const unsigned short *>(Blo), ldl,
-        n_aux, chi_f32, nullptr, tiles, n_tiles, F, group, G, g_stride, ldg);
+    launch(real ? pi_build_mixed_async_kernel<__bf16, true> : pi_build_mixed_async_kernel<__bf16, false>, a32, hi16,
+           lo16, nullptr);
 }
 
 }  // namespace gwc
