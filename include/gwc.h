@@ -140,7 +140,9 @@ typedef struct {
  *   vxc        [n_core] or NULL  <n|v_xc|n>, NULL means 0
  *   mode       enum gwc_mode
  *   precision  enum gwc_precision: the Pi builds (both axes) in that form; chi(z),
- *              the LU of 1 - Pi, the residue sums and E_QP stay FP64
+ *              the factorisation of 1 - Pi, the residue sums and E_QP stay FP64.
+ *              FP64 without wac takes W from one reduction of the RPA matrix of
+ *              the transitions instead where that is cheaper (same W to rounding)
  *   sym_group  [n_basis] or NULL  labels of symmetry-equivalent core levels
  *              (Eq. sigma_spectral_decoupled_symmetric): the equivalent set of a
  *              core state n is every orbital carrying n's label when that label
@@ -459,7 +461,8 @@ int gwc_server_destroy(gwc_server_handle server);
  * gwc_timing_enable(1) clears the counters and, until gwc_timing_enable(0),
  * brackets every launch of the named hot kernels with HIP events recorded on
  * the stream the kernel runs on.  gwc_timing_get returns, for one kernel name
- * ("pi_build_f64", "pi_build_mixed" or "lu_bordered"), the summed event time in ms, the number
+ * ("pi_build_f64", "pi_build_mixed", "ldlt_bordered", "lu_bordered",
+ * "spectral_reduce", "spectral_w", "jacobi_pairs" or "jacobi_apply"), the summed event time in ms, the number
  * of launches and the algorithmic flop count of those launches (Pi build, in
  * either precision: 2 N_aux (N_aux + 1) N_ov per complex residue frequency,
  * half that on the imaginary axis; LU: (8/3) N^3 + 8 N^2 R per bordered N x N matrix with R

@@ -934,9 +934,9 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   }
   if (std::numeric_limits<double>::epsilon() * max_d * max_d > 1e-10 * 2.0 * min_d * args->eta) return false;
   // The times of the two routes for ONE core state, so that a call for several
-  // cores and one for each take the same route.  Reduction: 75 us of dependent
-  // steps a panel and n^3 at 0.04 ps (measured 2.4 ms at n_ov = 1026, 20 ms at
-  // 5859, 212 ms at 16524).  Pi builds: 120 us of dependent factorisation steps
+  // cores and one for each take the same route.  Reduction: 68 us of dependent
+  // steps a panel and n^3 at 0.037 ps (measured 2.2 ms at n_ov = 1026, 19 ms at
+  // 5859, 203 ms at 16524).  Pi builds: 120 us of dependent factorisation steps
   // per 64 rows of N and 2 N^2 n + 4/3 N^3 flops a frequency at 58 TFLOP/s, less
   // on small matrices (measured 0.5 ms at N = 160, n_ov = 175 with 629
   // frequencies and 1.0 ms at 400, 651 with 40; 0.28 ms a frequency at 1200, 5859).
@@ -946,7 +946,7 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   const bool every = args->mode == GWC_MODE_FULL || rs.n_ov <= 320;
   const double tasks = args->n_imag + (double)args->n_real * (every ? rs.no : 1) + rs.no;
   const double panels = std::ceil(n / SPECTRAL_BAND) - 1;
-  const double t_reduce = 75e-6 * panels + 4.0e-14 * n * n * n;
+  const double t_reduce = 68e-6 * panels + 3.7e-14 * n * n * n;
   const double t_build = 120e-6 * std::ceil(N / 64) +
                          tasks * (2.0 * N * N * n + 4.0 / 3.0 * N * N * N) / (58e12 * N / (N + 150.0));
   return t_reduce < t_build;
