@@ -68,9 +68,9 @@ constexpr int XTHREADS = 1024;
 constexpr int UT = 64;        // tile of the rank update and the transition matrix
 constexpr int ULD = SB + 2;   // LDS row stride of its operands (no bank conflicts)
 // Rows from which panels go in pairs: the second panel's own products cost about
-// 60 us, half a pass over the matrix more than that from here on (whole reduction
-// at order 16524 in pairs down to 7168 rows: 295 -> 258 ms; at 5859 in pairs
-// throughout: 36 -> 38 ms).
+// 40 us, half a pass over the matrix more than that from here on (a call of order
+// 16524 in pairs down to 10240, 7168 and 3072 rows: 210.5, 208.1 and 209.0 ms;
+// one of 5859 without pairs 22.5 ms, with pairs down to 3072 rows 23.5).
 constexpr int PAIR_ROWS = 7168;
 constexpr int Q_PART = 768, Q_PART2 = 768 + 2 * SB * SB;  // partial sums of panel_q
 
@@ -1268,9 +1268,10 @@ spectral_transpose_kernel(const double *__restrict__ A, long long lda, int np, i
 // two blocks and their vectors is a product of the eliminated rows, on MFMA
 // (accumulators initialised with the band itself); the layouts change through
 // the wave's LDS.  COMPLEX = false is the imaginary axis (z^2 = -w^2, real).
-// Bound by the steps' chains where there are fewer tasks than fill the chip
-// (order 5859, 1029 complex tasks: 5.1 -> 2.6 ms against one wave a task and sixteen columns), by
-// instructions beyond that.
+// Bound by the steps' chains where there are fewer tasks than fill the chip, by
+// instructions beyond that (order 5859, 1029 complex tasks: 5.1 -> 2.6 ms against
+// one wave a task that updated sixteen columns of vectors; 608 real tasks 1.15 ->
+// 0.83).
 template <bool COMPLEX>
 __global__ void __launch_bounds__(128, COMPLEX ? 2 : 3)
 spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut, int np, int nb16,
@@ -1574,7 +1575,7 @@ void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, c
     const int off = k == 0 ? pad : 0, bw = SB - off;  // the first block's zero columns are no panel
     if (k & 1) second = pair;
     else second = false;
-    // a pair saves a pass over A22 and costs about 60 us of products of its own
+    // a pair saves a pass over A22 and costs products of its own
     pair = !(k & 1) && k + 1 < panels && m >= PAIR_ROWS;
     const double *P = A + (long long)(c0 + off) * lda + r0;  // transposed
     double *A22 = A + (long long)r0 * lda + r0;
