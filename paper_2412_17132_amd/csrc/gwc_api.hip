@@ -30,6 +30,7 @@
 #include "gwc.h"
 #include "gwc_host.h"
 #include "gwc_internal.h"
+#include "gwc_pointers.h"
 
 namespace gwc {
 
@@ -348,6 +349,21 @@ bool is_device_ptr(const void *ptr) {
   return a.type == hipMemoryTypeDevice || a.isManaged;
 }
 
+// A caller's array that the call's kernels use where it is (all others are copied).
+bool usable_in_place(const void *ptr) {
+  hipPointerAttribute_t a;
+  int current = -1;
+  if (hipPointerGetAttributes(&a, ptr) != hipSuccess || hipGetDevice(&current) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  gwc::PointerKind k;
+  k.device = a.type == hipMemoryTypeDevice;
+  k.managed = a.isManaged != 0;
+  k.owner = a.device;
+  return gwc::kernels_may_use(k, current);
+}
+
 // Copy `count` elements of a host-or-device array into a host vector.
 template <class T>
 std::vector<T> to_host(const T *p, size_t count, hipStream_t s) {
@@ -364,7 +380,7 @@ std::vector<T> to_host(const T *p, size_t count, hipStream_t s) {
 
 // Small arrays of a call brought to the host together: device arrays are
 // gathered into one block and copied with one synchronisation (each by itself
-// cost 15 us), host arrays are copied at once.
+// cost 15 us), all others are copied at once.
 struct GatherArgs {
   static constexpr int MAX = 12;
   const int *src[MAX];
@@ -384,8 +400,8 @@ class HostFetch {
   void add(std::vector<T> &dst, const T *src, size_t count) {
     dst.resize(count);
     if (count == 0) return;
-    if (!is_device_ptr(src)) {
-      std::copy(src, src + count, dst.begin());
+    if (!usable_in_place(src)) {
+      dst = to_host(src, count, s_);
       return;
     }
     if (g_.count == GatherArgs::MAX) run();
@@ -441,7 +457,7 @@ struct Staged {
   }
 };
 
-// An output of a call: the caller's own array where that is on the device, else
+// An output of a call: the caller's own array where kernels may write it, else
 // a temporary copied there.
 struct OutBuf {
   DevBuf tmp;
@@ -451,7 +467,7 @@ struct OutBuf {
   double *open(double *out, size_t count) {
     user = out;
     bytes = count * sizeof(double);
-    if (out && is_device_ptr(out)) {
+    if (out && usable_in_place(out)) {
       dev = out;
     } else {
       tmp.alloc(bytes);
@@ -643,7 +659,7 @@ static ResidentSystem *make_system(const gwc_system *sys, hipStream_t s, bool on
 
   const size_t n_oo = (size_t)N * no * no, n_ovt = (size_t)N * no * nv;
   auto stage = [&](PersistBuf &buf, const double *src, size_t count) -> const double * {
-    if (in_place && is_device_ptr(src)) return src;
+    if (in_place && usable_in_place(src)) return src;
     buf.alloc(count * sizeof(double));
     HIPCHECK(hipMemcpyAsync(buf.p, src, count * sizeof(double), hipMemcpyDefault, s));
     return buf.as<double>();
@@ -1585,8 +1601,8 @@ void run_cumulant(const gwc_cumulant_args *a, double *A_out, double *z_out, hipS
 
   DevBuf dw(s), dim(s), dnuc(s), dA(s), dB(s);
   OutBuf oA(s), oz(s);
-  const double *d_w = is_device_ptr(a->omega_real) ? a->omega_real : upload(dw, w, s);
-  const double *d_im = is_device_ptr(a->im_sigma) ? a->im_sigma : upload(dim, im, s);
+  const double *d_w = usable_in_place(a->omega_real) ? a->omega_real : upload(dw, w, s);
+  const double *d_im = usable_in_place(a->im_sigma) ? a->im_sigma : upload(dim, im, s);
   dnuc.alloc(2 * (size_t)a->n_real * sizeof(double));
   double *dnu = dnuc.as<double>(), *dc = dnu + a->n_real;
   dA.alloc((size_t)nt * sizeof(double2));
