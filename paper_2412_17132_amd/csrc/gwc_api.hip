@@ -1373,7 +1373,7 @@ void run_qp_newton(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_
     deq.alloc((size_t)na * sizeof(double));
     launch_assemble(dWr.as<double2>(), d_f, d_td, d_cjo, dI.as<double>(), na, 3, rs.d_eps.as<double>(),
                     d_core, d_sx, d_vxc, 1, dsig.as<double>(), dimd.as<double>(), dse.as<double>(),
-                    deq.as<double>(), s);
+                    deq.as<double>(), nullptr, s);
     HIPCHECK(hipGetLastError());
     std::vector<double> sig((size_t)na * 6);
     HIPCHECK(hipMemcpyAsync(sig.data(), dsig.p, sig.size() * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1495,15 +1495,16 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
   double *dse = ose.open(out->sigma_c_eps, (size_t)nc * 2);
   double *dsx = osx.open(out->sigma_x, nc);
   double *deq = oeq.open(out->e_qp, nc);
-  launch_sigma_x(rs.Moo, N, rs.no, d_core, nc, dsx, s);
+  // coefficients not checked yet: the outputs keep what they hold if they are bad
+  const int *refused = rs.unchecked ? rs.flag.as<int>() : nullptr;
+  launch_sigma_x(rs.Moo, N, rs.no, d_core, nc, dsx, refused, s);
   dI.alloc((size_t)nc * npts * sizeof(double));
   launch_quadrature(dWi.as<double2>(), rs.d_eps.as<double>(), nb, d_wi, d_wwi, ni, d_wr, nr, d_core,
                     nc, full ? npts : 1, dI.as<double>(), s);
   launch_assemble(dWr.as<double2>(), lists.at<double>(o_f), lists.at<int>(o_dec), lists.at<int>(o_cjo),
                   dI.as<double>(), nc, nr, rs.d_eps.as<double>(), d_core, dsx, d_vxc, full ? 1 : 0, dsig, dimd, dse,
-                  deq, s);
+                  deq, refused, s);
   HIPCHECK(hipGetLastError());
-  for (OutBuf *o : {&osig, &oimd, &ose, &osx, &oeq}) o->close(s);
   int unusable = 0;
   if (sp) {
     launch_nonfinite(dWi.as<double>(), (long long)nc * nb * ni * 2, sp->flag.as<int>() + 1, s);
@@ -1514,6 +1515,7 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
     timing_resolve(sp->pending);
     if (unusable) return false;
   }
+  for (OutBuf *o : {&osig, &oimd, &ose, &osx, &oeq}) o->close(s);
   std::vector<double> e_newton;
   std::vector<int> qp_it;
   if (in.qp) {
@@ -1769,7 +1771,7 @@ void run_analytic(ResidentSystem &rs, const gwc_analytic_args *args, gwc_analyti
   launch_pole_sum(dQ.as<double>(), n, dOm.as<double>(), n, rs.d_eps.as<double>(), no, nbas, d_core,
                   nc, d_wr, nr, args->eta, 0, nullptr, dpart.as<double2>(), dsig.as<double2>(), s);
   dsx.alloc(nc * sizeof(double));
-  launch_sigma_x(rs.Moo, N, no, d_core, nc, dsx.as<double>(), s);
+  launch_sigma_x(rs.Moo, N, no, d_core, nc, dsx.as<double>(), nullptr, s);
   dsc.alloc((size_t)nc * nr * 2 * sizeof(double));
   dse.alloc((size_t)nc * 2 * sizeof(double));
   deq.alloc(nc * sizeof(double));

@@ -90,8 +90,10 @@ size_t ldlt_scratch_bytes(int F, int N);
 hipError_t launch_ldlt_bordered(double2 *G, long long g_stride, int ldg, int N, int R, int F,
                                 const double *bb, const long long *out_base, const int *out_stride,
                                 double2 *W_out, int *status, void *scratch, bool real, hipStream_t stream);
+// `refused` of the two launches that write a call's outputs: device flag, or
+// nullptr; where it is set (bad input found on the device) nothing is written.
 void launch_sigma_x(const double *M_oo, int n_aux, int n_occ, const int *core_idx, int n_core,
-                    double *sigma_x, hipStream_t stream);
+                    double *sigma_x, const int *refused, hipStream_t stream);
 void launch_quadrature(const double2 *W_imag, const double *eps, int n_basis,
                        const double *omega_imag, const double *w_imag, int n_imag,
                        const double *omega_real, int n_real, const int *core_idx, int n_core,
@@ -100,7 +102,7 @@ void launch_assemble(const double2 *W_real, const double *f_task, const int *tas
                      const int *cj_offset, const double *I, int n_core,
                      int n_real, const double *eps, const int *core_idx, const double *sigma_x,
                      const double *vxc, int full, double *sigma_c, double *im_dec,
-                     double *sigma_c_eps, double *e_qp, hipStream_t stream);
+                     double *sigma_c_eps, double *e_qp, const int *refused, hipStream_t stream);
 
 void launch_nonfinite(const double *x, long long n, int *flag, hipStream_t stream);
 

@@ -62,9 +62,11 @@ void launch_border(const double *M_oo, const double *M_ov, int n_aux, int n_occ,
 }
 
 // Sigma^x_n = -sum_{i occ} sum_P (M^P_ni)^2  (exchange over occupied orbitals).
+// Nothing is written where `refused` is set.
 __global__ void __launch_bounds__(256)
 sigma_x_kernel(const double *__restrict__ M_oo, int n_aux, int n_occ,
-               const int *__restrict__ core_idx, double *__restrict__ sigma_x) {
+               const int *__restrict__ core_idx, double *__restrict__ sigma_x, const int *__restrict__ refused) {
+  if (refused && *refused) return;
   __shared__ double sh[256];
   const int c = blockIdx.x, n = core_idx[c];
   double acc = 0.0;
@@ -79,8 +81,8 @@ sigma_x_kernel(const double *__restrict__ M_oo, int n_aux, int n_occ,
 }
 
 void launch_sigma_x(const double *M_oo, int n_aux, int n_occ, const int *core_idx, int n_core,
-                    double *sigma_x, hipStream_t stream) {
-  sigma_x_kernel<<<n_core, 256, 0, stream>>>(M_oo, n_aux, n_occ, core_idx, sigma_x);
+                    double *sigma_x, const int *refused, hipStream_t stream) {
+  sigma_x_kernel<<<n_core, 256, 0, stream>>>(M_oo, n_aux, n_occ, core_idx, sigma_x, refused);
 }
 
 // I_n(w) = (1/pi) sum_k w_k sum_m W^c_nm(i w_k) a / (a^2 + w_k^2), a = w - eps_m.
@@ -118,14 +120,17 @@ void launch_quadrature(const double2 *W_imag, const double *eps, int n_basis,
 }
 
 // Residue sum and assembly, one thread per (core, point).  Tasks of a point
-// are contiguous and ordered by m, so the sum order is fixed.
+// are contiguous and ordered by m, so the sum order is fixed.  Nothing is
+// written where `refused` is set.
 __global__ void assemble_kernel(const double2 *__restrict__ W_real, const double *__restrict__ f_task,
                                 const int *__restrict__ cj_offset, const int *__restrict__ task_dec,
                                 const double *__restrict__ I, int n_core, int n_real,
                                 const double *__restrict__ eps, const int *__restrict__ core_idx,
                                 const double *__restrict__ sigma_x, const double *__restrict__ vxc,
                                 int full, double *__restrict__ sigma_c, double *__restrict__ im_dec,
-                                double *__restrict__ sigma_c_eps, double *__restrict__ e_qp) {
+                                double *__restrict__ sigma_c_eps, double *__restrict__ e_qp,
+                                const int *__restrict__ refused) {
+  if (refused && *refused) return;
   const int cj = blockIdx.x * blockDim.x + threadIdx.x;
   const int npts = n_real + 1;
   if (cj >= n_core * npts) return;
@@ -157,12 +162,12 @@ void launch_assemble(const double2 *W_real, const double *f_task, const int *tas
                      const int *cj_offset, const double *I, int n_core,
                      int n_real, const double *eps, const int *core_idx, const double *sigma_x,
                      const double *vxc, int full, double *sigma_c, double *im_dec,
-                     double *sigma_c_eps, double *e_qp, hipStream_t stream) {
+                     double *sigma_c_eps, double *e_qp, const int *refused, hipStream_t stream) {
   const int total = n_core * (n_real + 1);
   assemble_kernel<<<(total + 63) / 64, 64, 0, stream>>>(W_real, f_task, cj_offset, task_dec, I,
                                                         n_core, n_real, eps, core_idx, sigma_x,
                                                         vxc, full, sigma_c, im_dec, sigma_c_eps,
-                                                        e_qp);
+                                                        e_qp, refused);
 }
 
 // Count of non-finite values (for input validation of device-resident arrays).
