@@ -935,7 +935,11 @@ SpectralSizes spectral_sizes(const ResidentSystem &rs, int n_core) {
 // contour deformation only: the mixed forms are defined by their Pi builds, and
 // a continued fraction magnifies any change of rounding in its nodes.
 bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t batch_bytes) {
-  if (args->precision != GWC_PREC_FP64 || args->wac || std::getenv("GWC_FACTORIZATION")) return false;
+  if (args->precision != GWC_PREC_FP64 || args->wac) return false;
+  // GWC_FACTORIZATION: "spectral" whatever the costs, any other value never
+  const char *env = std::getenv("GWC_FACTORIZATION");
+  const bool forced = env && std::string(env) == "spectral";
+  if (env && !forced) return false;
   const SpectralSizes z = spectral_sizes(rs, args->n_core);
   if (z.bytes > batch_bytes || (long long)z.np + z.Rp > (1 << 20)) return false;
   // rounding of the reduction, eps max(Delta^2), against the distance of z^2
@@ -949,6 +953,7 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
     min_d = vlo - hi;
   }
   if (std::numeric_limits<double>::epsilon() * max_d * max_d > 1e-10 * 2.0 * min_d * args->eta) return false;
+  if (forced) return true;
   // The times of the two routes for ONE core state, so that a call for several
   // cores and one for each take the same route.  Reduction: 68 us of dependent
   // steps a panel and n^3 at 0.037 ps (measured 2.2 ms at n_ov = 1026, 19 ms at

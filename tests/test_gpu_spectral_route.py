@@ -1,0 +1,83 @@
+"""The self-energy by the reduced transition matrix with the route chosen and
+asserted: GWC_FACTORIZATION=spectral takes the reduction whatever the cost rule
+says, and the kernel timers tell which route ran.
+
+Orders: 0 to 20 panels of 32, odd and even in number, with and without padding
+rows, panels of one and of several 64-, 128- and 256-row workgroups; one and
+several cores; both modes; against the CPU oracle at the suite's 1e-9.  A
+matrix whose panels have no 32 independent columns (equal energies: only the
+rank-3 coupling tells the transitions apart) runs the reduction, then the Pi
+builds, and the results are those of the Pi builds bit for bit."""
+import numpy as np
+import pytest
+
+import paper_2412_17132_amd as gwc
+from oracle import sigma as OS
+from workloads import system_from_config
+from workloads.configs import small_config
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+TOL = 1e-9
+
+
+def _run(s, mode, route, monkeypatch):
+    """The outputs, and the launches of (reduction, Pi builds)."""
+    if route is None:
+        monkeypatch.delenv("GWC_FACTORIZATION", raising=False)
+    else:
+        monkeypatch.setenv("GWC_FACTORIZATION", route)
+    d = gwc.to_device(s, torch.device("cuda:0"))
+    gwc.timing_enable(True)
+    try:
+        out = gwc.gwc_sigma_core(d["eps"], d["occ"], d["M_oo"], d["M_ov"], d["core_idx"], d["omega_imag"],
+                                 d["w_imag"], d["omega_real"], d["eta"], mode=mode)
+        torch.cuda.synchronize()
+        ran = gwc.timing_get("spectral_reduce")["launches"], gwc.timing_get("pi_build_f64")["launches"]
+    finally:
+        gwc.timing_enable(False)
+    return out, ran
+
+
+def _matches_oracle(s, out, mode, tol=TOL):
+    ref = OS.sigma_core_system(s, mode)
+    for c in range(s.n_core):
+        if mode == "full":
+            sc, r = out["sigma_c"][c].cpu().numpy(), ref["sigma_c"][c]
+            assert np.max(np.abs(sc[:, 0] + 1j * sc[:, 1] - r)) <= tol * np.max(np.abs(r)), c
+        im, r = out["im_sigma_dec"][c].cpu().numpy(), ref["im_sigma_dec"][c]
+        assert np.max(np.abs(im - r)) <= tol * np.max(np.abs(r)), c
+    assert np.allclose(out["e_qp"].cpu().numpy(), ref["e_qp"], rtol=tol, atol=0)
+
+
+# n_occ, n_virt, n_aux, n_core
+ORDERS = [(2, 16, 40, 1), (3, 11, 20, 1), (4, 16, 70, 2), (5, 13, 40, 2), (4, 24, 33, 1), (5, 26, 97, 3),
+          (5, 35, 160, 1), (6, 48, 129, 2), (9, 33, 64, 1), (7, 55, 61, 2), (10, 62, 130, 1), (11, 59, 90, 2)]
+
+
+@pytest.mark.parametrize("case", ORDERS, ids=[f"ov{c[0] * c[1]}" for c in ORDERS])
+def test_reduction_matches_oracle(case, monkeypatch):
+    n_occ, n_virt, n_aux, n_core = case
+    s = system_from_config(small_config(n_occ=n_occ, n_virt=n_virt, n_aux=n_aux, n_core=n_core, n_real=6,
+                                        seed=n_occ + n_virt, real_rel_ev=(-30.0, 10.0)))
+    print(f"case n_ov {n_occ * n_virt}", flush=True)
+    for mode in ("full", "decoupled"):
+        out, ran = _run(s, mode, "spectral", monkeypatch)
+        assert ran == (1, 0), (mode, ran)
+        _matches_oracle(s, out, mode)
+
+
+def test_dependent_panels_run_the_builds_after_the_reduction(monkeypatch):
+    s = system_from_config(small_config(n_occ=3, n_virt=40, n_aux=30, n_core=1, n_real=5, seed=77))
+    rng = np.random.default_rng(1)
+    s.M_ov = np.einsum("Pk,kia->Pia", rng.standard_normal((30, 3)), rng.standard_normal((3, 3, 40))) * 0.02
+    s.eps[:3], s.eps[3:] = -0.5, 0.25
+    s.omega_real = np.linspace(-1.4, -0.3, 5)[None]
+    print("case rank 3, equal energies", flush=True)
+    got, ran = _run(s, "full", "spectral", monkeypatch)
+    assert ran[0] == 1 and ran[1] > 0, ran
+    want, ran = _run(s, "full", "ldlt", monkeypatch)
+    assert ran[0] == 0 and ran[1] > 0, ran
+    for k in ("sigma_c", "im_sigma_dec", "sigma_c_eps", "sigma_x", "e_qp"):
+        assert torch.equal(got[k], want[k]), k
+    _matches_oracle(s, got, "full")
