@@ -966,7 +966,7 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   const double n = rs.n_ov, N = rs.N;
   const bool every = args->mode == GWC_MODE_FULL || rs.n_ov <= 320;
   const double tasks = args->n_imag + (double)args->n_real * (every ? rs.no : 1) + rs.no;
-  const double panels = std::ceil(n / SPECTRAL_BAND) - 1;
+  const double panels = std::ceil(n / SPECTRAL_BAND);
   const double t_reduce = 68e-6 * panels + 3.7e-14 * n * n * n;
   const double t_build = 120e-6 * std::ceil(N / 64) +
                          tasks * (2.0 * N * N * n + 4.0 / 3.0 * N * N * N) / (58e12 * N / (N + 150.0));
@@ -1022,7 +1022,7 @@ void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int 
   const SpectralWork w{dQ.as<double>(), {dY.as<double>(), dY2.as<double>()}, dX.as<double>(),
                        {dW.as<double>(), dW2.as<double>()}, dXp.as<double>(),
                        dBk.as<double>(), dpart.as<double>(), dsm.p, sp.flag.as<int>(), sp.flag.as<int>() + 1};
-  launch_spectral_reduce(dA.as<double>(), lda, np, z.pad, z.Rp, w, s);
+  launch_spectral_reduce(dA.as<double>(), lda, np, z.Rp, w, s);
   launch_spectral_pack(dA.as<double>(), lda, np, z.R, dBk.as<double>(), sp.band.as<double>(), sp.Ut.as<double>(), s);
   HIPCHECK(hipGetLastError());
   if (ea) {

@@ -108,7 +108,7 @@ void launch_nonfinite(const double *x, long long n, int *flag, hipStream_t strea
 
 // Spectral screening (kernels_spectral.hip): C = diag(Delta^2) + V^T V over the
 // n_ov transitions, reduced once to half-bandwidth SPECTRAL_BAND; each W is a
-// banded elimination.  np = n_ov rounded up to the band (pad = np - n_ov zero
+// banded elimination.  np = n_ov rounded up to the band (pad = np - n_ov decoupled
 // rows in front); A is np x lda with the vectors u in the columns from np on,
 // Rp of them (a multiple of 32, the unused ones zero).
 constexpr int SPECTRAL_BAND = 32;
@@ -137,8 +137,7 @@ void launch_spectral_pairs(const double *M_oo, const double *M_ov, int n_aux, in
                            const int *core, int R, int Rp, double *B, hipStream_t s);
 void launch_spectral_matrix(const double *V, int np, const double *Bp, int Rp, int n_aux, const double *diag2,
                             int pad, double *A, long long lda, hipStream_t s);
-void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, const SpectralWork &w,
-                            hipStream_t s);
+void launch_spectral_reduce(double *A, long long lda, int np, int Rp, const SpectralWork &w, hipStream_t s);
 // band: (np / 16 + 2) x 768; Ut: R x np.
 void launch_spectral_pack(const double *A, long long lda, int np, int R, const double *Bk, double *band,
                           double *Ut, hipStream_t s);

@@ -14,10 +14,15 @@
 // N_aux x N_aux Pi build (2 N^2 n_ov flops) and a factorisation (4/3 N^3):
 // about 8 32^2 n_ov flops.  The reduction costs 4/3 n_ov^3 flops, once a call.
 //
-// Reduction (indices ordered by Delta, so that the large Delta^2 of the core
-// transitions come last and do not spread their rounding over the small ones;
-// SB - n_ov % SB decoupled zero rows in front make the order a multiple of
-// SB).  Per panel P of SB columns with the m rows below its diagonal block, five
+// Reduction (indices ordered by Delta; SB - n_ov % SB decoupled rows in front,
+// with diagonal elements taken from the Delta^2, make the order a multiple of SB).
+// It starts with a reflection that turns the first SB coordinates into SB
+// pseudo-random directions: a band grown from single transitions runs out of
+// directions in one irreducible block of a symmetric molecule before the others
+// (at order 567 with two to eight blocks panel 6 to 14 of 16 is singular), random
+// ones only where an eigenvalue is SB-fold (smallest pivot there 1e-5 of its
+// diagonal element).  It costs one panel more, 1/32 of the reduction at order
+// 1026.  Per panel P of SB columns with the m rows below its diagonal block, five
 // dependent launches:
 //   panel_q        Q = P L1^-T by rows, with G = P^T P = L1 L1^T from the launch
 //                  before, and partial sums of G2 = Q^T Q = 1 + E;
@@ -446,8 +451,9 @@ static unsigned triangle_tiles(int nt) { return (unsigned)((nt + 1) / 2) * (unsi
 // out[i][j] = sum_P A[P][i] B[P][j] on MFMA, a square of 16 W columns per wave,
 // four waves a workgroup; the operands are rows of A and B (16 consecutive
 // doubles a quarter wave), read through the L1 a batch of 32 / W rows ahead.
-// SYM: A = B, tiles i <= j, and diag2[i - pad] is added on the diagonal.  Sizes
-// are multiples of 32.  Bound by the matrix cores where W = 4 (half the operand
+// SYM: A = B, tiles i <= j, and diag2[i - pad] is added on the diagonal (on the
+// `pad` rows in front, where A is zero, elements spread over diag2: distinct, so
+// that no eigenvalue becomes SB-fold by them).  Sizes are multiples of 32.  Bound by the matrix cores where W = 4 (half the operand
 // loads a product), which needs many tiles to fill the chip.
 template <bool SYM, int W>
 __global__ void __launch_bounds__(256, W == 4 ? 2 : 4)
@@ -517,10 +523,23 @@ spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__rest
       for (int r = 0; r < 4; ++r) {
         const int i = i0 + 16 * a + 4 * r + lk, j = j0 + 16 * b + li;
         double x = acc[a][b][r];
-        if (SYM && i == j && i >= pad) x += diag2[i - pad];
+        if (SYM && i == j) x += diag2[i >= pad ? i - pad : (int)((long long)i * (M - pad) / SB)];
         out[(long long)i * ldo + j] = x;
       }
     }
+}
+
+// The panel of the first reflection: column c of P[c][row] is SB m pseudo-random
+// numbers in (-1, 1) (the mixing function of splitmix64 on the element's index).
+__global__ void __launch_bounds__(256)
+panel_start_kernel(double *__restrict__ P, long long count) {
+  const long long e = blockIdx.x * 256LL + threadIdx.x;
+  if (e >= count) return;
+  unsigned long long x = (unsigned long long)(e + 1) * 0x9e3779b97f4a7c15ull;
+  x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+  x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+  x ^= x >> 31;
+  P[e] = (double)(long long)x * 0x1p-63;
 }
 
 // Sum of the per-wave Gram tiles (0,0), (0,1), (1,1) through LDS: element
@@ -543,24 +562,23 @@ __device__ __forceinline__ void gram_combine(double *buf, const d4 &g00, const d
   }
 }
 
-// The symmetric 32 x 32 matrix of `count` partial sums; a unit diagonal for
-// the inactive columns bw ..
-__device__ __forceinline__ void gram_collect(const double *part, int stride, int count, int bw, double (*G)[SLD]) {
+// The symmetric 32 x 32 matrix of `count` partial sums.
+__device__ __forceinline__ void gram_collect(const double *part, int stride, int count, double (*G)[SLD]) {
   const int tid = threadIdx.x, i = tid >> 4, j = tid & 15;
   double s[3];
   ordered_sums(part, tid, 256, stride, count, s);
-  G[i][j] = (i == j && i >= bw) ? 1.0 : s[0];
+  G[i][j] = s[0];
   G[i][16 + j] = s[1];
   G[16 + j][i] = s[1];
-  G[16 + i][16 + j] = (i == j && 16 + i >= bw) ? 1.0 : s[2];
+  G[16 + i][16 + j] = s[2];
 }
 
 // G = L1 L1^T by one workgroup; buf holds SB SLD doubles.
-__device__ __forceinline__ void panel_factor(const double *part, int count, int bw, double *buf, PanelSmall *sm, int *flag) {
+__device__ __forceinline__ void panel_factor(const double *part, int count, double *buf, PanelSmall *sm, int *flag) {
   __shared__ double rdsh[SB];
   double(*G)[SLD] = reinterpret_cast<double(*)[SLD]>(buf);
   const int tid = threadIdx.x;
-  gram_collect(part, 768, count, bw, G);
+  gram_collect(part, 768, count, G);
   __syncthreads();
   if (tid < 64) {
     const bool bad = chol32(G, rdsh, tid);
@@ -575,10 +593,9 @@ __device__ __forceinline__ void panel_factor(const double *part, int count, int 
   if (tid < SB) sm->rd1[tid] = rdsh[tid];
 }
 
-// G of the first panel (m rows from P, `bw` active columns; the others count as
-// zero) and its factor: 256 rows per workgroup.
+// G of the first reflection's panel (m rows) and its factor: 256 rows per workgroup.
 __global__ void __launch_bounds__(PROWS)
-panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, int bw, PanelSmall *__restrict__ sm,
+panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, PanelSmall *__restrict__ sm,
                   double *part, int *__restrict__ ticket, int *__restrict__ flag) {
   __shared__ double buf[PROWS * SLD];
   __shared__ int last;
@@ -587,7 +604,7 @@ panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, int bw, Pa
   const int row0 = blockIdx.x * PROWS;
   double q[SB];
 #pragma unroll
-  for (int c = 0; c < SB; ++c) q[c] = (row0 + tid < m && c < bw) ? P[(long long)c * ldp + row0 + tid] : 0.0;
+  for (int c = 0; c < SB; ++c) q[c] = row0 + tid < m ? P[(long long)c * ldp + row0 + tid] : 0.0;
 #pragma unroll
   for (int c = 0; c < SB; ++c) S[tid][c] = q[c];
   __syncthreads();
@@ -602,7 +619,7 @@ panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, int bw, Pa
   }
   __syncthreads();
   gram_combine(buf, g00, g01, g11, [&](int e, double v) { put_through(part + (long long)blockIdx.x * 768 + e, v); });
-  if (last_arrival(ticket, gridDim.x, &last)) panel_factor(part, gridDim.x, bw, buf, sm, flag);
+  if (last_arrival(ticket, gridDim.x, &last)) panel_factor(part, gridDim.x, buf, sm, flag);
 }
 
 // Q = P L1^-T, one row per thread, and the partial sums of Q^T Q; for a pair's
@@ -611,7 +628,7 @@ panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, int bw, Pa
 // (24 -> 10.7 us at 5859 rows; four batches and scalar loads of L1 before).
 template <bool SECOND>
 __global__ void __launch_bounds__(PROWS)
-panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const PanelSmall *__restrict__ sm,
+panel_q_kernel(const double *__restrict__ P, long long ldp, int m, const PanelSmall *__restrict__ sm,
                const double *__restrict__ Ya, const double *__restrict__ Wa, double *__restrict__ Q,
                double *__restrict__ part) {
   __shared__ double buf[PROWS * SLD];
@@ -621,7 +638,7 @@ panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const
   // R1's row j at lane li: columns li (ra, j < 16) and 16 + li (rb)
   double q[SB], ra[16], rb[SB];
 #pragma unroll
-  for (int c = 0; c < SB; ++c) q[c] = (row0 + tid < m && c < bw) ? P[(long long)c * ldp + row0 + tid] : 0.0;
+  for (int c = 0; c < SB; ++c) q[c] = row0 + tid < m ? P[(long long)c * ldp + row0 + tid] : 0.0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) ra[j] = sm->R1[j * SB + li];
 #pragma unroll
@@ -719,7 +736,7 @@ panel_q_kernel(const double *__restrict__ P, long long ldp, int m, int bw, const
 // (see the head of this file), by one workgroup, and V1, V2 of a pair's second
 // panel; buf holds 4 SB SLD + SB doubles.
 template <bool SECOND>
-__device__ __forceinline__ void panel_reconstruct(const double *__restrict__ Q, const double *part, int count, int bw,
+__device__ __forceinline__ void panel_reconstruct(const double *__restrict__ Q, const double *part, int count,
                                   const double *__restrict__ Ya, const double *__restrict__ Wa, double *buf,
                                   PanelSmall *__restrict__ sm, int *flag, double *__restrict__ Bk) {
   constexpr int PART = SECOND ? Q_PART2 : Q_PART;
@@ -737,7 +754,7 @@ __device__ __forceinline__ void panel_reconstruct(const double *__restrict__ Q, 
     q0[q] = Q[e];
     r1[q] = sm->R1[e];
   }
-  gram_collect(part, PART, count, bw, G);
+  gram_collect(part, PART, count, G);
   __syncthreads();
   int off = 0;
   double phi[4], r2[4];
@@ -799,12 +816,10 @@ __device__ __forceinline__ void panel_reconstruct(const double *__restrict__ Q, 
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = i0 + 4 * r, j = j0, e = i * SB + j;
-    sm->M2[e] = j < bw ? G[i][j] - pu[r] : 0.0;
-    sm->SU[e] = j < bw ? sg[i] * G[i][j] : 0.0;
-    sm->T[e] = (i <= j && j < bw) ? tf[r] : 0.0;
-    // column j of the panel is column SB - bw + j of its block
-    if (j < bw) Bk[i * SB + SB - bw + j] = i <= j ? sg[i] * b[r] : 0.0;
-    else Bk[i * SB + j - bw] = 0.0;
+    sm->M2[e] = G[i][j] - pu[r];
+    sm->SU[e] = sg[i] * G[i][j];
+    sm->T[e] = i <= j ? tf[r] : 0.0;
+    Bk[e] = i <= j ? sg[i] * b[r] : 0.0;
   }
   if (SECOND) {
     // V = (Z^T Q) M2 - Z_top^T SU for Z = Wa, Ya: M2 in G, SU in H
@@ -846,13 +861,13 @@ __device__ __forceinline__ void panel_reconstruct(const double *__restrict__ Q, 
 // registers are bounded by what the product needs.)
 template <bool SECOND>
 __global__ void __launch_bounds__(256, 3)
-panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int bw, int splits,
+panel_x_kernel(const double *__restrict__ A, long long lda, int m, int mx, int splits,
                const double *__restrict__ Q, double *__restrict__ Xpart, const double *__restrict__ part,
                int parts2, const double *__restrict__ Ya, const double *__restrict__ Wa,
                PanelSmall *__restrict__ sm, int *__restrict__ flag, double *__restrict__ Bk) {
   __shared__ double buf[4 * SB * SLD + SB];
   if (blockIdx.x == 0) {
-    panel_reconstruct<SECOND>(Q, part, parts2, bw, Ya, Wa, buf, sm, flag, Bk);
+    panel_reconstruct<SECOND>(Q, part, parts2, Ya, Wa, buf, sm, flag, Bk);
     return;
   }
   double(*red)[SB * SB] = reinterpret_cast<double(*)[SB * SB]>(buf);
@@ -1211,7 +1226,7 @@ panel_update_kernel(double *__restrict__ A, long long lda, int m, int mx, const 
   }
   __syncthreads();
   gram_combine(Rs, g00, g01, g11, [&](int e, double v) { put_through(part + (long long)(j0 / UT) * 768 + e, v); });
-  if (last_arrival(ticket, nt, &last)) panel_factor(part, nt, SB, Ls, sm, flag);
+  if (last_arrival(ticket, nt, &last)) panel_factor(part, nt, Ls, sm, flag);
 }
 
 // The band in 16 x 16 tiles, per 16-row block p: (p, p), (p, p + 1), (p, p + 2);
@@ -1566,42 +1581,51 @@ void launch_spectral_matrix(const double *V, int np, const double *Bp, int Rp, i
                                                                           A + np, lda);
 }
 
-void launch_spectral_reduce(double *A, long long lda, int np, int pad, int Rp, const SpectralWork &w, hipStream_t s) {
+void launch_spectral_reduce(double *A, long long lda, int np, int Rp, const SpectralWork &w, hipStream_t s) {
   PanelSmall *sm = static_cast<PanelSmall *>(w.small);
   const int panels = np / SB - 1;
-  bool pair = false, second = false;
-  for (int k = 0; k < panels; ++k) {
-    const int c0 = k * SB, r0 = c0 + SB, m = np - r0, mx = m + Rp;
-    const int off = k == 0 ? pad : 0, bw = SB - off;  // the first block's zero columns are no panel
-    if (k & 1) second = pair;
-    else second = false;
-    // a pair saves a pass over A22 and costs products of its own
-    pair = !(k & 1) && k + 1 < panels && m >= PAIR_ROWS;
-    const double *P = A + (long long)(c0 + off) * lda + r0;  // transposed
-    double *A22 = A + (long long)r0 * lda + r0;
+  if (panels < 1) return;
+  // One reflection: of the matrix A22 (m rows, u's columns behind) by the panel P
+  // (transposed); `second`: of a pair; `strip`: the pair's first, whose update of
+  // all but the next panel waits for the second's.
+  auto reflect = [&](const double *P, long long ldp, double *A22, int m, double *Bk, bool second, bool strip) {
     // rows of the first panel's Y and W from this panel's first row on
     const double *Ya = w.Y[0] + SB * SB, *Wa = w.W[0] + SB * SB;
-    double *Y = w.Y[second], *W = w.W[second], *Bk = w.Bk + (long long)k * SB * SB;
-    const int ng = (m + PROWS - 1) / PROWS, nx = mx / SB;
+    double *Y = w.Y[second], *W = w.W[second];
+    const int mx = m + Rp, ng = (m + PROWS - 1) / PROWS, nx = mx / SB;
     // splits of the rows: about eight workgroups a CU, a wave's part at least 32 rows
     const int splits = std::max(1, std::min({SPECTRAL_MAX_SPLITS, 2048 / nx, m / 128}));
     const unsigned gx = 1 + nx * splits, gs = (mx + XROWS - 1) / XROWS;
-    if (k == 0) panel_gram_kernel<<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, w.part, w.ticket, w.flag);
     if (second) {
-      panel_q_kernel<true><<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, Ya, Wa, w.Q, w.part);
-      panel_x_kernel<true><<<gx, 256, 0, s>>>(A22, lda, m, mx, bw, splits, w.Q, w.Xpart, w.part, ng, Ya, Wa, sm, w.flag, Bk);
+      panel_q_kernel<true><<<ng, PROWS, 0, s>>>(P, ldp, m, sm, Ya, Wa, w.Q, w.part);
+      panel_x_kernel<true><<<gx, 256, 0, s>>>(A22, lda, m, mx, splits, w.Q, w.Xpart, w.part, ng, Ya, Wa, sm, w.flag, Bk);
       panel_xsum_kernel<true><<<gs, XTHREADS, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, Ya, Wa, sm, sm, w.X, Y, w.part, w.ticket);
     } else {
-      panel_q_kernel<false><<<ng, PROWS, 0, s>>>(P, lda, m, bw, sm, nullptr, nullptr, w.Q, w.part);
-      panel_x_kernel<false><<<gx, 256, 0, s>>>(A22, lda, m, mx, bw, splits, w.Q, w.Xpart, w.part, ng, nullptr, nullptr, sm, w.flag, Bk);
+      panel_q_kernel<false><<<ng, PROWS, 0, s>>>(P, ldp, m, sm, nullptr, nullptr, w.Q, w.part);
+      panel_x_kernel<false><<<gx, 256, 0, s>>>(A22, lda, m, mx, splits, w.Q, w.Xpart, w.part, ng, nullptr, nullptr, sm, w.flag, Bk);
       panel_xsum_kernel<false><<<gs, XTHREADS, 0, s>>>(w.Xpart, splits, A22, lda, m, mx, w.Q, nullptr, nullptr, sm, sm, w.X, Y, w.part, w.ticket);
     }
     panel_w_kernel<<<(mx + 63) / 64, 256, 0, s>>>(w.X, Y, m, mx, sm, W);
     const double *y0 = second ? Ya : Y, *w0 = second ? Wa : W, *y1 = second ? Y : nullptr, *w1 = second ? W : nullptr;
     const int nt = (m + UT - 1) / UT, nu = (Rp + UT - 1) / UT;
     const unsigned tri = triangle_tiles(nt);
-    if (pair) panel_update_kernel<true><<<nt + nu, 256, 0, s>>>(A22, lda, m, mx, y0, w0, y1, w1, nt, sm, w.part, w.ticket, w.flag);
+    if (strip) panel_update_kernel<true><<<nt + nu, 256, 0, s>>>(A22, lda, m, mx, y0, w0, y1, w1, nt, sm, w.part, w.ticket, w.flag);
     else panel_update_kernel<false><<<tri + nt * nu, 256, 0, s>>>(A22, lda, m, mx, y0, w0, y1, w1, (int)tri, sm, w.part, w.ticket, w.flag);
+  };
+  // the first coordinates, pseudo-random: their panel in X, which is written only
+  // after the panel has been read; its coupling goes to Bk's last block, which no
+  // pair of diagonal blocks uses
+  const long long count = (long long)SB * np;
+  panel_start_kernel<<<(unsigned)((count + 255) / 256), 256, 0, s>>>(w.X, count);
+  panel_gram_kernel<<<(np + PROWS - 1) / PROWS, PROWS, 0, s>>>(w.X, np, np, sm, w.part, w.ticket, w.flag);
+  reflect(w.X, np, A, np, w.Bk + (long long)panels * SB * SB, false, false);
+  bool pair = false, second = false;
+  for (int k = 0; k < panels; ++k) {
+    const int c0 = k * SB, r0 = c0 + SB, m = np - r0;
+    second = (k & 1) && pair;
+    // a pair saves a pass over A22 and costs products of its own
+    pair = !(k & 1) && k + 1 < panels && m >= PAIR_ROWS;
+    reflect(A + (long long)c0 * lda + r0, lda, A + (long long)r0 * lda + r0, m, w.Bk + (long long)k * SB * SB, second, pair);
   }
 }
 

@@ -67,6 +67,39 @@ def test_reduction_matches_oracle(case, monkeypatch):
         _matches_oracle(s, out, mode)
 
 
+def _symmetric(n_irreps, coupling, n_occ=9, n_virt=63, n_aux=288):
+    """Coefficients that vanish by the product rule of an Abelian group (up to
+    `coupling` of an ordinary one): C falls into n_irreps blocks."""
+    s = system_from_config(small_config(n_occ=n_occ, n_virt=n_virt, n_aux=n_aux, n_core=3, n_real=6, seed=n_irreps))
+    rng = np.random.default_rng(n_irreps + 5)
+    go, gv, gp = (rng.integers(n_irreps, size=n) for n in (n_occ, n_virt, n_aux))
+    keep = lambda a, b: np.where((a[:, None] ^ b[None, :])[None] == gp[:, None, None], np.sqrt(n_irreps), coupling)  # noqa: E731
+    s.M_oo, s.M_ov = s.M_oo * keep(go, go), s.M_ov * keep(go, gv)
+    return s
+
+
+@pytest.mark.parametrize("coupling", [0.0, 1e-14])
+@pytest.mark.parametrize("n_irreps", [2, 4, 8])
+def test_symmetric_molecules_are_reduced(n_irreps, coupling, monkeypatch):
+    """A band grown from single transitions exhausts one irreducible block before
+    the others, and its panels become singular (panel 6 to 14 of 16 here)."""
+    print(f"case {n_irreps} blocks, coupling {coupling}", flush=True)
+    s = _symmetric(n_irreps, coupling)
+    out, ran = _run(s, "decoupled", "spectral", monkeypatch)
+    assert ran == (1, 0), ran
+    _matches_oracle(s, out, "decoupled")
+
+
+def test_fewer_coefficients_than_a_panel_has_columns(monkeypatch):
+    """The coupling has rank 31: the panels of a band grown from single
+    transitions have no 32 independent columns."""
+    print("case rank 31", flush=True)
+    s = system_from_config(small_config(n_occ=7, n_virt=55, n_aux=31, n_core=2, n_real=6, seed=62, real_rel_ev=(-30.0, 10.0)))
+    out, ran = _run(s, "full", "spectral", monkeypatch)
+    assert ran == (1, 0), ran
+    _matches_oracle(s, out, "full")
+
+
 def test_dependent_panels_run_the_builds_after_the_reduction(monkeypatch):
     s = system_from_config(small_config(n_occ=3, n_virt=40, n_aux=30, n_core=1, n_real=5, seed=77))
     rng = np.random.default_rng(1)
