@@ -903,32 +903,59 @@ void run_screening(ResidentSystem &rs, const MixedOperands *mx, int precision, c
 
 // ---------------------------------------------------------------------------
 // Spectral screening (kernels_spectral.hip): the transition matrix of a system
-// reduced to a band, with the vectors u = V^T b_nm of the call's core states.
+// reduced to a band, with what turns its solutions into the W of the call's core
+// states.
 struct Spectral {
-  int np = 0, nb = 0;
+  int np = 0, pad = 0, Np = 0, Rp = 0, N = 0, nb = 0, batch = 0;
   std::vector<int> column;  // by state: its first vector, or -1
-  DevBuf band, Ut, flag;
+  const double *delta = nullptr;  // ascending, kept by the call
+  DevBuf band, Ut, V, Vh, B, flag;
   std::vector<PendingTiming> pending;
   std::deque<std::vector<SpectralTask>> tasks;  // uploaded, kept until the call has synchronised
-  explicit Spectral(hipStream_t s) : band(s), Ut(s), flag(s) {}
+  explicit Spectral(hipStream_t s) : band(s), Ut(s), V(s), Vh(s), B(s), flag(s) {}
 };
 
 struct SpectralSizes {
-  int pad, np, R, Rp;
-  size_t bytes;  // the most the reduction holds at a time
+  int pad, np, Np, R, Rp;
+  int batch;     // residue tasks of one launch
+  size_t bytes;  // the most the reduction and the residues hold at a time
 };
 
-SpectralSizes spectral_sizes(const ResidentSystem &rs, int n_core) {
+// `residues`: the call's residue tasks or a bound of them; `budget`: what the
+// call may hold (batch = 0: nothing fits).
+SpectralSizes spectral_sizes(const ResidentSystem &rs, int n_core, size_t residues, size_t budget) {
+  // as many tasks at once as fill the device twice over, and 16 GiB
+  constexpr size_t MOST = 2048, MOST_BYTES = size_t(16) << 30;
   SpectralSizes z;
   z.np = (int)round_up(rs.n_ov, SPECTRAL_BAND);
   z.pad = z.np - rs.n_ov;
+  z.Np = (int)round_up(rs.N, SPECTRAL_BAND);
   z.R = n_core * rs.nb;
   z.Rp = (int)round_up(z.R, SPECTRAL_BAND);
-  const size_t np = z.np, ext = (size_t)z.np + z.Rp;
-  z.bytes = sizeof(double) * (np * ext + (size_t)rs.N * ext + SPECTRAL_BAND * (4 * np + (3 + SPECTRAL_MAX_SPLITS) * ext) +
-                              (np / 16 + 2) * 768 + np * z.R + spectral_gram_parts(z.np) + spectral_xsum_parts(z.np)) +
-            np * (sizeof(int) + sizeof(double)) + spectral_small_bytes() + 8192;
+  const size_t np = z.np, ext = np + z.Np, d = sizeof(double);
+  const size_t kept = d * ((size_t)rs.N * (np + z.Rp) + np * z.Np + (size_t)z.Rp * np + (np / 16 + 2) * 768) +
+                      np * (sizeof(int) + d) + 8192;
+  const size_t reduce = d * (np * ext + (size_t)rs.N * np + SPECTRAL_BAND * (4 * np + (3 + SPECTRAL_MAX_SPLITS) * ext) +
+                             std::max(spectral_gram_parts(z.np), spectral_xsum_parts(z.np))) +
+                        spectral_small_bytes();
+  auto residue = [&](size_t T) {
+    return T * (np / 16 * SPECTRAL_ROWS + 1) * sizeof(double2) +
+           d * (2 * T * np + (np + z.Np) * spectral_columns((int)T) + spectral_residue_parts(rs.N, z.np, (int)T));
+  };
+  size_t T = std::max<size_t>(1, std::min(residues, MOST));
+  while (T > 1 && (residue(T) > MOST_BYTES || kept + residue(T) > budget)) T -= (T + 7) / 8;
+  z.bytes = kept + std::max(reduce, residue(T));
+  z.batch = z.bytes <= budget ? (int)T : 0;
   return z;
+}
+
+// The residue tasks of a call, bounded without reading its grids: every orbital
+// at every point (FULL), or the equivalent set (at most every occupied orbital)
+// per point plus every orbital at eps_n (DECOUPLED).
+size_t residue_bound(const ResidentSystem &rs, const gwc_sigma_args *args) {
+  const size_t nc = std::max(args->n_core, 1), nr = std::max(args->n_real, 1);
+  const size_t per_point = args->sym_group ? (size_t)rs.no : 1;
+  return args->mode == GWC_MODE_FULL ? nc * (nr + 1) * rs.nb : nc * (nr * per_point + rs.nb);
 }
 
 // Whether the W of a call come from the reduced transition matrix.  FP64
@@ -940,8 +967,8 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   const char *env = std::getenv("GWC_FACTORIZATION");
   const bool forced = env && std::string(env) == "spectral";
   if (env && !forced) return false;
-  const SpectralSizes z = spectral_sizes(rs, args->n_core);
-  if (z.bytes > batch_bytes || (long long)z.np + z.Rp > (1 << 20)) return false;
+  const SpectralSizes z = spectral_sizes(rs, args->n_core, residue_bound(rs, args), batch_bytes);
+  if (z.batch < 1 || (long long)z.np + z.Np > (1 << 20) || z.R > (1 << 20)) return false;
   // rounding of the reduction, eps max(Delta^2), against the distance of z^2
   // from the poles, 2 x eta with x at least the smallest transition
   double max_d = 0.0, min_d = std::numeric_limits<double>::infinity();
@@ -973,33 +1000,38 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   return t_reduce < t_build;
 }
 
-// Transitions by ascending Delta, and Delta^2 in that order.
-void spectral_order(const ResidentSystem &rs, std::vector<int> &perm, std::vector<double> &diag2) {
+// Transitions by ascending Delta, and Delta in that order.
+void spectral_order(const ResidentSystem &rs, std::vector<int> &perm, std::vector<double> &sorted) {
   const int no = rs.no, nv = rs.nv, n = rs.n_ov;
   std::vector<double> delta(n);
   perm.resize(n);
-  diag2.resize(n);
+  sorted.resize(n);
   for (int i = 0; i < no; ++i)
     for (int a = 0; a < nv; ++a) delta[(size_t)i * nv + a] = rs.eps[no + a] - rs.eps[i];
   for (int k = 0; k < n; ++k) perm[k] = k;
   std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) { return delta[x] < delta[y]; });
-  for (int k = 0; k < n; ++k) diag2[k] = delta[perm[k]] * delta[perm[k]];
+  for (int k = 0; k < n; ++k) sorted[k] = delta[perm[k]];
 }
 
-void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int *d_core, const int *d_perm,
-                    const double *d_diag2, Spectral &sp, hipStream_t s) {
+void spectral_build(ResidentSystem &rs, const SpectralSizes &z, const std::vector<int> &core, const int *d_core,
+                    const int *d_perm, const double *d_delta, Spectral &sp, hipStream_t s) {
   const int no = rs.no, nv = rs.nv, n = rs.n_ov, N = rs.N;
-  const SpectralSizes z = spectral_sizes(rs, (int)core.size());
   const int np = z.np;
-  const long long lda = (long long)np + z.Rp;
+  const long long lda = (long long)np + z.Np;
   sp.np = np;
+  sp.pad = z.pad;
+  sp.Np = z.Np;
+  sp.Rp = z.Rp;
+  sp.N = N;
   sp.nb = rs.nb;
+  sp.batch = z.batch;
+  sp.delta = d_delta;
   sp.column.assign(no, -1);
   for (size_t c = core.size(); c-- > 0;) sp.column[core[c]] = (int)c * rs.nb;
-  DevBuf dA(s), dV(s), dB(s), dQ(s), dY(s), dY2(s), dX(s), dW(s), dW2(s), dXp(s), dBk(s), dpart(s), dsm(s);
+  DevBuf dA(s), dVt(s), dQ(s), dY(s), dY2(s), dX(s), dW(s), dW2(s), dXp(s), dBk(s), dpart(s), dsm(s);
   dA.alloc((size_t)np * lda * sizeof(double));
-  dV.alloc((size_t)N * np * sizeof(double));
-  dB.alloc((size_t)N * z.Rp * sizeof(double));
+  sp.V.alloc((size_t)N * np * sizeof(double));
+  sp.B.alloc((size_t)N * z.Rp * sizeof(double));
   const size_t row = SPECTRAL_BAND * sizeof(double);
   dQ.alloc(np * row);
   dY.alloc(np * row);
@@ -1012,51 +1044,76 @@ void spectral_build(ResidentSystem &rs, const std::vector<int> &core, const int 
   dpart.alloc((size_t)std::max(spectral_gram_parts(np), spectral_xsum_parts(np)) * sizeof(double));
   dsm.alloc(spectral_small_bytes());
   sp.band.alloc((size_t)(np / 16 + 2) * 768 * sizeof(double));
-  sp.Ut.alloc((size_t)z.R * np * sizeof(double));
+  sp.Ut.alloc((size_t)z.Rp * np * sizeof(double));
+  dVt.alloc((size_t)N * np * sizeof(double));
+  sp.Vh.alloc((size_t)np * z.Np * sizeof(double));
   sp.flag.alloc(2 * sizeof(int));
   launch_zero_counters(sp.flag.as<int>(), 2, s);
-  launch_spectral_operand(rs.Mov, rs.d_eps.as<double>(), d_perm, N, no, nv, z.pad, np, dV.as<double>(), s);
-  launch_spectral_pairs(rs.Moo, rs.Mov, N, no, nv, d_core, z.R, z.Rp, dB.as<double>(), s);
+  launch_spectral_operand(rs.Mov, rs.d_eps.as<double>(), d_perm, N, no, nv, z.pad, np, sp.V.as<double>(), s);
+  launch_spectral_pairs(rs.Moo, rs.Mov, N, no, nv, d_core, z.R, z.Rp, sp.B.as<double>(), s);
   hipEvent_t ea = g_timing ? timing_mark(s) : nullptr;
-  launch_spectral_matrix(dV.as<double>(), np, dB.as<double>(), z.Rp, N, d_diag2, z.pad, dA.as<double>(), lda, s);
+  launch_spectral_matrix(sp.V.as<double>(), np, z.Np, N, d_delta, z.pad, dA.as<double>(), lda, s);
   const SpectralWork w{dQ.as<double>(), {dY.as<double>(), dY2.as<double>()}, dX.as<double>(),
                        {dW.as<double>(), dW2.as<double>()}, dXp.as<double>(),
                        dBk.as<double>(), dpart.as<double>(), dsm.p, sp.flag.as<int>(), sp.flag.as<int>() + 1};
-  launch_spectral_reduce(dA.as<double>(), lda, np, z.Rp, w, s);
-  launch_spectral_pack(dA.as<double>(), lda, np, z.R, dBk.as<double>(), sp.band.as<double>(), sp.Ut.as<double>(), s);
+  launch_spectral_reduce(dA.as<double>(), lda, np, z.Np, w, s);
+  launch_spectral_pack(dA.as<double>(), lda, np, z.Np, N, dBk.as<double>(), sp.B.as<double>(), z.Rp, sp.band.as<double>(),
+                       dVt.as<double>(), sp.Vh.as<double>(), sp.Ut.as<double>(), s);
   HIPCHECK(hipGetLastError());
   if (ea) {
-    // V^T V (its half) and V^T b, the reduction of the matrix and of u
+    // V^T V (its half), the reduction of the matrix and of V, the vectors u
     const double nn = (double)n * n;
-    sp.pending.push_back({6, ea, timing_mark(s), nn * N + 2.0 * N * n * z.R + 4.0 / 3.0 * nn * n + 2.0 * nn * z.R});
+    sp.pending.push_back({6, ea, timing_mark(s), nn * N + 4.0 / 3.0 * nn * n + 2.0 * nn * N + 2.0 * N * n * z.R});
   }
 }
 
-// W of every task from the band (the spectral counterpart of run_screening).
+// W of every task from the band (the spectral counterpart of run_screening): all
+// on the imaginary axis, of R vectors each, or residues of one vector.
 void spectral_screen(Spectral &sp, const TaskList &tl, int R, double2 *W_out, hipStream_t s) {
   const size_t T = tl.size();
   if (T == 0) return;
   sp.tasks.emplace_back();
   std::vector<SpectralTask> &tasks = sp.tasks.back();
-  const bool real = std::all_of(tl.z.begin(), tl.z.end(), [](const double2 &z) { return z.x == 0.0; });
-  const int most = real ? SPECTRAL_MAX_RHS : 1;
+  const bool real = R > 1;
   for (size_t t = 0; t < T; ++t) {
-    const double x = tl.z[t].x, y = tl.z[t].y;
-    SpectralTask k{(x - y) * (x + y), 2.0 * x * y, tl.out_base[t], tl.out_stride[t], sp.column[tl.n[t]] + std::max(tl.m[t], 0), 1};
-    for (int r = 0; r < R; r += most) {
+    const SpectralTask k{tl.z[t].x, tl.z[t].y, tl.out_base[t], tl.out_stride[t], sp.column[tl.n[t]] + std::max(tl.m[t], 0), 1};
+    for (int r = 0; r < R; r += SPECTRAL_MAX_RHS) {
       SpectralTask q = k;
       q.out_base += (long long)r * k.out_stride;
       q.col += r;
-      q.nrhs = std::min(most, R - r);
+      q.nrhs = std::min(SPECTRAL_MAX_RHS, R - r);
       tasks.push_back(q);
     }
   }
   DevBuf dt(s);
   const SpectralTask *d_t = upload(dt, tasks, s);
+  const int np = sp.np, count = (int)tasks.size();
   hipEvent_t ea = g_timing ? timing_mark(s) : nullptr;
-  launch_spectral_w(sp.band.as<double>(), sp.Ut.as<double>(), sp.np, d_t, (int)tasks.size(), real, W_out, s);
+  double flops = (double)count * SPECTRAL_BAND * SPECTRAL_BAND * np;
+  if (real) {
+    launch_spectral_w(sp.band.as<double>(), sp.Ut.as<double>(), np, d_t, count, W_out, s);
+  } else {
+    // the elimination in complex numbers, and V H x and V^T w
+    flops = 4.0 * flops + 8.0 * (double)count * sp.N * np;
+    // equal launches, of whole rounds of the device: 1024 tasks run at once
+    const int parts = (count + sp.batch - 1) / sp.batch;
+    const int each = std::min({count, sp.batch, (int)round_up((count + parts - 1) / parts, 1024)});
+    DevBuf df(s), dX(s), dXG(s), dY(s), dp(s), dW(s);
+    df.alloc((size_t)each * (np / 16) * SPECTRAL_ROWS * sizeof(double2));
+    dX.alloc((size_t)2 * each * np * sizeof(double));
+    dXG.alloc((size_t)np * spectral_columns(each) * sizeof(double));
+    dY.alloc((size_t)sp.Np * spectral_columns(each) * sizeof(double));
+    dp.alloc(spectral_residue_parts(sp.N, np, each) * sizeof(double));
+    dW.alloc((size_t)each * sizeof(double2));
+    const SpectralResidueWork w{df.as<double2>(), dX.as<double>(), dXG.as<double>(), dY.as<double>(), dp.as<double>(),
+                                dW.as<double2>()};
+    for (int t0 = 0; t0 < count; t0 += each)
+      launch_spectral_residues(sp.band.as<double>(), sp.Ut.as<double>(), np, sp.pad, sp.V.as<double>(), sp.N,
+                               sp.Vh.as<double>(), sp.Np, sp.B.as<double>(), sp.Rp, sp.delta, d_t + t0,
+                               std::min(each, count - t0), w, W_out, sp.flag.as<int>() + 1, s);
+  }
   HIPCHECK(hipGetLastError());
-  if (ea) sp.pending.push_back({7, ea, timing_mark(s), (real ? 1.0 : 4.0) * tasks.size() * SPECTRAL_BAND * SPECTRAL_BAND * sp.np});
+  if (ea) sp.pending.push_back({7, ea, timing_mark(s), flops});
 }
 
 struct SigmaInputs {
@@ -1410,12 +1467,7 @@ void validate_sigma_args(int n_occ, int n_basis, const gwc_sigma_args *args,
 size_t predict_sigma_bytes(const ResidentSystem &rs, const gwc_sigma_args *args, size_t batch_bytes) {
   if (batch_bytes == 0) batch_bytes = default_batch_bytes();
   const int nc = std::max(args->n_core, 1), nr = std::max(args->n_real, 1), ni = std::max(args->n_imag, 1);
-  // residue task count bounded without reading the grids: every orbital at
-  // every point (FULL), or the equivalent set (at most every occupied orbital)
-  // per point plus every orbital at eps_n (DECOUPLED)
-  const size_t per_point = args->sym_group ? (size_t)rs.no : 1;
-  const size_t t_real = args->mode == GWC_MODE_FULL ? (size_t)nc * (nr + 1) * rs.nb
-                                                    : (size_t)nc * ((size_t)nr * per_point + rs.nb);
+  const size_t t_real = residue_bound(rs, args);
   const BatchPlan pi = plan_batch(rs, (size_t)ni * nc, rs.nb, batch_bytes);
   BatchPlan pr = plan_batch(rs, t_real, 1, batch_bytes);
   if (args->wac) {
@@ -1427,15 +1479,16 @@ size_t predict_sigma_bytes(const ResidentSystem &rs, const gwc_sigma_args *args,
   const size_t fixed = (size_t)nc * rs.nb * ni * sizeof(double2) + t_real * (sizeof(double2) + sizeof(double)) +
                        (size_t)nc * (nr + 1) * 8 * sizeof(double) + (1 << 20);
   size_t most = std::max(pi.bytes, pr.bytes);
-  if (spectral_route(rs, args, batch_bytes)) most = std::max(most, spectral_sizes(rs, nc).bytes);
+  if (spectral_route(rs, args, batch_bytes)) most = std::max(most, spectral_sizes(rs, nc, t_real, batch_bytes).bytes);
   return most + fixed;
 }
 
 // One evaluation by one of the two routes to W; false when the reduced
-// transition matrix turned out unusable (a panel of dependent columns, a
-// value that is not finite), and the outputs are then to be computed by Pi builds.
+// transition matrix turned out unusable (a panel of dependent columns, a value
+// that is not finite or not exact enough), and the outputs are then to be
+// computed by Pi builds.
 static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const SigmaInputs &in, gwc_sigma_out *out,
-                         hipStream_t s, size_t batch_bytes, bool spectral) {
+                         hipStream_t s, size_t batch_bytes, const SpectralSizes *spectral) {
   CallScope scope;
   const int N = rs.N, nb = rs.nb;
   const int nc = args->n_core, ni = args->n_imag, nr = args->n_real;
@@ -1446,21 +1499,21 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
 
   // the call's lists, sent in one copy
   TaskList tr;
-  std::vector<double> ftask, diag2;
+  std::vector<double> ftask, delta;
   std::vector<int> cj_off, tdec, perm;
   build_residue_tasks(rs, args, in, tr, ftask, cj_off, tdec);
-  if (spectral) spectral_order(rs, perm, diag2);
+  if (spectral) spectral_order(rs, perm, delta);
   Staged lists(s);
   const size_t o_core = lists.add(in.core), o_wi = lists.add(in.wi), o_wwi = lists.add(in.wwi), o_wr = lists.add(in.wr),
                o_vxc = lists.add(in.vxc), o_f = lists.add(ftask), o_cjo = lists.add(cj_off), o_dec = lists.add(tdec),
-               o_perm = lists.add(perm), o_diag2 = lists.add(diag2);
+               o_perm = lists.add(perm), o_delta = lists.add(delta);
   lists.send(s);
   const int *d_core = lists.at<int>(o_core);
   const double *d_wi = lists.at<double>(o_wi), *d_wwi = lists.at<double>(o_wwi), *d_wr = lists.at<double>(o_wr),
                *d_vxc = lists.at<double>(o_vxc);
   std::vector<int> status;
   Spectral spec(s), *sp = spectral ? &spec : nullptr;
-  if (sp) spectral_build(rs, in.core, d_core, lists.at<int>(o_perm), lists.at<double>(o_diag2), *sp, s);
+  if (sp) spectral_build(rs, *spectral, in.core, d_core, lists.at<int>(o_perm), lists.at<double>(o_delta), *sp, s);
 
   // ---- imaginary axis: W_imag[c][m][k]
   DevBuf dWi(s);
@@ -1513,7 +1566,6 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
   int unusable = 0;
   if (sp) {
     launch_nonfinite(dWi.as<double>(), (long long)nc * nb * ni * 2, sp->flag.as<int>() + 1, s);
-    launch_nonfinite(dWr.as<double>(), (long long)tr.size() * 2, sp->flag.as<int>() + 1, s);
     HIPCHECK(hipMemcpyAsync(&unusable, sp->flag.as<int>() + 1, sizeof(int), hipMemcpyDeviceToHost, s));
     if (!rs.unchecked) HIPCHECK(hipStreamSynchronize(s));
     check_finite(rs, s);
@@ -1542,8 +1594,11 @@ static void run_sigma_checked(ResidentSystem &rs, const gwc_sigma_args *args, co
                               gwc_sigma_out *out, hipStream_t s, size_t batch_bytes) {
   const size_t reduction = batch_bytes ? batch_bytes : default_batch_bytes(~size_t(0));
   if (batch_bytes == 0) batch_bytes = default_batch_bytes();
-  if (spectral_route(rs, args, reduction) && run_sigma_by(rs, args, in, out, s, batch_bytes, true)) return;
-  (void)run_sigma_by(rs, args, in, out, s, batch_bytes, false);
+  if (spectral_route(rs, args, reduction)) {
+    const SpectralSizes z = spectral_sizes(rs, args->n_core, residue_bound(rs, args), reduction);
+    if (run_sigma_by(rs, args, in, out, s, batch_bytes, &z)) return;
+  }
+  (void)run_sigma_by(rs, args, in, out, s, batch_bytes, nullptr);
 }
 
 void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *out, hipStream_t s,

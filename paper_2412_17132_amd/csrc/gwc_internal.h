@@ -108,20 +108,22 @@ void launch_nonfinite(const double *x, long long n, int *flag, hipStream_t strea
 
 // Spectral screening (kernels_spectral.hip): C = diag(Delta^2) + V^T V over the
 // n_ov transitions, reduced once to half-bandwidth SPECTRAL_BAND; each W is a
-// banded elimination.  np = n_ov rounded up to the band (pad = np - n_ov decoupled
-// rows in front); A is np x lda with the vectors u in the columns from np on,
-// Rp of them (a multiple of 32, the unused ones zero).
+// banded elimination, that of a residue corrected by the untransformed V.
+// np = n_ov rounded up to the band (pad = np - n_ov decoupled rows in front), Np =
+// N_aux and Rp = the number of pairs (core, m) rounded up to 32; A is np x lda with
+// V^T in the Np columns from np on (the unused ones zero), which becomes (V H)^T.
 constexpr int SPECTRAL_BAND = 32;
 constexpr int SPECTRAL_MAX_SPLITS = 8;
 constexpr int SPECTRAL_MAX_RHS = 16;
+constexpr int SPECTRAL_ROWS = 528;  // values kept of 16 eliminated rows
 struct SpectralTask {
-  double z2_re, z2_im;  // z^2
+  double x, y;  // z
   long long out_base;
   int out_stride, col, nrhs;  // vectors col .. col + nrhs - 1: nrhs <= SPECTRAL_MAX_RHS, 1 off the imaginary axis
 };
 struct SpectralWork {  // doubles unless stated
   double *Q, *Y[2];    // np x SPECTRAL_BAND
-  double *X, *W[2];    // (np + Rp) x SPECTRAL_BAND
+  double *X, *W[2];    // (np + Np) x SPECTRAL_BAND
   double *Xpart;       // SPECTRAL_MAX_SPLITS times that
   double *Bk;          // np x SPECTRAL_BAND: the couplings of the blocks
   double *part;        // max(spectral_gram_parts, spectral_xsum_parts)
@@ -135,14 +137,33 @@ void launch_spectral_operand(const double *M_ov, const double *eps, const int *p
                              int n_virt, int pad, int np, double *V, hipStream_t s);
 void launch_spectral_pairs(const double *M_oo, const double *M_ov, int n_aux, int n_occ, int n_virt,
                            const int *core, int R, int Rp, double *B, hipStream_t s);
-void launch_spectral_matrix(const double *V, int np, const double *Bp, int Rp, int n_aux, const double *diag2,
-                            int pad, double *A, long long lda, hipStream_t s);
-void launch_spectral_reduce(double *A, long long lda, int np, int Rp, const SpectralWork &w, hipStream_t s);
-// band: (np / 16 + 2) x 768; Ut: R x np.
-void launch_spectral_pack(const double *A, long long lda, int np, int R, const double *Bk, double *band,
-                          double *Ut, hipStream_t s);
+// delta: the n_ov transitions, ascending.
+void launch_spectral_matrix(const double *V, int np, int Np, int n_aux, const double *delta, int pad, double *A,
+                            long long lda, hipStream_t s);
+void launch_spectral_reduce(double *A, long long lda, int np, int Np, const SpectralWork &w, hipStream_t s);
+// band: (np / 16 + 2) x 768; Vt = V H: N_aux x np (needed here only); Vh = (V H)^T:
+// np x Np; Ut = the vectors u of the pairs in Bp (N_aux x Rp): Rp x np.
+void launch_spectral_pack(const double *A, long long lda, int np, int Np, int n_aux, const double *Bk, const double *Bp,
+                          int Rp, double *band, double *Vt, double *Vh, double *Ut, hipStream_t s);
+// W of tasks on the imaginary axis.
 void launch_spectral_w(const double *band, const double *Ut, int np, const SpectralTask *tasks, int n_tasks,
-                       bool real, double2 *W_out, hipStream_t s);
+                       double2 *W_out, hipStream_t s);
+struct SpectralResidueWork {
+  double2 *factors;  // T x np / 16 x SPECTRAL_ROWS
+  double *X;         // 2 T x np
+  double *XG;        // np x spectral_columns(T)
+  double *Y;         // Np x spectral_columns(T)
+  double *part;      // spectral_residue_parts
+  double2 *W;        // T
+};
+int spectral_columns(int T);
+size_t spectral_residue_parts(int n_aux, int np, int T);
+// W of T residue tasks; flag |= 1 where the reduction's error is too large for the
+// correction to remove it.
+void launch_spectral_residues(const double *band, const double *Ut, int np, int pad, const double *V, int n_aux,
+                              const double *Vh, int Np, const double *Bp, int Rp, const double *delta,
+                              const SpectralTask *tasks, int T, const SpectralResidueWork &w, double2 *W_out, int *flag,
+                              hipStream_t s);
 
 // Cumulant tail.
 void launch_cumulant_weights(const double *omega_real, const double *im_sigma, int n_real,

@@ -8,11 +8,27 @@
 //        W^c_nm(z) = u^T (z^2 - C)^-1 u,      u = V^T b_nm,
 //
 // so every frequency of a call is a shift of the same real symmetric matrix.
-// C is brought once to block-tridiagonal form by orthogonal transformations
-// that are applied to the vectors u as well; each W is then a banded complex
-// symmetric elimination of order n_ov and half-bandwidth SB = 32 instead of an
-// N_aux x N_aux Pi build (2 N^2 n_ov flops) and a factorisation (4/3 N^3):
-// about 8 32^2 n_ov flops.  The reduction costs 4/3 n_ov^3 flops, once a call.
+// C is brought once to block-tridiagonal form by an orthogonal transformation H
+// that is applied to the rows of V as well (V H, from which u = (V H)^T b_nm);
+// each W is then a banded complex symmetric elimination of order n_ov and
+// half-bandwidth SB = 32 instead of an N_aux x N_aux Pi build (2 N^2 n_ov flops)
+// and a factorisation (4/3 N^3): about 8 32^2 n_ov flops.  The reduction costs
+// 4/3 n_ov^3 + 2 n_ov^2 N_aux flops, once a call.
+//
+// The reduction rounds C by eps |C|, of which the Delta^2 of the core levels are
+// the largest, and a residue W lies within 2 x eta of the poles: by the
+// elimination alone Sigma is off by up to 5e-13 and Im Sigma^dec by 4e-12 of
+// their largest values (n_ov 175 and 1026), 25 to 160 times what the Pi builds
+// give.  So W of a residue is taken from
+//
+//        W = w^T Pi w - y^T y,   w = b + y,   w^T Pi w = sum_ia (V^T w)_ia^2 / (z^2 - Delta_ia^2),
+//
+// which is b^T [(1 - Pi)^-1 - 1] b for y = (1 - Pi)^-1 b - b and stationary there
+// (with 1 - Pi between y and its error twice): y = V x from the band's solution
+// x = (z^2 - T)^-1 u has the reduction's error e, W its square.  Every Delta_ia
+// enters by itself, as in a Pi build, and V is the untransformed one.  The band's
+// own W, off by e to first order, tells how large e is.  On the imaginary axis
+// nothing is near a pole and the elimination's W is as exact as the Pi builds'.
 //
 // Reduction (indices ordered by Delta; SB - n_ov % SB decoupled rows in front,
 // with diagonal elements taken from the Delta^2, make the order a multiple of SB).
@@ -451,14 +467,14 @@ static unsigned triangle_tiles(int nt) { return (unsigned)((nt + 1) / 2) * (unsi
 // out[i][j] = sum_P A[P][i] B[P][j] on MFMA, a square of 16 W columns per wave,
 // four waves a workgroup; the operands are rows of A and B (16 consecutive
 // doubles a quarter wave), read through the L1 a batch of 32 / W rows ahead.
-// SYM: A = B, tiles i <= j, and diag2[i - pad] is added on the diagonal (on the
-// `pad` rows in front, where A is zero, elements spread over diag2: distinct, so
+// SYM: A = B, tiles i <= j, and delta[i - pad]^2 is added on the diagonal (on the
+// `pad` rows in front, where A is zero, elements spread over delta: distinct, so
 // that no eigenvalue becomes SB-fold by them).  Sizes are multiples of 32.  Bound by the matrix cores where W = 4 (half the operand
 // loads a product), which needs many tiles to fill the chip.
 template <bool SYM, int W>
 __global__ void __launch_bounds__(256, W == 4 ? 2 : 4)
 spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__restrict__ B, int ldb,
-                     int M, int N, int K, const double *__restrict__ diag2, int pad,
+                     int M, int N, int K, const double *__restrict__ delta, int pad,
                      double *__restrict__ out, long long ldo) {
   constexpr int WT = 16 * W, TILE = 2 * WT, S = 8 / W;
   int ti, tj;
@@ -523,7 +539,10 @@ spectral_gemm_kernel(const double *__restrict__ A, int lda, const double *__rest
       for (int r = 0; r < 4; ++r) {
         const int i = i0 + 16 * a + 4 * r + lk, j = j0 + 16 * b + li;
         double x = acc[a][b][r];
-        if (SYM && i == j) x += diag2[i >= pad ? i - pad : (int)((long long)i * (M - pad) / SB)];
+        if (SYM && i == j) {
+          const double d = delta[i >= pad ? i - pad : (int)((long long)i * (M - pad) / SB)];
+          x = fma(d, d, x);
+        }
         out[(long long)i * ldo + j] = x;
       }
     }
@@ -1258,17 +1277,20 @@ spectral_band_kernel(const double *__restrict__ A, long long lda, const double *
   o[512] = f;
 }
 
-// u's columns as rows: Ut[r][i] = A[i][c0 + r].  32 x 32 tiles through LDS.
+// out[c][r] = in[r][c] for c < cols and r < rows; zero for rows <= r < rows_out.
+// 32 x 32 tiles through LDS.
 __global__ void __launch_bounds__(256)
-spectral_transpose_kernel(const double *__restrict__ A, long long lda, int np, int R, double *__restrict__ Ut) {
+spectral_transpose_kernel(const double *__restrict__ in, long long ldi, int rows, int cols, double *__restrict__ out,
+                          long long ldo, int rows_out) {
   __shared__ double t[32][33];
-  const int i0 = blockIdx.x * 32, r0 = blockIdx.y * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
 #pragma unroll
-  for (int q = 0; q < 32; q += 8) t[q + y][x] = r0 + x < R ? A[(long long)(i0 + q + y) * lda + r0 + x] : 0.0;
+  for (int q = 0; q < 32; q += 8)
+    t[q + y][x] = r0 + q + y < rows && c0 + x < cols ? in[(long long)(r0 + q + y) * ldi + c0 + x] : 0.0;
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < 32; q += 8)
-    if (r0 + q + y < R) Ut[(long long)(r0 + q + y) * np + i0 + x] = t[x][q + y];
+    if (c0 + q + y < cols && r0 + x < rows_out) out[(long long)(c0 + q + y) * ldo + r0 + x] = t[x][q + y];
 }
 
 // W = u^T (z^2 - C)^-1 u of a task's one to 16 vectors u (one where COMPLEX) by
@@ -1283,6 +1305,12 @@ spectral_transpose_kernel(const double *__restrict__ A, long long lda, int np, i
 // two blocks and their vectors is a product of the eliminated rows, on MFMA
 // (accumulators initialised with the band itself); the layouts change through
 // the wave's LDS.  COMPLEX = false is the imaginary axis (z^2 = -w^2, real).
+// COMPLEX also solves for x = (z^2 - T)^-1 u: the eliminated rows over their pivots
+// go to `factors`, SPECTRAL_ROWS values a step (per row the solved right-hand side
+// and the 32 columns behind the diagonal), and each wave substitutes back from the
+// middle over its own; x's planes go to row blockIdx.x (real parts) and gridDim.x +
+// blockIdx.x of X, the elimination's W to W_out[blockIdx.x].  The way back reads
+// 8.4 KB a step, loaded a step ahead, and takes 15 dependent products of it.
 // Bound by the steps' chains where there are fewer tasks than fill the chip, by
 // instructions beyond that (order 5859, 1029 complex tasks: 5.1 -> 2.6 ms against
 // one wave a task that updated sixteen columns of vectors; 608 real tasks 1.15 ->
@@ -1290,7 +1318,8 @@ spectral_transpose_kernel(const double *__restrict__ A, long long lda, int np, i
 template <bool COMPLEX>
 __global__ void __launch_bounds__(128, COMPLEX ? 2 : 3)
 spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut, int np, int nb16,
-                  const SpectralTask *__restrict__ tasks, double2 *__restrict__ W_out) {
+                  const SpectralTask *__restrict__ tasks, double2 *__restrict__ W_out, double2 *factors,
+                  double *__restrict__ X) {
   constexpr int C2 = COMPLEX ? 2 : 1;
   __shared__ double rows[2][16 * 64 * C2];  // eliminated rows, [t][column]
   __shared__ double2 invs[2][16];           // 1/d_t
@@ -1299,7 +1328,7 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
   const bool up = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double *const row = rows[up];
   double2 *const dinv = invs[up];
-  const double zr = task.z2_re, zi = COMPLEX ? task.z2_im : 0.0;
+  const double zr = (task.x - task.y) * (task.x + task.y), zi = COMPLEX ? 2.0 * task.x * task.y : 0.0;
   const double *u = Ut + (long long)(task.col + (COMPLEX ? 0 : min(li, task.nrhs - 1))) * np;
   const bool urow = li < task.nrhs;
 
@@ -1375,6 +1404,8 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
     if (lk == 0) *reinterpret_cast<double2 *>(buf + (li * 64 + c) * C2) = make_double2(re, im);
   };
   double wr = 0.0, wi = 0.0;
+  // the factors of the wave's p-th block
+  auto factor_of = [&](int p) { return factors + ((long long)blockIdx.x * nb16 + (up ? nb16 - 1 - p : p)) * SPECTRAL_ROWS; };
 
 #pragma unroll 1
   for (int p = 0; p < half + 2; ++p) {
@@ -1394,7 +1425,7 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
         put(rows[0], 16, d4{wr, 0.0, 0.0, 0.0}, d4{wi, 0.0, 0.0, 0.0});  // not a tile: [lk][16 + li]
       }
       __syncthreads();
-      if (up) return;
+      if (up) break;
       d4 o11r, o11i, o22r, o22i;
       shifted_diag(tile_of(false, half, 0), o11r, o11i);
       shifted_diag(tile_of(false, half + 1, 0), o22r, o22i);
@@ -1455,6 +1486,8 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
 #pragma unroll
     for (int t = 0; t < 16; ++t) get(row, t * 64 + lane, mr[t], mi[t]);
     wave_sync();
+    double2 *const fac = COMPLEX ? factor_of(p) + (lane == 48 ? 0 : lane) : nullptr;
+    const int keep_step = lane == 48 ? 33 : 32;  // the right-hand side's lane, or 32 t + lane
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
       const double dr = bcast(mr[t], t);
@@ -1468,6 +1501,7 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
         lm = mr[t] * ii + mi[t] * ir;
         wr += mr[t] * lr - mi[t] * lm;
         wi += mr[t] * lm + mi[t] * lr;
+        if (lane == 48 || (unsigned)(lane - t - 1) < 32u) fac[t * keep_step] = make_double2(lr, lm);
 #pragma unroll
         for (int i = t + 1; i < 16; ++i) {
           const double a = bcast(lr, i), b = bcast(lm, i);
@@ -1546,8 +1580,172 @@ spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut
     }
     f = -nf;
   }
-  if (lane >= 48 && lane - 48 < task.nrhs)
-    W_out[task.out_base + (long long)(lane - 48) * task.out_stride] = make_double2(wr, wi);
+  if (!COMPLEX) {
+    if (!up && lane >= 48 && lane - 48 < task.nrhs)
+      W_out[task.out_base + (long long)(lane - 48) * task.out_stride] = make_double2(wr, wi);
+    return;
+  }
+  if (!up && lane == 48) W_out[blockIdx.x] = make_double2(wr, wi);
+  // back: window[16 ..] holds x of the two blocks behind the one being solved
+  __shared__ d2 windows[2][48];
+  d2 *const window = windows[up], *const rowz = reinterpret_cast<d2 *>(row);
+  constexpr int LOADS = (SPECTRAL_ROWS + 63) / 64;
+  static_assert(SPECTRAL_ROWS == 16 * 33 && LOADS == 9, "16 rows of 33; the ninth load takes the last 16");
+  auto load = [&](int p, d2(&v)[LOADS]) {
+    const d2 *f = reinterpret_cast<const d2 *>(factor_of(p));
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) v[q] = f[min(64 * q + lane, SPECTRAL_ROWS - 1)];
+  };
+  // x of a block, element li in every lane
+  auto solve = [&](const d2(&v)[LOADS], double &xr, double &xi) {
+#pragma unroll
+    for (int q = 0; q < LOADS - 1; ++q) rowz[64 * q + lane] = v[q];
+    if (lane < 16) rowz[64 * (LOADS - 1) + lane] = v[LOADS - 1];
+    wave_sync();
+    const d2 *r = rowz + 33 * li;
+    const d2 y = r[0];
+    double sr = lk == 0 ? y.x : 0.0, si = lk == 0 ? y.y : 0.0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int k = 1 + lk + 4 * c;
+      const d2 m = r[k], x = window[li + k];  // zero inside the block
+      sr = fma(m.y, x.y, fma(-m.x, x.x, sr));
+      si = fma(-m.y, x.x, fma(-m.x, x.y, si));
+    }
+    d2 m[16];
+#pragma unroll
+    for (int t = 1; t < 16; ++t) {
+      m[t] = r[max(t - li, 0)];
+      m[t] *= li < t ? 1.0 : 0.0;
+    }
+    sr = row_sum(sr);
+    si = row_sum(si);
+    for_each_index<15>([&](auto ic) {
+      constexpr int t = 15 - decltype(ic)::value;
+      const double a = row_bcast<t>(sr), b = row_bcast<t>(si);
+      sr = fma(m[t].y, b, fma(-m[t].x, a, sr));
+      si = fma(-m[t].y, a, fma(-m[t].x, b, si));
+    });
+    xr = sr;
+    xi = si;
+    wave_sync();
+  };
+  auto keep = [&](int p, double xr, double xi) {
+    const int at = up ? np - 1 - 16 * p - li : 16 * p + li;
+    if (lk < 2) X[((long long)blockIdx.x + (lk ? gridDim.x : 0)) * np + at] = lk ? xi : xr;
+    if (lk == 0) {
+      window[32 + li] = window[16 + li];
+      window[16 + li] = d2{xr, xi};
+    }
+    wave_sync();
+  };
+  d2 v[LOADS], next[LOADS];
+  double xr, xi;
+  if (!up) {
+    if (lane < 48) window[lane] = d2{0.0, 0.0};
+    load(half + 1, v);
+    load(half, next);
+    wave_sync();
+    solve(v, xr, xi);
+    keep(half + 1, xr, xi);
+    if (lk == 0) windows[1][16 + 15 - li] = d2{xr, xi};  // the upward wave's order
+    solve(next, xr, xi);
+    keep(half, xr, xi);
+    if (lk == 0) {
+      windows[1][32 + 15 - li] = d2{xr, xi};
+      windows[1][li] = d2{0.0, 0.0};
+    }
+  }
+  if (half > 0) load(half - 1, v);
+  __syncthreads();
+#pragma unroll 1
+  for (int p = half - 1; p >= 0; --p) {
+    if (p > 0) load(p - 1, next);
+    solve(v, xr, xi);
+    keep(p, xr, xi);
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) v[q] = next[q];
+  }
+}
+
+// w = b + y in the place of y (real parts of the T tasks, then imaginary ones),
+// and by blocks of YROWS rows the sums of y^2 (complex) and of b^2.
+constexpr int YROWS = 32, GROWS = 64;
+__global__ void __launch_bounds__(64)
+spectral_shift_kernel(double *__restrict__ Y, int ldy, int n_aux, const double *__restrict__ B, int ldb,
+                      const SpectralTask *__restrict__ tasks, int T, double *__restrict__ part) {
+  const int t = blockIdx.x * 64 + threadIdx.x;
+  if (t >= T) return;
+  const double *b = B + tasks[t].col;
+  const int P0 = blockIdx.y * YROWS, P1 = min(n_aux, P0 + YROWS);
+  double sr = 0.0, si = 0.0, sb = 0.0;
+#pragma unroll 8
+  for (int P = P0; P < P1; ++P) {
+    double *y = Y + (long long)P * ldy + t;
+    const double yr = y[0], yi = y[T], bp = b[(long long)P * ldb];
+    sr = fma(yr, yr, fma(-yi, yi, sr));
+    si = fma(2.0 * yr, yi, si);
+    sb = fma(bp, bp, sb);
+    y[0] = bp + yr;
+  }
+  double *o = part + (long long)blockIdx.y * 3 * T + t;
+  o[0] = sr;
+  o[T] = si;
+  o[2 * T] = sb;
+}
+
+// By blocks of GROWS transitions the sums of g^2 / (z^2 - Delta^2), g = V^T w.
+__global__ void __launch_bounds__(64)
+spectral_poles_kernel(const double *__restrict__ G, int ldg, int np, int pad, const double *__restrict__ delta,
+                      const SpectralTask *__restrict__ tasks, int T, double *__restrict__ part) {
+  const int t = blockIdx.x * 64 + threadIdx.x;
+  if (t >= T) return;
+  const double x = tasks[t].x, y = tasks[t].y, y2 = y * y, im = 2.0 * x * y;
+  const int k0 = max(pad, (int)blockIdx.y * GROWS), k1 = min(np, ((int)blockIdx.y + 1) * GROWS);
+  double sr = 0.0, si = 0.0;
+#pragma unroll 4
+  for (int k = k0; k < k1; ++k) {
+    const double d = delta[k - pad], re = (x - d) * (x + d) - y2, q = 1.0 / fma(re, re, im * im);
+    const double gr = G[(long long)k * ldg + t], gi = G[(long long)k * ldg + T + t];
+    const double ar = fma(gr, gr, -gi * gi) * q, ai = 2.0 * gr * gi * q;
+    sr = fma(ar, re, fma(ai, im, sr));
+    si = fma(ai, re, fma(-ar, im, si));
+  }
+  double *o = part + (long long)blockIdx.y * 2 * T + t;
+  o[0] = sr;
+  o[T] = si;
+}
+
+// W = w^T Pi w - y^T y.  The band's own W is off by the first-order error e of
+// the reduction, this one by its square times |1 - Pi| (up to some hundreds next
+// to a pole): where they differ by more than 1e-8, that may be above rounding,
+// and the flag sends the call to the Pi builds.  (Measured differences: up to
+// 1e-11.  The second term is rounding of W where it cancels against b^T b.)
+__global__ void __launch_bounds__(64)
+spectral_finish_kernel(const double *__restrict__ part_y, int ny, const double *__restrict__ part_g, int ng,
+                       const double2 *__restrict__ W_band, const SpectralTask *__restrict__ tasks, int T,
+                       double2 *__restrict__ W_out, int *__restrict__ flag) {
+  const int t = blockIdx.x * 64 + threadIdx.x;
+  if (t >= T) return;
+  double yr = 0.0, yi = 0.0, bb = 0.0, gr = 0.0, gi = 0.0;
+#pragma unroll 4
+  for (int k = 0; k < ny; ++k) {
+    const double *o = part_y + (long long)k * 3 * T + t;
+    yr += o[0];
+    yi += o[T];
+    bb += o[2 * T];
+  }
+#pragma unroll 8
+  for (int k = 0; k < ng; ++k) {
+    const double *o = part_g + (long long)k * 2 * T + t;
+    gr += o[0];
+    gi += o[T];
+  }
+  const double wr = gr - yr, wi = gi - yi;
+  const double2 w0 = W_band[t];
+  const double off = fmax(fabs(wr - w0.x), fabs(wi - w0.y));
+  if (!(off <= 1e-8 * fmax(fabs(wr), fabs(wi)) + 1e-13 * bb)) atomicOr(flag, 1);
+  W_out[tasks[t].out_base] = make_double2(wr, wi);
 }
 
 size_t spectral_small_bytes() { return sizeof(PanelSmall); }
@@ -1568,17 +1766,32 @@ void launch_spectral_pairs(const double *M_oo, const double *M_ov, int n_aux, in
   spectral_pairs_kernel<<<grid, 256, 0, s>>>(M_oo, M_ov, n_aux, n_occ, n_virt, core, R, Rp, B);
 }
 
-void launch_spectral_matrix(const double *V, int np, const double *Bp, int Rp, int n_aux, const double *diag2,
-                            int pad, double *A, long long lda, hipStream_t s) {
+static void transpose(const double *in, long long ldi, int rows, int cols, double *out, long long ldo, int rows_out,
+                      hipStream_t s) {
+  spectral_transpose_kernel<<<dim3((rows_out + 31) / 32, (cols + 31) / 32), 256, 0, s>>>(in, ldi, rows, cols, out, ldo, rows_out);
+}
+
+// out[i][j] = sum_P A[P][i] B[P][j]: 128 x 128 tiles where they are twice what
+// runs at once (512), else 64 x 64.
+static void product(const double *A, int lda, const double *B, int ldb, int M, int N, int K, double *out, long long ldo,
+                    hipStream_t s) {
+  auto tiles = [&](int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
+  if (tiles(2 * UT) >= 512)
+    spectral_gemm_kernel<false, 4><<<tiles(2 * UT), 256, 0, s>>>(A, lda, B, ldb, M, N, K, nullptr, 0, out, ldo);
+  else
+    spectral_gemm_kernel<false, 2><<<tiles(UT), 256, 0, s>>>(A, lda, B, ldb, M, N, K, nullptr, 0, out, ldo);
+}
+
+void launch_spectral_matrix(const double *V, int np, int Np, int n_aux, const double *delta, int pad, double *A,
+                            long long lda, hipStream_t s) {
   const int nt = (np + UT - 1) / UT, nt2 = (np + 2 * UT - 1) / (2 * UT);
   // 128 x 128 tiles from where they are twice what runs at once (512): at order
   // 16544 15.5 -> 11.0 ms, at 5888 1.03 -> 0.85 ms, at 1056 0.053 against 0.079.
   if (np >= 4096)
-    spectral_gemm_kernel<true, 4><<<triangle_tiles(nt2), 256, 0, s>>>(V, np, V, np, np, np, n_aux, diag2, pad, A, lda);
+    spectral_gemm_kernel<true, 4><<<triangle_tiles(nt2), 256, 0, s>>>(V, np, V, np, np, np, n_aux, delta, pad, A, lda);
   else
-    spectral_gemm_kernel<true, 2><<<triangle_tiles(nt), 256, 0, s>>>(V, np, V, np, np, np, n_aux, diag2, pad, A, lda);
-  spectral_gemm_kernel<false, 2><<<nt * ((Rp + UT - 1) / UT), 256, 0, s>>>(V, np, Bp, Rp, np, Rp, n_aux, nullptr, 0,
-                                                                          A + np, lda);
+    spectral_gemm_kernel<true, 2><<<triangle_tiles(nt), 256, 0, s>>>(V, np, V, np, np, np, n_aux, delta, pad, A, lda);
+  transpose(V, np, n_aux, np, A + np, lda, Np, s);
 }
 
 void launch_spectral_reduce(double *A, long long lda, int np, int Rp, const SpectralWork &w, hipStream_t s) {
@@ -1629,16 +1842,38 @@ void launch_spectral_reduce(double *A, long long lda, int np, int Rp, const Spec
   }
 }
 
-void launch_spectral_pack(const double *A, long long lda, int np, int R, const double *Bk, double *band, double *Ut,
-                          hipStream_t s) {
+void launch_spectral_pack(const double *A, long long lda, int np, int Np, int n_aux, const double *Bk, const double *Bp,
+                          int Rp, double *band, double *Vt, double *Vh, double *Ut, hipStream_t s) {
   spectral_band_kernel<<<np / 16 + 2, 256, 0, s>>>(A, lda, Bk, np / SB, band);
-  spectral_transpose_kernel<<<dim3(np / 32, (R + 31) / 32), 256, 0, s>>>(A + np, lda, np, R, Ut);
+  transpose(A + np, lda, np, n_aux, Vt, np, np, s);
+  transpose(Vt, np, n_aux, np, Vh, Np, Np, s);
+  product(Bp, Rp, Vt, np, Rp, np, n_aux, Ut, np, s);
 }
 
 void launch_spectral_w(const double *band, const double *Ut, int np, const SpectralTask *tasks, int n_tasks,
-                       bool real, double2 *W_out, hipStream_t s) {
-  if (real) spectral_w_kernel<false><<<n_tasks, 128, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
-  else spectral_w_kernel<true><<<n_tasks, 128, 0, s>>>(band, Ut, np, np / 16, tasks, W_out);
+                       double2 *W_out, hipStream_t s) {
+  spectral_w_kernel<false><<<n_tasks, 128, 0, s>>>(band, Ut, np, np / 16, tasks, W_out, nullptr, nullptr);
+}
+
+int spectral_columns(int T) { return (2 * T + SB - 1) / SB * SB; }
+size_t spectral_residue_parts(int n_aux, int np, int T) {
+  return (size_t)T * (3 * ((n_aux + YROWS - 1) / YROWS) + 2 * ((np + GROWS - 1) / GROWS));
+}
+
+void launch_spectral_residues(const double *band, const double *Ut, int np, int pad, const double *V, int n_aux,
+                              const double *Vh, int Np, const double *Bp, int Rp, const double *delta,
+                              const SpectralTask *tasks, int T, const SpectralResidueWork &w, double2 *W_out, int *flag,
+                              hipStream_t s) {
+  const int C = spectral_columns(T), tb = (T + 63) / 64;
+  const int ny = (n_aux + YROWS - 1) / YROWS, ng = (np + GROWS - 1) / GROWS;
+  double *part_y = w.part, *part_g = part_y + (size_t)3 * ny * T;
+  spectral_w_kernel<true><<<T, 128, 0, s>>>(band, Ut, np, np / 16, tasks, w.W, w.factors, w.X);
+  transpose(w.X, np, 2 * T, np, w.XG, C, C, s);
+  product(Vh, Np, w.XG, C, Np, C, np, w.Y, C, s);  // y = V H x
+  spectral_shift_kernel<<<dim3(tb, ny), 64, 0, s>>>(w.Y, C, n_aux, Bp, Rp, tasks, T, part_y);
+  product(V, np, w.Y, C, np, C, n_aux, w.XG, C, s);  // g = V^T w
+  spectral_poles_kernel<<<dim3(tb, ng), 64, 0, s>>>(w.XG, C, np, pad, delta, tasks, T, part_g);
+  spectral_finish_kernel<<<tb, 64, 0, s>>>(part_y, ny, part_g, ng, w.W, tasks, T, W_out, flag);
 }
 
 }  // namespace gwc

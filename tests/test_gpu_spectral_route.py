@@ -13,6 +13,7 @@ import pytest
 
 import paper_2412_17132_amd as gwc
 from oracle import sigma as OS
+from extended import dyadic_system, im_sigma_dec
 from workloads import system_from_config
 from workloads.configs import small_config
 
@@ -114,3 +115,20 @@ def test_dependent_panels_run_the_builds_after_the_reduction(monkeypatch):
     for k in ("sigma_c", "im_sigma_dec", "sigma_c_eps", "sigma_x", "e_qp"):
         assert torch.equal(got[k], want[k]), k
     _matches_oracle(s, got, "full")
+
+
+@pytest.mark.parametrize("route", ["spectral", "ldlt"])
+@pytest.mark.parametrize("shape", [(5, 35, 48, 60), (9, 63, 80, 24), (3, 21, 30, 30)], ids=["ov175", "ov567", "ov63"])
+def test_residues_are_as_exact_as_the_arithmetic_allows(shape, route, monkeypatch):
+    """Im Sigma^dec next to the poles against long double, by either route within 8
+    eps of the terms of w^T Pi w (extended.py): each takes a few roundings.  The
+    reduction rounds the whole matrix by eps max(Delta^2): the band's own W is off
+    by 35 to 120 eps of them."""
+    n_occ, n_virt, n_aux, n_real = shape
+    s = dyadic_system(n_occ, n_virt, n_aux, n_real)
+    want, bound = im_sigma_dec(s)
+    print(f"case n_ov {n_occ * n_virt} {route}", flush=True)
+    out, ran = _run(s, "decoupled", route, monkeypatch)
+    assert (ran[0] > 0, ran[1] > 0) == (route == "spectral", route == "ldlt"), ran
+    got = out["im_sigma_dec"][0].cpu().numpy()
+    assert np.max(np.abs(got - want) / bound) <= 8 * np.finfo(float).eps
