@@ -982,22 +982,23 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   if (std::numeric_limits<double>::epsilon() * max_d * max_d > 1e-10 * 2.0 * min_d * args->eta) return false;
   if (forced) return true;
   // The times of the two routes for ONE core state, so that a call for several
-  // cores and one for each take the same route.  Reduction: 68 us of dependent
-  // steps a panel and n^3 at 0.037 ps (measured 2.2 ms at n_ov = 1026, 19 ms at
-  // 5859, 203 ms at 16524).  Pi builds: 120 us of dependent factorisation steps
-  // per 64 rows of N and 2 N^2 n + 4/3 N^3 flops a frequency at 58 TFLOP/s, less
-  // on small matrices (measured 0.5 ms at N = 160, n_ov = 175 with 629
-  // frequencies and 1.0 ms at 400, 651 with 40; 0.28 ms a frequency at 1200, 5859).
-  // Up to n_ov = 320, where the two differ by 0.1 ms, FULL and DECOUPLED count
-  // the same frequencies, so that both modes give the same last digits.
+  // cores and one for each take the same route.  Reduction: 77 us of dependent
+  // steps a panel, n^3 at 0.046 ps and the launches of the correction (measured
+  // 0.80 ms at n_ov = 175, 3.0 ms at 1026, 24 ms at 5859, 71 ms at 10071, hardly
+  // more with 10 times the frequencies).  Pi builds: 120 us of dependent
+  // factorisation steps per 64 rows of N and 2 N^2 n + 4/3 N^3 flops a frequency
+  // at 60 TFLOP/s, less on small matrices, 0.4 of that on the imaginary axis
+  // (measured, DECOUPLED with 9 and with 100 points: 0.57 and 0.61 ms at N = 160,
+  // n_ov = 175; 1.6 and 2.9 ms at 491, 1026; 17 and 44 ms at 1200, 5859).
   const double n = rs.n_ov, N = rs.N;
-  const bool every = args->mode == GWC_MODE_FULL || rs.n_ov <= 320;
-  const double tasks = args->n_imag + (double)args->n_real * (every ? rs.no : 1) + rs.no;
-  const double panels = std::ceil(n / SPECTRAL_BAND);
-  const double t_reduce = 68e-6 * panels + 3.7e-14 * n * n * n;
-  const double t_build = 120e-6 * std::ceil(N / 64) +
-                         tasks * (2.0 * N * N * n + 4.0 / 3.0 * N * N * N) / (58e12 * N / (N + 150.0));
-  return t_reduce < t_build;
+  auto t_build = [&](double residues) {
+    return 120e-6 * std::ceil(N / 64) + (0.4 * args->n_imag + residues + rs.no) * (2.0 * N * N * n + 4.0 / 3.0 * N * N * N) /
+                                            (60e12 * N / (N + 150.0));
+  };
+  const double t_reduce = 1e-4 + 77e-6 * std::ceil(n / SPECTRAL_BAND) + 4.6e-14 * n * n * n;
+  // One route for both modes, so that they give the same digits: the reduction
+  // where FULL gains by it, unless DECOUPLED lost more than half its time.
+  return t_reduce < std::min(t_build((double)args->n_real * rs.no), 1.5 * t_build(args->n_real));
 }
 
 // Transitions by ascending Delta, and Delta in that order.

@@ -132,3 +132,17 @@ def test_residues_are_as_exact_as_the_arithmetic_allows(shape, route, monkeypatc
     assert (ran[0] > 0, ran[1] > 0) == (route == "spectral", route == "ldlt"), ran
     got = out["im_sigma_dec"][0].cpu().numpy()
     assert np.max(np.abs(got - want) / bound) <= 8 * np.finfo(float).eps
+
+
+@pytest.mark.parametrize("case", [(4, 40, 160, 10), (5, 35, 160, 120), (8, 76, 330, 20), (8, 76, 330, 100), (9, 114, 491, 9),
+                                  (10, 110, 480, 61)], ids=lambda c: f"ov{c[0] * c[1]}_points{c[3]}")
+def test_both_modes_take_one_route(case, monkeypatch):
+    """FULL and DECOUPLED share Sigma^c(eps_n) and E_QP, and so their last digits."""
+    n_occ, n_virt, n_aux, n_real = case
+    s = system_from_config(small_config(n_occ=n_occ, n_virt=n_virt, n_aux=n_aux, n_core=1, n_imag=24, n_real=n_real, seed=n_real))
+    print(f"case n_ov {n_occ * n_virt}, {n_real} points", flush=True)
+    full, ran_full = _run(s, "full", None, monkeypatch)
+    dec, ran_dec = _run(s, "decoupled", None, monkeypatch)
+    assert ran_full[0] == ran_dec[0]
+    for k in ("im_sigma_dec", "sigma_c_eps", "sigma_x", "e_qp"):
+        assert torch.equal(full[k], dec[k]), k
