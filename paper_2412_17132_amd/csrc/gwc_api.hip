@@ -501,20 +501,33 @@ bool all_finite(const std::vector<double> &v) {
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// The workspace of one call: the environment's, else `most` (for a batch of
-// matrices, whose size gains nothing beyond that), and at most half of what is free.
-size_t default_batch_bytes(size_t most = size_t(48) << 30) {
-  size_t budget = most;
+size_t batch_bytes_or(size_t otherwise) {
   if (const char *e = std::getenv("GWC_BATCH_BYTES")) {
     const long long v = std::atoll(e);
-    if (v > 0) budget = (size_t)v;
+    if (v > 0) return (size_t)v;
   }
+  return otherwise;
+}
+
+// The matrices of one call's batches: the environment's, else 48 GiB (larger ones
+// gain nothing), and at most half of what is free.
+size_t default_batch_bytes() {
+  size_t budget = batch_bytes_or(size_t(48) << 30);
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b > 0)
     budget = std::min(budget, (free_b + device_cache().idle_bytes()) / 2);  // idle cached blocks count as free
   else
     (void)hipGetLastError();
   return budget;
+}
+
+// The reduced transition matrix of one call: the environment's, else half the
+// device's memory, whatever of it is free at the moment: the route, and with it
+// the last digits, do not depend on what else holds memory.
+size_t default_reduction_bytes() {
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) (void)hipGetLastError();
+  return batch_bytes_or(total_b / 2);
 }
 
 int max_batch_tasks() {
@@ -1593,7 +1606,7 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
 
 static void run_sigma_checked(ResidentSystem &rs, const gwc_sigma_args *args, const SigmaInputs &in,
                               gwc_sigma_out *out, hipStream_t s, size_t batch_bytes) {
-  const size_t reduction = batch_bytes ? batch_bytes : default_batch_bytes(~size_t(0));
+  const size_t reduction = batch_bytes ? batch_bytes : default_reduction_bytes();
   if (batch_bytes == 0) batch_bytes = default_batch_bytes();
   if (spectral_route(rs, args, reduction)) {
     const SpectralSizes z = spectral_sizes(rs, args->n_core, residue_bound(rs, args), reduction);
