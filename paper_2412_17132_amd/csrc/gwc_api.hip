@@ -22,6 +22,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <exception>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -433,6 +434,17 @@ class HostFetch {
   GatherArgs g_;
   void *dst_[GatherArgs::MAX];
   long long total_ = 0, most_ = 0;
+};
+
+// Waits for the stream when an exception leaves the scope: declared behind host
+// arrays whose copies may still be under way.
+struct SyncOnUnwind {
+  hipStream_t s;
+  const int before = std::uncaught_exceptions();
+  explicit SyncOnUnwind(hipStream_t stream) : s(stream) {}
+  ~SyncOnUnwind() {
+    if (std::uncaught_exceptions() > before && hipStreamSynchronize(s) != hipSuccess) (void)hipGetLastError();
+  }
 };
 
 // Host arrays of a call sent to the device in one copy.
@@ -1527,6 +1539,7 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
                *d_vxc = lists.at<double>(o_vxc);
   std::vector<int> status;
   Spectral spec(s), *sp = spectral ? &spec : nullptr;
+  SyncOnUnwind unwind(s);
   if (sp) spectral_build(rs, *spectral, in.core, d_core, lists.at<int>(o_perm), lists.at<double>(o_delta), *sp, s);
 
   // ---- imaginary axis: W_imag[c][m][k]
@@ -1610,7 +1623,12 @@ static void run_sigma_checked(ResidentSystem &rs, const gwc_sigma_args *args, co
   if (batch_bytes == 0) batch_bytes = default_batch_bytes();
   if (spectral_route(rs, args, reduction)) {
     const SpectralSizes z = spectral_sizes(rs, args->n_core, residue_bound(rs, args), reduction);
-    if (run_sigma_by(rs, args, in, out, s, batch_bytes, &z)) return;
+    // no room beside what else holds memory: the Pi builds take smaller batches
+    try {
+      if (run_sigma_by(rs, args, in, out, s, batch_bytes, &z)) return;
+    } catch (const GwcError &e) {
+      if (e.code != GWC_ERR_OUT_OF_MEMORY) throw;
+    }
   }
   (void)run_sigma_by(rs, args, in, out, s, batch_bytes, nullptr);
 }

@@ -25,3 +25,8 @@ def test_route_does_not_depend_on_free_memory():
     """1.3 GB of reduction (order 12000) with 2 GB free, and with all of it."""
     for hold in (False, True):
         assert _run(2000, 24, 500, hold) == dict(reduced=1, built=0, same=0, close=1), hold
+
+
+def test_no_room_for_the_reduction():
+    """3.2 GB of matrix (order 20000) with 2 GB free: the call goes by the Pi builds."""
+    assert _run(2000, 20, 1000, True) == dict(reduced=0, built=2, same=1, close=1)
