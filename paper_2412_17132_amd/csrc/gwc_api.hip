@@ -1394,8 +1394,9 @@ void run_wac(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_args *
 
 // Newton solution of the quasiparticle equation (Eq. quasiparticle_equation)
 // for every core: per iteration Sigma^c at E - h, E, E + h by contour
-// deformation on the cores still iterating, then the update on the host.
-void run_qp_newton(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_args *args,
+// deformation on the cores still iterating, then the update on the host.  False
+// when the reduced transition matrix is no use at these energies.
+bool run_qp_newton(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_args *args,
                    const SigmaInputs &in, const double2 *d_Wimag, const double *d_wi,
                    const double *d_wwi, const std::vector<double> &sx, std::vector<double> &E,
                    std::vector<int> &iters, std::vector<int> &status, hipStream_t s,
@@ -1465,7 +1466,10 @@ void run_qp_newton(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_
     HIPCHECK(hipGetLastError());
     std::vector<double> sig((size_t)na * 6);
     HIPCHECK(hipMemcpyAsync(sig.data(), dsig.p, sig.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+    int unusable = 0;
+    if (sp) HIPCHECK(hipMemcpyAsync(&unusable, sp->flag.as<int>() + 1, sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
+    if (unusable) return false;
     for (int k = 0; k < na; ++k) {
       const int c = idx[k];
       const double en = rs.eps[in.core[c]];
@@ -1481,6 +1485,7 @@ void run_qp_newton(ResidentSystem &rs, const MixedOperands *mx, const gwc_sigma_
       }
     }
   }
+  return true;
 }
 
 }  // namespace
@@ -1606,9 +1611,10 @@ static bool run_sigma_by(ResidentSystem &rs, const gwc_sigma_args *args, const S
     std::vector<double> sx(nc);
     HIPCHECK(hipMemcpyAsync(sx.data(), dsx, nc * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
-    run_qp_newton(rs, mx, args, in, dWi.as<double2>(), d_wi, d_wwi, sx, e_newton, qp_it, status, s,
-                  batch_bytes, sp);
+    const bool usable = run_qp_newton(rs, mx, args, in, dWi.as<double2>(), d_wi, d_wwi, sx, e_newton, qp_it, status, s,
+                                      batch_bytes, sp);
     if (sp) timing_resolve(sp->pending);
+    if (!usable) return false;
     copy_out(out->e_qp_newton, e_newton.data(), (size_t)nc * sizeof(double), s);
     copy_out(out->qp_iterations, qp_it.data(), (size_t)nc * sizeof(int), s);
   }

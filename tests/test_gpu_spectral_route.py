@@ -22,7 +22,7 @@ torch = pytest.importorskip("torch")
 TOL = 1e-9
 
 
-def _run(s, mode, route, monkeypatch):
+def _run(s, mode, route, monkeypatch, **more):
     """The outputs, and the launches of (reduction, Pi builds)."""
     if route is None:
         monkeypatch.delenv("GWC_FACTORIZATION", raising=False)
@@ -32,7 +32,7 @@ def _run(s, mode, route, monkeypatch):
     gwc.timing_enable(True)
     try:
         out = gwc.gwc_sigma_core(d["eps"], d["occ"], d["M_oo"], d["M_ov"], d["core_idx"], d["omega_imag"],
-                                 d["w_imag"], d["omega_real"], d["eta"], mode=mode)
+                                 d["w_imag"], d["omega_real"], d["eta"], mode=mode, **more)
         torch.cuda.synchronize()
         ran = gwc.timing_get("spectral_reduce")["launches"], gwc.timing_get("pi_build_f64")["launches"]
     finally:
@@ -146,3 +146,19 @@ def test_both_modes_take_one_route(case, monkeypatch):
     assert ran_full[0] == ran_dec[0]
     for k in ("im_sigma_dec", "sigma_c_eps", "sigma_x", "e_qp"):
         assert torch.equal(full[k], dec[k]), k
+
+
+def test_newton_steps_out_of_the_reductions_range(monkeypatch):
+    """A v_xc of 1e80 Ha throws Newton's second step to where |z|^4 overflows: the
+    elimination's pivots have no reciprocal there, and the call goes by the Pi
+    builds (whose chi is 0)."""
+    s = system_from_config(small_config(n_occ=5, n_virt=35, n_aux=60, n_core=1, n_real=4, seed=8))
+    more = dict(vxc=torch.full((1,), 1e80, dtype=torch.float64, device="cuda:0"), qp=dict(max_iter=4, tol=1e68, step=1e72))
+    print("case Newton at -1e80", flush=True)
+    want, ran = _run(s, "decoupled", "ldlt", monkeypatch, **more)
+    assert ran[0] == 0
+    got, ran = _run(s, "decoupled", "spectral", monkeypatch, **more)
+    assert ran[0] == 1
+    assert torch.isfinite(want["e_qp_newton"]).all()
+    for k in ("e_qp_newton", "qp_iterations", "e_qp", "im_sigma_dec"):
+        assert torch.equal(got[k], want[k]), k
