@@ -992,8 +992,12 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   const char *env = std::getenv("GWC_FACTORIZATION");
   const bool forced = env && std::string(env) == "spectral";
   if (env && !forced) return false;
-  const SpectralSizes z = spectral_sizes(rs, args->n_core, residue_bound(rs, args), batch_bytes);
-  if (z.batch < 1 || (long long)z.np + z.Np > (1 << 20) || z.R > (1 << 20)) return false;
+  // what the Pi builds refuse (an order, or one matrix of the imaginary axis beyond
+  // the budget) stays refused, by them
+  if (rs.N + rs.nb > lu_max_order() || plan_batch(rs, 1, rs.nb, batch_bytes).F < 1) return false;
+  constexpr long long MOST = 1 << 20;
+  if ((long long)rs.n_ov + rs.N + 2 * SPECTRAL_BAND > MOST || (long long)args->n_core * rs.nb > MOST) return false;
+  if (spectral_sizes(rs, args->n_core, residue_bound(rs, args), batch_bytes).batch < 1) return false;
   // rounding of the reduction, eps max(Delta^2), against the distance of z^2
   // from the poles, 2 x eta with x at least the smallest transition
   double max_d = 0.0, min_d = std::numeric_limits<double>::infinity();

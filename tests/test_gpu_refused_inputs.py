@@ -1,5 +1,6 @@
-"""A call that refuses its coefficients leaves every output as it was, whichever
-route to W its sizes take and wherever the outputs are."""
+"""What a call refuses: bad coefficients, with every output left as it was,
+whichever route to W the sizes take and wherever the outputs are; and the orders
+and budgets that the Pi builds refuse, also where the reduction would fit."""
 import numpy as np
 import pytest
 
@@ -30,3 +31,27 @@ def test_outputs_untouched(outputs, route, monkeypatch):
     assert e.value.status == -4
     for k, v in out.items():
         assert bool((v == 7.25).all()), k
+
+
+def _status(s):
+    d = gwc.to_device(s, torch.device("cuda:0"))
+    with pytest.raises(gwc.GwcError) as e:
+        gwc.gwc_sigma_core(d["eps"], d["occ"], d["M_oo"], d["M_ov"], d["core_idx"], d["omega_imag"], d["w_imag"],
+                           d["omega_real"], d["eta"], mode="decoupled")
+    return e.value.status
+
+
+def test_order_beyond_the_factorisations(monkeypatch):
+    monkeypatch.delenv("GWC_FACTORIZATION", raising=False)
+    s = system_from_config(small_config(n_occ=2, n_virt=30, n_aux=12270, n_core=1, n_real=4, seed=5))
+    print("case order 12302", flush=True)
+    assert _status(s) == -8
+
+
+def test_budget_below_one_matrix(monkeypatch):
+    """8 MB: the reduction would take 5 MB, one bordered matrix of order 1018 takes 17 MB."""
+    monkeypatch.delenv("GWC_FACTORIZATION", raising=False)
+    monkeypatch.setenv("GWC_BATCH_BYTES", "8000000")
+    s = system_from_config(small_config(n_occ=2, n_virt=16, n_aux=1000, n_core=1, n_real=4, seed=5))
+    print("case 8 MB", flush=True)
+    assert _status(s) == -6
