@@ -134,6 +134,18 @@ def test_residues_are_as_exact_as_the_arithmetic_allows(shape, route, monkeypatc
     assert np.max(np.abs(got - want) / bound) <= 8 * np.finfo(float).eps
 
 
+@pytest.mark.parametrize("factor", [30.0, 300.0])
+def test_large_coefficients(factor, monkeypatch):
+    """V^T V up to 1e7 |Delta^2|: the band's own W is off by 30 to 70 eps of the terms."""
+    s = dyadic_system()
+    s.M_ov = s.M_ov * factor
+    want, bound = im_sigma_dec(s)
+    print(f"case coefficients times {factor}", flush=True)
+    out, ran = _run(s, "decoupled", "spectral", monkeypatch)
+    assert ran == (1, 0), ran
+    assert np.max(np.abs(out["im_sigma_dec"][0].cpu().numpy() - want) / bound) <= 8 * np.finfo(float).eps
+
+
 @pytest.mark.parametrize("case", [(4, 40, 160, 10), (5, 35, 160, 120), (8, 76, 330, 20), (8, 76, 330, 100), (9, 114, 491, 9),
                                   (10, 110, 480, 61)], ids=lambda c: f"ov{c[0] * c[1]}_points{c[3]}")
 def test_both_modes_take_one_route(case, monkeypatch):
