@@ -938,6 +938,12 @@ struct Spectral {
   std::vector<PendingTiming> pending;
   std::deque<std::vector<SpectralTask>> tasks;  // uploaded, kept until the call has synchronised
   explicit Spectral(hipStream_t s) : band(s), Ut(s), V(s), Vh(s), B(s), flag(s) {}
+  ~Spectral() {
+    for (PendingTiming &p : pending) {  // of a call that ended before it resolved them
+      (void)hipEventDestroy(p.a);
+      (void)hipEventDestroy(p.b);
+    }
+  }
 };
 
 struct SpectralSizes {
@@ -951,7 +957,7 @@ struct SpectralSizes {
 SpectralSizes spectral_sizes(const ResidentSystem &rs, int n_core, size_t residues, size_t budget) {
   // three rounds of the device's 1024 tasks at once (c2 FULL, 8421 tasks: 56 -> 54 ms
   // against two, by fuller products), and 16 GiB
-  constexpr size_t MOST = 3072, MOST_BYTES = size_t(16) << 30;
+  constexpr size_t MOST = 3072, FEWEST = 128, MOST_BYTES = size_t(16) << 30;
   SpectralSizes z;
   z.np = (int)round_up(rs.n_ov, SPECTRAL_BAND);
   z.pad = z.np - rs.n_ov;
@@ -971,7 +977,8 @@ SpectralSizes spectral_sizes(const ResidentSystem &rs, int n_core, size_t residu
   size_t T = std::max<size_t>(1, std::min(residues, MOST));
   while (T > 1 && (residue(T) > MOST_BYTES || kept + residue(T) > budget)) T -= (T + 7) / 8;
   z.bytes = kept + std::max(reduce, residue(T));
-  z.batch = z.bytes <= budget ? (int)T : 0;
+  // a launch of fewer than half a workgroup a CU would take as long as a full one
+  z.batch = z.bytes <= budget && T >= std::min(residues, FEWEST) ? (int)T : 0;
   return z;
 }
 

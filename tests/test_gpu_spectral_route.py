@@ -14,7 +14,7 @@ import pytest
 import paper_2412_17132_amd as gwc
 from oracle import sigma as OS
 from extended import dyadic_system, im_sigma_dec
-from workloads import system_from_config
+from workloads import CONFIGS, system_from_config
 from workloads.configs import small_config
 
 pytestmark = pytest.mark.gpu
@@ -132,6 +132,23 @@ def test_residues_are_as_exact_as_the_arithmetic_allows(shape, route, monkeypatc
     assert (ran[0] > 0, ran[1] > 0) == (route == "spectral", route == "ldlt"), ran
     got = out["im_sigma_dec"][0].cpu().numpy()
     assert np.max(np.abs(got - want) / bound) <= 8 * np.finfo(float).eps
+
+
+def test_residues_in_several_launches(monkeypatch):
+    """About 600 residue tasks of 0.11 MB: all at once, and in launches of some 250 and
+    150 with a ragged last one, bit for bit; a budget of fewer than 128 goes to the
+    Pi builds."""
+    s = system_from_config(CONFIGS["c1"])
+    print("case c1", flush=True)
+    want, ran = _run(s, "full", "spectral", monkeypatch)
+    assert ran == (1, 0)
+    for budget, reduced in ((32, True), (22, True), (9, False)):
+        monkeypatch.setenv("GWC_BATCH_BYTES", str(budget * 10 ** 6))
+        got, ran = _run(s, "full", "spectral", monkeypatch)
+        assert (ran[0] > 0, ran[1] > 0) == (reduced, not reduced), (budget, ran)
+        for k in want:
+            if reduced:
+                assert torch.equal(got[k], want[k]), (budget, k)
 
 
 @pytest.mark.parametrize("factor", [30.0, 300.0])
