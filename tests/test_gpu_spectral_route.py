@@ -134,6 +134,21 @@ def test_residues_are_as_exact_as_the_arithmetic_allows(shape, route, monkeypatc
     assert np.max(np.abs(got - want) / bound) <= 8 * np.finfo(float).eps
 
 
+@pytest.mark.parametrize("case", [(8, 896), (8, 899), (7, 1033), (10, 725)], ids=lambda c: f"ov{c[0] * c[1]}")
+def test_end_of_the_paired_panels(case, monkeypatch):
+    """Panels go in pairs while 7168 rows are left: orders with no pair, with one, with
+    one and a panel more above the limit, and with two, against the Pi builds."""
+    n_occ, n_virt = case
+    s = system_from_config(small_config(n_occ=n_occ, n_virt=n_virt, n_aux=50, n_core=1, n_imag=6, n_real=5, seed=n_virt))
+    print(f"case n_ov {n_occ * n_virt}", flush=True)
+    got, ran = _run(s, "decoupled", "spectral", monkeypatch)
+    assert ran == (1, 0), ran
+    want, ran = _run(s, "decoupled", "ldlt", monkeypatch)
+    assert ran[0] == 0 and ran[1] > 0, ran
+    for k in ("im_sigma_dec", "sigma_c_eps", "e_qp"):
+        assert torch.max(torch.abs(got[k] - want[k])) <= TOL * torch.max(torch.abs(want[k])), k
+
+
 def test_residues_in_several_launches(monkeypatch):
     """About 600 residue tasks of 0.11 MB: all at once, and in launches of some 250 and
     150 with a ragged last one, bit for bit; a budget of fewer than 128 goes to the
