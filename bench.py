@@ -656,8 +656,8 @@ def main():
     pi = gwc.timing_get(pi_name)
     fact_name, lu = FACT_TIMER, gwc.timing_get(FACT_TIMER)
     if args.precision == "fp64" and pi["launches"] == 0:
-        # the solves went by the reduced transition matrix: its reduction and
-        # the banded eliminations that give each W
+        # the solves went by the reduced transition matrix: its reduction, and the
+        # banded solutions and products that give each W
         pi_name, pi = "spectral_reduce", gwc.timing_get("spectral_reduce")
         fact_name, lu = "spectral_w", gwc.timing_get("spectral_w")
     gwc.timing_enable(False)
@@ -902,9 +902,10 @@ def main():
     def leg_peaks():
         return measure_peaks(gwc)
 
-    # a Pi build and factorisation at the benchmark's size (0.3 ms in FP64), scaled
-    # by the Pi-build work of a task (N_aux^2 N_ov), bounds the larger workloads'
-    # FP64 and precision-form solves for the wall-clock guard
+    # the time of a frequency, scaled by the Pi-build work of a task (N_aux^2 N_ov),
+    # estimates the larger workloads' FP64 and precision-form solves for the
+    # wall-clock guard: the timed one, and at least half of the 0.3 ms that a Pi
+    # build and its factorisation take in FP64 at the benchmark's size
     t_task = max(elapsed / max(n_tasks + args.steps * len(s.omega_imag), 1), 1.5e-4)
 
     def scaled(name, mode):

@@ -70,7 +70,11 @@ enum gwc_precision {
   GWC_PREC_FP16X3 = 2, /* same with fp16 and power-of-two column and frequency scaling */
   GWC_PREC_FP8 = 3     /* fp8 e4m3 hi*hi + hi*lo + lo*hi, fp32 accumulation, power-of-two column
                         * and frequency scaling aimed below the e4m3 limit (448); ~2^-7
-                        * relative per product, so ~1e-3 on Sigma^c: a throughput option */
+                        * relative per product, so ~1e-3 on Sigma^c.  The three forms
+                        * screen by Pi builds, each frequency by itself: against the
+                        * reduction that FP64 takes (gwc_sigma_args) they are faster where
+                        * the frequencies are few for the order n_occ n_virt (DECOUPLED
+                        * grids of large systems), and slower on FULL grids */
 };
 
 /* A closed-shell system in the RI representation.
@@ -142,7 +146,9 @@ typedef struct {
  *   precision  enum gwc_precision: the Pi builds (both axes) in that form; chi(z),
  *              the factorisation of 1 - Pi, the residue sums and E_QP stay FP64.
  *              FP64 without wac takes W from one reduction of the RPA matrix of
- *              the transitions instead where that is cheaper (same W to rounding)
+ *              the transitions instead where that is cheaper (as exact as by Pi builds;
+ *              which way a call goes depends on its sizes, grids and budget, not on
+ *              the mode or the number of core states)
  *   sym_group  [n_basis] or NULL  labels of symmetry-equivalent core levels
  *              (Eq. sigma_spectral_decoupled_symmetric): the equivalent set of a
  *              core state n is every orbital carrying n's label when that label
@@ -466,7 +472,9 @@ int gwc_server_destroy(gwc_server_handle server);
  * of launches and the algorithmic flop count of those launches (Pi build, in
  * either precision: 2 N_aux (N_aux + 1) N_ov per complex residue frequency,
  * half that on the imaginary axis; LU: (8/3) N^3 + 8 N^2 R per bordered N x N matrix with R
- * border vectors).  Returns GWC_ERR_INVALID_ARG for an unknown name. */
+ * border vectors; LDL^T half of that; the reduction: 4/3 N_ov^3 + 3 N_aux N_ov^2 + 2 N_aux N_ov
+ * per pair (core, m); W from the band: 32^2 N_ov per 16 vectors on the imaginary axis,
+ * (4 32^2 + 8 N_aux) N_ov per residue).  Returns GWC_ERR_INVALID_ARG for an unknown name. */
 int gwc_timing_enable(int on);
 int gwc_timing_get(const char *kernel, double *total_ms, long long *launches, double *flops);
 

@@ -34,7 +34,8 @@ std::string &last_error();
 size_t resident_bytes(const ResidentSystem &rs);
 
 // Self-energy of the requested core states on a resident system.  Batched
-// matrices of one launch use at most `batch_bytes` (0: min(48 GB, free / 2)).
+// matrices of one launch use at most `batch_bytes` (0: min(48 GB, free / 2)), the
+// reduced transition matrix as much (0: half of the device's memory).
 void run_sigma(ResidentSystem &rs, const gwc_sigma_args *args, gwc_sigma_out *out, hipStream_t s,
                size_t batch_bytes);
 

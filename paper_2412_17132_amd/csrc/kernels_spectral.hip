@@ -159,8 +159,16 @@ __device__ __forceinline__ double get_through(const double *p) {
 }
 
 // True in exactly one workgroup of `count`, the one that arrives last: what the
-// others wrote through is then in memory (every wave has waited for its stores
-// before the workgroup's arrival).  The ticket is left at 0.
+// others wrote through is then in memory.  The ticket is left at 0.
+// This relies on two properties of gfx950 rather than on the language's rule, which
+// would ask for a release and an acquire at agent scope around the ticket: an
+// agent-scope atomic store is issued with sc1, is performed at the point where the
+// device's XCDs agree, and leaves the wave's vmcnt only then, so that the wait for
+// 0 below, in every wave before the workgroup's barrier and thread 0's arrival, is
+// all that a release at that scope does for such stores (the rest of it writes
+// back other dirty lines of the L2, 2 us a launch here); and an agent-scope atomic
+// load (sc1) is served from there, past lines that the reader's caches still hold.
+// Only put_through and get_through may carry values across it.
 __device__ __forceinline__ bool last_arrival(int *ticket, int count, int *shared_flag) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_waitcnt(0);
@@ -644,7 +652,7 @@ panel_gram_kernel(const double *__restrict__ P, long long ldp, int m, PanelSmall
 // Q = P L1^-T, one row per thread, and the partial sums of Q^T Q; for a pair's
 // second panel also of Wa^T Q and Ya^T Q.  Latency: the panel and L1 are loaded
 // in one batch and L1's elements reach the rows' threads by DPP, from registers
-// (24 -> 10.7 us at 5859 rows; four batches and scalar loads of L1 before).
+// (24 -> 10.3 us at 5859 rows; four batches and scalar loads of L1 before).
 template <bool SECOND>
 __global__ void __launch_bounds__(PROWS)
 panel_q_kernel(const double *__restrict__ P, long long ldp, int m, const PanelSmall *__restrict__ sm,
@@ -1312,9 +1320,9 @@ spectral_transpose_kernel(const double *__restrict__ in, long long ldi, int rows
 // blockIdx.x of X, the elimination's W to W_out[blockIdx.x].  The way back reads
 // 8.4 KB a step, loaded a step ahead, and takes 15 dependent products of it.
 // Bound by the steps' chains where there are fewer tasks than fill the chip, by
-// instructions beyond that (order 5859, 1029 complex tasks: 5.1 -> 2.6 ms against
-// one wave a task that updated sixteen columns of vectors; 608 real tasks 1.15 ->
-// 0.83).
+// instructions beyond that (order 5859, 1024 complex tasks without the way back:
+// 5.1 -> 1.8 ms a round of the device against one wave a task that updated sixteen
+// columns of vectors, with it 2.6; 608 real tasks 1.15 -> 0.83).
 template <bool COMPLEX>
 __global__ void __launch_bounds__(128, COMPLEX ? 2 : 3)
 spectral_w_kernel(const double *__restrict__ band, const double *__restrict__ Ut, int np, int nb16,
