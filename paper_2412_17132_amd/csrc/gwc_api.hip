@@ -1034,8 +1034,10 @@ bool spectral_route(const ResidentSystem &rs, const gwc_sigma_args *args, size_t
   };
   const double t_reduce = 1e-4 + 77e-6 * std::ceil(n / SPECTRAL_BAND) + 4.6e-14 * n * n * n;
   // One route for both modes, so that they give the same digits: the reduction
-  // where FULL gains by it, unless DECOUPLED lost more than half its time.
-  return t_reduce < std::min(t_build((double)args->n_real * rs.no), 1.5 * t_build(args->n_real));
+  // where FULL gains by it, unless DECOUPLED took more than twice its time.  (The
+  // factor also keeps grids of few and of many points on one route: at n_ov = 16524
+  // with 2 to 400 points; 9 points DECOUPLED take 240 ms there, 154 by builds.)
+  return t_reduce < std::min(t_build((double)args->n_real * rs.no), 2.0 * t_build(args->n_real));
 }
 
 // Transitions by ascending Delta, and Delta in that order.
